@@ -538,6 +538,29 @@ tbpm_status Job::collect_profile()
     return TBPM_OK;
 }
 
+// Mode and coefficients of the pair of terms (m, m + 1) of a series of M terms
+// whose out holds the terms up to `held` (-1: nothing yet, out unwritten),
+// which is brought up to date.  A pair has terms m - 2 .. m + 1 of its rows at
+// hand, so it leaves out alone when the next one can still take what is missing.
+static int pair_mode(const double *c, int m, int M, int &held, PairArgs &pa)
+{
+    auto take = [&](int k, double &re, double &im) {
+        const bool due = k > held && k < M;
+        re = due ? c[2 * k] : 0.0;
+        im = due ? c[2 * k + 1] : 0.0;
+    };
+    take(m - 2, pa.cy_re, pa.cy_im);
+    take(m - 1, pa.cx_re, pa.cx_im);
+    take(m, pa.c0_re, pa.c0_im);
+    take(m + 1, pa.c1_re, pa.c1_im);
+    const bool last = m + 2 == M;
+    if (m + 2 < M && held + 1 >= m)
+        return PAIR_SKIP;
+    const int mode = last ? PAIR_LAST : held < 0 ? PAIR_SET : PAIR_MID;
+    held = m + 1;
+    return mode;
+}
+
 // O = sum_{m<M} c_m T_m(H/rho) P (see tbpm_engine.h).
 tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape &shape, bool pairs, bool clenshaw,
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
@@ -760,10 +783,14 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         return TBPM_OK;
     }
 
-    // term 1: Q = (1/rho) H P; O = c0 P + c1 Q (unless a previous launch formed them)
+    // term 1: Q = (1/rho) H P; O = c0 P + c1 Q (unless a previous launch formed
+    // Q).  An even number of further terms in pairs starts the series in the
+    // first pair, which holds P and Q, unless that pair is also the last.
+    const bool paired = pairs && (B == 1 || (!clenshaw && block_pairs(ham, B))) && M >= 4;
+    const bool late = paired && M % 2 == 0 && M >= 6;
     a.x = bf.P;
     a.y = bf.Q;
-    a.out = bf.O;
+    a.out = late ? nullptr : bf.O;
     if (!skip_first) {
         a.scale = 1.0 / rescale;
         a.ca_re = c[0];
@@ -777,8 +804,9 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
     if (prof && prof->ev[1])
         SER_HIP(hipEventRecord(prof->ev[1], st));
     a.scale = 2.0 / rescale;
+    a.out = bf.O;
     *nblk = shape.grid;
-    if (pairs && (B == 1 || (!clenshaw && block_pairs(ham, B))) && M >= 4) {
+    if (paired) {
         // terms m = 2..M-1 two at a time (one single term first when their number is odd)
         void *cx = bf.Q, *cy = bf.P, *sp1 = bf.S1, *sp2 = bf.S2;
         int m = 2;
@@ -812,12 +840,13 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         pa.vdiag_real = ham->vdiag_real;
         pa.ldh = ham->ldh;
         pa.out = bf.O;
-        pa.psi0 = psi0;
+        pa.psi0 = dots ? psi0 : nullptr;
         pa.scale = 2.0 / rescale;
         pa.scale_b = 2.0 / rescale;
         pa.partials = partials;
         pa.B = B;
         pa.max_halo = ham->max_halo;
+        int held = late ? -1 : m - 1;                   // the newest term O holds
         while (m < M) {                                 // an even number of terms remains
             const bool last = (m + 2 == M);
             if (prof && last && prof->ev[2])
@@ -826,11 +855,8 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
             pa.yin = cy;
             pa.yout = sp1;
             pa.xout = sp2;
-            pa.c0_re = c[2 * m];
-            pa.c0_im = c[2 * m + 1];
-            pa.c1_re = c[2 * m + 2];
-            pa.c1_im = c[2 * m + 3];
-            SER_HIP(launch_pair((last && dots) ? PAIR_LAST : PAIR_MID, ham->dtype, pa, ham->patch_rows, st));
+            const int mode = pair_mode(c, m, M, held, pa);
+            SER_HIP(launch_pair(mode, ham->dtype, pa, ham->patch_rows, st));
             if (prof)
                 prof->launches[last ? K_LAST : K_MID] += 1;
             void *ocx = cx, *ocy = cy;
@@ -915,6 +941,7 @@ tbpm_status apply_series_cross(const tbpm_ham *ham, hipStream_t st, const double
     };
     // terms 1 and 2: p_1 = (1/rho) H P to Q, p_2 = (2/rho) H p_1 - P to spare[0],
     // O = c_0 P + c_1 p_1 + c_2 p_2
+    int held = 2;
     pa.xin = P;
     pa.yin = P;                                      // not read
     pa.yout = Q;
@@ -922,9 +949,9 @@ tbpm_status apply_series_cross(const tbpm_ham *ham, hipStream_t st, const double
     pa.out = O;
     pa.scale = 1.0 / rescale;
     pa.scale_b = 2.0 / rescale;
-    coef(0, pa.c0_re, pa.c0_im);
-    coef(1, pa.c1_re, pa.c1_im);
-    coef(2, pa.c2_re, pa.c2_im);
+    coef(0, pa.cx_re, pa.cx_im);
+    coef(1, pa.c0_re, pa.c0_im);
+    coef(2, pa.c1_re, pa.c1_im);
     SER_HIP(launch_pair(PAIR_FIRST, ham->dtype, pa, ham->patch_rows, st));
     if (prof) {
         if (prof->ev[1])
@@ -940,9 +967,7 @@ tbpm_status apply_series_cross(const tbpm_ham *ham, hipStream_t st, const double
         pa.yin = cy;
         pa.yout = sp1;
         pa.xout = sp2;
-        coef(m, pa.c0_re, pa.c0_im);
-        coef(m + 1, pa.c1_re, pa.c1_im);
-        SER_HIP(launch_pair(PAIR_MID, ham->dtype, pa, ham->patch_rows, st));
+        SER_HIP(launch_pair(pair_mode(c, m, M, held, pa), ham->dtype, pa, ham->patch_rows, st));
         if (prof)
             prof->launches[K_MID] += 1;
         void *ocx = cx, *ocy = cy;
@@ -952,7 +977,8 @@ tbpm_status apply_series_cross(const tbpm_ham *ham, hipStream_t st, const double
         sp2 = ocy;
     }
     // term M-1 (x_{M-2} in cx, y_{M-3} in cy) and the next step's term 1, into
-    // three vectors none of this launch reads
+    // vectors none of this launch reads; the next step's first pair starts its
+    // series from psi and p_1
     void *fr[3] = {sp1, sp2, spare[2]};
     int ko = 0;
     for (int i = 0; i < 3; ++i)
@@ -966,12 +992,9 @@ tbpm_status apply_series_cross(const tbpm_ham *ham, hipStream_t st, const double
     pa.out = O;
     pa.yout = *Pn;
     pa.xout = *Qn;
-    pa.out2 = *On;
     pa.scale = 2.0 / rescale;
     pa.scale_b = 1.0 / rescale;
-    coef(M - 1, pa.c0_re, pa.c0_im);
-    coef(0, pa.c1_re, pa.c1_im);
-    coef(1, pa.c2_re, pa.c2_im);
+    pair_mode(c, M - 1, M, held, pa);                // cy, cx, c0 (the next step's p_1 is no term of this series)
     if (prof && prof->ev[2])
         SER_HIP(hipEventRecord(prof->ev[2], st));
     SER_HIP(launch_pair(PAIR_CROSS, ham->dtype, pa, ham->patch_rows, st));

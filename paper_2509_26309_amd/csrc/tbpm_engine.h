@@ -176,7 +176,7 @@ struct SeriesProfile {
 // `pairs`, B = 1, M >= 6 and two terms per pass).  dots: the last launch also writes the per-block partials of
 // <psi0|O> and <O|O> into `partials`; *nblk receives their count (-1: M = 2,
 // none written).  c: M complex coefficients (interleaved).
-// skip_first: term 1 (Q = (1/rho) H P, O = c_0 P + c_1 Q) is already in Q and O.
+// skip_first: term 1 (Q = (1/rho) H P) is already in Q (pairs, M even and at least 6).
 tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape &shape, bool pairs, bool clenshaw,
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
                          double *partials, int *nblk, SeriesProfile *prof, std::string &err,

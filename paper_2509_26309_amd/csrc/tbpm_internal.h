@@ -20,7 +20,7 @@ enum DevFmt { F_CSR = 0, F_ELL = 1 };
 
 // Arguments of one Chebyshev term (one application of H, fused with the
 // recurrence update and the coefficient accumulation).
-//   FIRST: y = scale*H x;          out = c_a * x + c_b * y
+//   FIRST: y = scale*H x;          out = c_a * x + c_b * y   (out null: not formed)
 //   MID:   y = scale*H x - y;      out = out + c_a * y
 //   LAST:  MID, then per-block partial sums of conj(psi0)*out and |out|^2
 // Chebyshev moments (no out, no coefficients):
@@ -107,7 +107,8 @@ hipError_t launch_unpack_state(int dtype, const void *src, double *dst, int64_t 
 // Two Chebyshev terms in one pass (patch-reordered ELL, one vector):
 //   y_m     = scale H x_{m-1} - y_{m-2}   (into yout, kept on chip for the patch + halo)
 //   x_{m+1} = scale H y_m - x_{m-1}       (into xout)
-//   out    += c_m y_m + c_{m+1} x_{m+1}   (LAST: + per-patch correlation partial sums)
+//   out    += c_{m-2} y_{m-2} + c_{m-1} x_{m-1} + c_m y_m + c_{m+1} x_{m+1}
+// (cy, cx, c0, c1; terms that out already holds have a zero coefficient)
 struct PairArgs {
     const uint64_t *lcol;    // patch-local column indices, 4 to a word [(w+3)/4][ld]: < cnt in the patch, else cnt + halo position
     const void *val;
@@ -124,8 +125,7 @@ struct PairArgs {
     const void *psi0;
     double scale;
     double c0_re, c0_im, c1_re, c1_im;
-    double c2_re, c2_im;     // FIRST, CROSS: the third coefficient
-    void *out2;              // CROSS: the next step's accumulated series
+    double cy_re, cy_im, cx_re, cx_im;   // forward modes: the coefficients of yin and xin
     double *partials;        // [npatch][4]
     double *partials2;       // PAIR_MOM: the second term's [npatch][4]
     // optional: only the patches plist[0..pcount) (partials still indexed by patch)
@@ -144,13 +144,15 @@ struct PairArgs {
     const void *vtab;
     const void *vdiag;
     int32_t vdiag_real;      // vdiag holds real parts only (double or float)
-    // complex64 blocks (bpair_kernel): B = 8 or 16 vectors, modes MID and LAST
+    // complex64 blocks (bpair_kernel): B = 8 or 16 vectors, modes MID, SKIP, SET and LAST
     // (partials [npatch][B][4]); 0 or 1: one vector.  max_halo: the largest
     // halo of a patch, in rows
     int32_t B;
     int32_t max_halo;
 };
-// pair modes: MID, LAST (+ correlation partials), MOM (moments: no out; with
+// pair modes: MID, SKIP (no out), SET (out written, not read), LAST (yout and
+// xout not written; with psi0, + per-patch correlation partial sums), MOM
+// (moments: no out; with
 // x = xin = p_m, partials = (<x|y>, <x|x>) and partials2 = (<y|z>, <y|y>) for
 // y = yout = p_m+1 and z = xout = p_m+2).
 // Clenshaw modes, for O = sum_m c_m T_m(H/rho) psi by the backward recurrence
@@ -165,13 +167,13 @@ struct PairArgs {
 // Forward modes that straddle time steps (one vector, dots):
 //   FIRST: terms 1 and 2 of a step from psi = xin (no yin, no out read):
 //          y = p_1 = scale H psi; x' = p_2 = scale_b H p_1 - psi;
-//          out = c0 psi + c1 p_1 + c2 p_2 (written, not read);
+//          out = cx psi + c0 p_1 + c1 p_2 (written, not read);
 //   CROSS: the last term of a step and term 1 of the next:
-//          psi' = out + c0 (scale H x - yin) for patch and halo rows (to yout
-//          for the patch rows, kept in LDS); x' = p_1' = scale_b H psi' (to
-//          xout); out2 = c1 psi' + c2 p_1'; partials of <psi0|psi'>, <psi'|psi'>.
+//          psi' = out + cy yin + cx xin + c0 (scale H x - yin) for patch and
+//          halo rows (to yout for the patch rows, kept in LDS); x' = p_1' =
+//          scale_b H psi' (to xout); partials of <psi0|psi'>, <psi'|psi'>.
 enum PairMode { PAIR_MID = 0, PAIR_LAST = 1, PAIR_MOM = 2, PAIR_CL = 3, PAIR_CL_LAST = 4, PAIR_CL_SINGLE = 5,
-                PAIR_CL_FIRST = 6, PAIR_FIRST = 7, PAIR_CROSS = 8 };
+                PAIR_CL_FIRST = 6, PAIR_FIRST = 7, PAIR_CROSS = 8, PAIR_SKIP = 9, PAIR_SET = 10 };
 constexpr int PAIR_WG = 1024;        // lanes per workgroup of the pair kernel
 // halo rows a patch may have: LDS holds y_m for (patch + halo) rows
 constexpr int pair_halo_max(int patch_rows) { return patch_rows > PAIR_WG ? 1024 : 2048; }

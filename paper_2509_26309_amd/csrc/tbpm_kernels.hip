@@ -174,7 +174,8 @@ __global__ __launch_bounds__(WG) void term_kernel(TermArgs a)
                     st_stream(E::from_d(cmul(ca, s) + cmul(cb, E::to_d(xo))), y + e);
                 } else {
                     st_stream(E::from_d(s), y + e);
-                    st_stream(E::from_d(cmul(ca, E::to_d(xo)) + cmul(cb, s)), out + e);
+                    if (out)
+                        st_stream(E::from_d(cmul(ca, E::to_d(xo)) + cmul(cb, s)), out + e);
                 }
             } else if (cl) {
                 const d2 yn = (use_y ? s - E::to_d(yo) : s) + cmul(ca, E::to_d(qo));
@@ -384,9 +385,11 @@ __device__ __forceinline__ void spmm2_update(d2 s0, d2 s1, f4 xo, f4 yo, f4 oo, 
             st_stream(join2(down(b0), down(b1)), yp);
         } else {
             st_stream(join2(down(s0), down(s1)), yp);
-            const d2 o0 = cmul(ca, up(lo2(xo))) + cmul(cb, s0);
-            const d2 o1 = cmul(ca, up(hi2(xo))) + cmul(cb, s1);
-            st_stream(join2(down(o0), down(o1)), op);
+            if (op) {
+                const d2 o0 = cmul(ca, up(lo2(xo))) + cmul(cb, s0);
+                const d2 o1 = cmul(ca, up(hi2(xo))) + cmul(cb, s1);
+                st_stream(join2(down(o0), down(o1)), op);
+            }
         }
     } else if (cl) {
         const d2 y0 = (use_y ? s0 - up(lo2(yo)) : s0) + cmul(ca, up(lo2(qo)));
@@ -527,7 +530,8 @@ __global__ __launch_bounds__(WG) void spmm2_kernel(TermArgs a)
         }
         if (live)
             spmm2_update<KIND>(up(acc0) * a.scale, up(acc1) * a.scale, xo, yo, oo, po, qo, ca, cb, cl, use_y,
-                               reinterpret_cast<f4 *>(y + e), reinterpret_cast<f4 *>(out + e), dre, dim, nrm);
+                               reinterpret_cast<f4 *>(y + e), out ? reinterpret_cast<f4 *>(out + e) : nullptr, dre, dim,
+                               nrm);
     }
     if constexpr (KIND == K_LAST || KIND == K_MOM0 || KIND == K_MOM) {
         // lanes with equal (lane mod LR) hold the same two vectors: fold them
@@ -847,7 +851,7 @@ __global__ __launch_bounds__(PSPMM_WG) void patch_spmm_kernel(TermArgs a)
 #pragma unroll
             for (int j = 0; j < NC; ++j)
                 spmm2_update<KIND>(up(acc[j][0]) * a.scale, up(acc[j][1]) * a.scale, xo[j], yo[j], oo[j], po[j], qo[j],
-                                   ca, cb, cl, use_y, y + e + j, out + e + j, dre[j], dim[j], nrm[j]);
+                                   ca, cb, cl, use_y, y + e + j, out ? out + e + j : nullptr, dre[j], dim[j], nrm[j]);
         }
     };
     for (int r0 = 0; r0 < cnt; r0 += 2 * ROWS) {
@@ -979,10 +983,14 @@ hipError_t launch_term(int kind, int dtype, int fmt, const TermArgs &a, const Ke
 //            stays in registers) and for the halo rows, into LDS; patch rows
 //            also to yout;
 //   phase B: x_{m+1} = scale H y_m - x_{m-1} for the patch rows, gathering y_m
-//            from LDS, then out += c_m y_m + c_{m+1} x_{m+1} (one update of
-//            out for two terms).
-// H is read once for two terms (plus the halo rows' H), out is touched once,
-// and y_m is not read back from HBM.  Inputs (x_{m-1}, y_{m-2}) and outputs
+//            from LDS.
+// The series out = sum_m c_m p_m takes its terms in every other pair: a pair
+// holds four of them for its rows (y_{m-2}, x_{m-1}, y_m, x_{m+1}), so MID adds
+// those of the pair before it too, and SKIP leaves out alone.  SET starts a
+// series (out written, not read), and LAST ends one: y_m stays on chip and
+// x_{m+1} is not stored, since nothing reads them after it.
+// H is read once for two terms (plus the halo rows' H), out is touched once
+// in four, and y_m is not read back from HBM.  Inputs (x_{m-1}, y_{m-2}) and outputs
 // (y_m, x_{m+1}) are different buffers, since a halo row of one patch is a
 // patch row of another.
 //
@@ -1004,6 +1012,8 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
     constexpr bool CL = MODE == PAIR_CL || CLL || CLS || first;   // Clenshaw: psi enters every phase, no out
     constexpr bool FST = MODE == PAIR_FIRST;             // terms 1 and 2 of a step: xin = psi, no yin, no out read
     constexpr bool CRS = MODE == PAIR_CROSS;             // the last term of a step and term 1 of the next
+    constexpr bool SKIP = MODE == PAIR_SKIP;             // no series terms
+    constexpr bool SET = MODE == PAIR_SET || FST;        // the series starts here: out is not read
     constexpr bool DOTS = LAST || MOM || CLL || CRS;
     constexpr int NV = MOM ? 6 : 3;                 // partial sums per workgroup
     using E = Elem<T>;
@@ -1041,7 +1051,8 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
     const d2 ka = d2{a.ka_re, a.ka_im};
     const d2 c0 = d2{a.c0_re, a.c0_im};
     const d2 c1 = d2{a.c1_re, a.c1_im};
-    const d2 c2 = d2{a.c2_re, a.c2_im};
+    const d2 cx = d2{a.cx_re, a.cx_im};
+    const d2 cy = d2{a.cy_re, a.cy_im};
 
     // the halo list maps local column indices >= cnt to rows
     for (int h = threadIdx.x; h < hc; h += NT)
@@ -1119,8 +1130,10 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
         } else if constexpr (FST) {
             ym[r] = E::acc_to_d(acc) * scale;       // p_1 = (1/rho) H psi
         } else if constexpr (CRS) {
-            // psi(t + dt) = out + c_{M-1} p_{M-1}, as stored (it starts the next step)
-            ym[r] = E::to_d(E::from_d(E::to_d(oo[r]) + cmul(c0, E::acc_to_d(acc) * scale - E::to_d(yo[r]))));
+            // psi(t + dt) = out + the last terms of the series, as stored (it starts the next step)
+            const d2 yd = E::to_d(yo[r]);
+            ym[r] = E::to_d(E::from_d(((E::to_d(oo[r]) + cmul(cy, yd)) + cmul(cx, E::to_d(xo[r]))) +
+                                      cmul(c0, E::acc_to_d(acc) * scale - yd)));
         } else {
             ym[r] = E::acc_to_d(acc) * scale - E::to_d(yo[r]);
         }
@@ -1131,7 +1144,7 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
             const T ys = E::from_d(ym[r]);
             if constexpr (!CLS)
                 ylds[li] = ys;
-            if constexpr (!CLL)                     // b_1 of a Clenshaw series stays on chip
+            if constexpr (!CLL && !LAST)            // the last pair's y_m stays on chip
                 st_stream(ys, yout + base + li);
         }
     }
@@ -1181,7 +1194,9 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
         } else if constexpr (FST) {
             ylds[cnt + h] = E::from_d(E::acc_to_d(acc) * scale);
         } else if constexpr (CRS) {
-            ylds[cnt + h] = E::from_d(E::to_d(out[rh]) + cmul(c0, E::acc_to_d(acc) * scale - E::to_d(yh)));
+            const d2 yd = E::to_d(yh);
+            ylds[cnt + h] = E::from_d(((E::to_d(out[rh]) + cmul(cy, yd)) + cmul(cx, E::to_d(xin[rh]))) +
+                                      cmul(c0, E::acc_to_d(acc) * scale - yd));
         } else {
             ylds[cnt + h] = E::from_d(E::acc_to_d(acc) * scale - E::to_d(yh));
         }
@@ -1216,13 +1231,11 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
                 xn = E::acc_to_d(acc) * sb - E::to_d(xo[r]);
             }
             const T xs = E::from_d(xn);
-            st_stream(xs, xout + row);
-            if constexpr (FST) {                    // out = c_0 psi + c_1 p_1 + c_2 p_2
-                st_stream(E::from_d((cmul(c0, E::to_d(xo[r])) + cmul(c1, ym[r])) + cmul(c2, xn)), out + row);
+            if constexpr (!LAST)
+                st_stream(xs, xout + row);
+            if constexpr (SKIP)
                 continue;
-            }
-            if constexpr (CRS) {                    // next step's out = c_0 psi + c_1 p_1; sums of psi
-                st_stream(E::from_d(cmul(c1, ym[r]) + cmul(c2, xn)), static_cast<T *>(a.out2) + row);
+            if constexpr (CRS) {                    // sums of psi(t + dt)
                 const d2 p = E::to_d(ld_stream(static_cast<const T *>(a.psi0) + row));
                 const d2 o = ym[r];
                 sum[0] += p.x * o.x + p.y * o.y;
@@ -1250,10 +1263,18 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
                 sum[5] += yd.x * yd.x + yd.y * yd.y;
                 continue;
             }
-            const d2 on = (E::to_d(ld_stream(out + row)) + cmul(c0, ym[r])) + cmul(c1, xn);
+            // the series' terms of the pair's rows, oldest first
+            d2 on = cmul(cx, E::to_d(xo[r]));
+            if constexpr (!FST)
+                on = cmul(cy, E::to_d(yo[r])) + on;
+            if constexpr (!SET)
+                on = E::to_d(ld_stream(out + row)) + on;
+            on = (on + cmul(c0, ym[r])) + cmul(c1, xn);
             const T os = E::from_d(on);
             st_stream(os, out + row);
             if constexpr (LAST) {
+                if (!a.psi0)                        // a series without correlation sums
+                    continue;
                 const d2 p = E::to_d(ld_stream(static_cast<const T *>(a.psi0) + row));
                 const d2 o = E::to_d(os);
                 sum[0] += p.x * o.x + p.y * o.y;
@@ -1263,6 +1284,8 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
         }
     }
     if constexpr (DOTS) {
+        if (LAST && !a.psi0)
+            return;                                 // uniform
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
 #pragma unroll
@@ -1342,6 +1365,12 @@ static hipError_t launch_pair_w(int mode, const PairArgs &a, hipStream_t st)
         break;
     case PAIR_CROSS:
         hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_CROSS, DICT>), dim3(g), dim3(NT), 0, st, a);
+        break;
+    case PAIR_SKIP:
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_SKIP, DICT>), dim3(g), dim3(NT), 0, st, a);
+        break;
+    case PAIR_SET:
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_SET, DICT>), dim3(g), dim3(NT), 0, st, a);
         break;
     default:
         hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_MID, DICT>), dim3(g), dim3(NT), 0, st, a);
@@ -1445,6 +1474,11 @@ template <int B, int W, int MODE, bool DICT>
 __global__ __launch_bounds__(BP_PASS * BP_VG / 2) __attribute__((amdgpu_waves_per_eu(4))) void bpair_kernel(PairArgs a)
 {
     constexpr bool LAST = MODE == PAIR_LAST;
+    constexpr bool SKIP = MODE == PAIR_SKIP;       // no series terms
+    constexpr bool SET = MODE == PAIR_SET;         // the series starts here: out is not read
+    // y_{m-2} of the lane's rows is read again for the series where holding it
+    // through phase B spills registers
+    constexpr bool REREAD_Y = !SKIP && (LAST || W >= 8);
     constexpr int LR = BP_VG / 2;          // lanes per row (two vectors each)
     constexpr int NT = BP_PASS * LR;       // lanes per workgroup
     constexpr int GR = B / BP_VG;          // vector groups per patch
@@ -1483,6 +1517,8 @@ __global__ __launch_bounds__(BP_PASS * BP_VG / 2) __attribute__((amdgpu_waves_pe
     const double scale = a.scale;
     const d2 c0 = d2{a.c0_re, a.c0_im};
     const d2 c1 = d2{a.c1_re, a.c1_im};
+    const d2 cx = d2{a.cx_re, a.cx_im};
+    const d2 cy = d2{a.cy_re, a.cy_im};
 
     auto load_row = [&](int p, H &h) {
         const int64_t row = pbase + min(p * BP_PASS + rl, cnt - 1);
@@ -1653,13 +1689,14 @@ __global__ __launch_bounds__(BP_PASS * BP_VG / 2) __attribute__((amdgpu_waves_pe
         const d2 y1 = up(acc1) * scale - up(hi2(yo[p]));
         yk[p] = join2(down(y0), down(y1));
         if (li < cnt)
-            st_shared(yk[p], yout + e);
+            st_shared(yk[p], yout + e);            // (LAST too: without this store its passes merge and spill)
     }
     // out of the lane's rows, for phase B (loaded while the barriers wait)
     f4 oo[BP_NP];
 #pragma unroll
     for (int p = 0; p < BP_NP; ++p)
-        oo[p] = ld_shared(out + (pbase + min(p * BP_PASS + rl, cnt - 1)) * RC + ch);
+        if constexpr (!SKIP && !SET)
+            oo[p] = ld_shared(out + (pbase + min(p * BP_PASS + rl, cnt - 1)) * RC + ch);
     __syncthreads();                               // every gather of the staged x done
     // y_m takes the place of x_{m-1}; the lane's own x_{m-1} stays for phase B
     f4 xk[BP_NP];
@@ -1699,10 +1736,21 @@ __global__ __launch_bounds__(BP_PASS * BP_VG / 2) __attribute__((amdgpu_waves_pe
         }
         const d2 xn0 = up(acc0) * a.scale_b - up(lo2(xk[p]));
         const d2 xn1 = up(acc1) * a.scale_b - up(hi2(xk[p]));
-        const f2 os0 = down((up(lo2(oo[p])) + cmul(c0, up(lo2(yk[p])))) + cmul(c1, xn0));
-        const f2 os1 = down((up(hi2(oo[p])) + cmul(c0, up(hi2(yk[p])))) + cmul(c1, xn1));
-        if (li < cnt) {
+        if (!LAST && li < cnt)
             st_shared(join2(down(xn0), down(xn1)), xout + e);
+        if constexpr (SKIP)
+            continue;
+        // the series' terms of the lane's row, oldest first
+        const f4 yp = REREAD_Y ? ld_shared(yin + e) : yo[p];
+        d2 on0 = cmul(cy, up(lo2(yp))) + cmul(cx, up(lo2(xk[p])));
+        d2 on1 = cmul(cy, up(hi2(yp))) + cmul(cx, up(hi2(xk[p])));
+        if constexpr (!SET) {
+            on0 = up(lo2(oo[p])) + on0;
+            on1 = up(hi2(oo[p])) + on1;
+        }
+        const f2 os0 = down((on0 + cmul(c0, up(lo2(yk[p])))) + cmul(c1, xn0));
+        const f2 os1 = down((on1 + cmul(c0, up(hi2(yk[p])))) + cmul(c1, xn1));
+        if (li < cnt) {
             st_shared(join2(os0, os1), out + e);
             if constexpr (LAST) {
                 const f4 pv = ld_shared(static_cast<const f4 *>(a.psi0) + e);
@@ -1763,10 +1811,20 @@ static hipError_t launch_bpair_w(int mode, const PairArgs &a, hipStream_t st)
     const int64_t per = (a.npatch + NXCD - 1) / NXCD;
     const dim3 grid((unsigned)(per * (B / BP_VG) * NXCD));
     const dim3 block(BP_PASS * BP_VG / 2);
-    if (mode == PAIR_LAST)
+    switch (mode) {
+    case PAIR_LAST:
         hipLaunchKernelGGL((bpair_kernel<B, W, PAIR_LAST, DICT>), grid, block, 0, st, a);
-    else
+        break;
+    case PAIR_SKIP:
+        hipLaunchKernelGGL((bpair_kernel<B, W, PAIR_SKIP, DICT>), grid, block, 0, st, a);
+        break;
+    case PAIR_SET:
+        hipLaunchKernelGGL((bpair_kernel<B, W, PAIR_SET, DICT>), grid, block, 0, st, a);
+        break;
+    default:
         hipLaunchKernelGGL((bpair_kernel<B, W, PAIR_MID, DICT>), grid, block, 0, st, a);
+        break;
+    }
     return hipGetLastError();
 }
 
@@ -1791,7 +1849,7 @@ bool bpair_supported(int dtype, int B, int w, int patch_rows, int max_halo)
 
 static hipError_t launch_bpair(int mode, int dtype, const PairArgs &a, int patch_rows, hipStream_t st)
 {
-    if (!bpair_supported(dtype, a.B, a.w, patch_rows, a.max_halo) || (mode != PAIR_MID && mode != PAIR_LAST) ||
+    if (!bpair_supported(dtype, a.B, a.w, patch_rows, a.max_halo) || (mode != PAIR_MID && mode != PAIR_LAST && mode != PAIR_SKIP && mode != PAIR_SET) ||
         a.plist || !a.hcol || (mode == PAIR_LAST && (!a.psi0 || !a.partials)))
         return hipErrorInvalidValue;
     const bool dict = a.vidx && a.hvidx && a.vtab;
@@ -1804,8 +1862,9 @@ hipError_t launch_pair(int mode, int dtype, const PairArgs &a, int patch_rows, h
 {
     if (a.B > 1)
         return launch_bpair(mode, dtype, a, patch_rows, st);
-    if (!pair_supported(a.w, patch_rows) || !a.lcol || a.npatch <= 0 || mode < PAIR_MID || mode > PAIR_CROSS ||
-        (mode == PAIR_CROSS && (!a.out2 || !a.partials || !a.psi0)) ||
+    if (!pair_supported(a.w, patch_rows) || !a.lcol || a.npatch <= 0 || mode < PAIR_MID || mode > PAIR_SET ||
+        (mode == PAIR_CROSS && (!a.out || !a.partials || !a.psi0)) ||
+        (mode == PAIR_LAST && a.psi0 && !a.partials) ||
         (mode == PAIR_MOM && !a.partials2) || (a.plist && (a.pcount <= 0 || a.pcount > a.npatch)))
         return hipErrorInvalidValue;
     const bool cl = mode >= PAIR_CL && mode <= PAIR_CL_FIRST;
