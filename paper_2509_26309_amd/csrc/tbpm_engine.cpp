@@ -561,6 +561,25 @@ static int pair_mode(const double *c, int m, int M, int &held, PairArgs &pa)
     return mode;
 }
 
+// The same for the single term m, which has terms m - 2 .. m at hand.
+static int term_kind(const double *c, int m, int M, int &held, bool last_sums, TermArgs &a)
+{
+    auto take = [&](int k, double &re, double &im) {
+        const bool due = k > held;
+        re = due ? c[2 * k] : 0.0;
+        im = due ? c[2 * k + 1] : 0.0;
+    };
+    take(m - 2, a.cc_re, a.cc_im);
+    take(m - 1, a.cb_re, a.cb_im);
+    take(m, a.ca_re, a.ca_im);
+    const bool last = m == M - 1;
+    if (!last && held + 2 >= m)
+        return K_SKIP;
+    const int kind = last && last_sums ? K_LAST : held < 0 ? K_SET : K_MID;
+    held = m;
+    return kind;
+}
+
 // O = sum_{m<M} c_m T_m(H/rho) P (see tbpm_engine.h).
 tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape &shape, bool pairs, bool clenshaw,
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
@@ -783,11 +802,12 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         return TBPM_OK;
     }
 
-    // term 1: Q = (1/rho) H P; O = c0 P + c1 Q (unless a previous launch formed
-    // Q).  An even number of further terms in pairs starts the series in the
-    // first pair, which holds P and Q, unless that pair is also the last.
+    // term 1: Q = (1/rho) H P (unless a previous launch formed it).  The series
+    // starts in the launch after it, which has P and Q at hand, or here (O = c0
+    // P + c1 Q) where that launch is also the last.
     const bool paired = pairs && (B == 1 || (!clenshaw && block_pairs(ham, B))) && M >= 4;
-    const bool late = paired && M % 2 == 0 && M >= 6;
+    const bool late = M >= (paired && M % 2 == 0 ? 6 : 4);
+    int held = late ? -1 : 1;                           // the newest term O holds
     a.x = bf.P;
     a.y = bf.Q;
     a.out = late ? nullptr : bf.O;
@@ -813,9 +833,8 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         if ((M - 2) % 2 == 1) {
             a.x = cx;
             a.y = cy;
-            a.ca_re = c[2 * m];
-            a.ca_im = c[2 * m + 1];
-            SER_HIP(launch_term(K_MID, ham->dtype, fmt, a, shape, st));
+            const int kind = term_kind(c, m, M, held, false, a);
+            SER_HIP(launch_term(kind, ham->dtype, fmt, a, shape, st));
             if (prof)
                 prof->launches[K_MID] += 1;
             std::swap(cx, cy);
@@ -846,7 +865,6 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         pa.partials = partials;
         pa.B = B;
         pa.max_halo = ham->max_halo;
-        int held = late ? -1 : m - 1;                   // the newest term O holds
         while (m < M) {                                 // an even number of terms remains
             const bool last = (m + 2 == M);
             if (prof && last && prof->ev[2])
@@ -871,17 +889,16 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         *nblk = (int)ham->npatch;
         return TBPM_OK;
     }
-    // terms m = 2..M-1: Y = (2/rho) H X - Y; O += c_m Y
+    // terms m = 2..M-1: Y = (2/rho) H X - Y, three of them into O at a time
     void *X = bf.Q, *Y = bf.P;
     for (int m = 2; m < M; ++m) {
         a.x = X;
         a.y = Y;
-        a.ca_re = c[2 * m];
-        a.ca_im = c[2 * m + 1];
         const bool last = (m == M - 1);
         if (prof && last && prof->ev[2])
             SER_HIP(hipEventRecord(prof->ev[2], st));
-        SER_HIP(launch_term(last ? kind_last : K_MID, ham->dtype, fmt, a, shape, st));
+        const int kind = term_kind(c, m, M, held, dots, a);
+        SER_HIP(launch_term(kind, ham->dtype, fmt, a, shape, st));
         if (prof)
             prof->launches[last ? K_LAST : K_MID] += 1;
         std::swap(X, Y);

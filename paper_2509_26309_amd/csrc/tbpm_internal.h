@@ -15,14 +15,16 @@
 
 namespace tbpm {
 
-enum Kind { K_FIRST = 0, K_MID = 1, K_LAST = 2, K_MOM0 = 3, K_MOM = 4 };
+enum Kind { K_FIRST = 0, K_MID = 1, K_LAST = 2, K_MOM0 = 3, K_MOM = 4, K_SKIP = 5, K_SET = 6 };
 enum DevFmt { F_CSR = 0, F_ELL = 1 };
 
 // Arguments of one Chebyshev term (one application of H, fused with the
 // recurrence update and the coefficient accumulation).
 //   FIRST: y = scale*H x;          out = c_a * x + c_b * y   (out null: not formed)
-//   MID:   y = scale*H x - y;      out = out + c_a * y
-//   LAST:  MID, then per-block partial sums of conj(psi0)*out and |out|^2
+//   MID:   y' = scale*H x - y;     out = out + c_c * y + c_b * x + c_a * y'
+//   SET:   MID with out written, not read
+//   SKIP:  y' alone
+//   LAST:  MID without storing y', then per-block partial sums of conj(psi0)*out and |out|^2
 // Chebyshev moments (no out, no coefficients):
 //   MOM0:  y = scale*H x;          partial sums of conj(x)*y and |x|^2
 //   MOM:   y = scale*H x - y;      the same partial sums with the new y
@@ -46,6 +48,7 @@ struct TermArgs {
     double scale;
     double ca_re, ca_im;
     double cb_re, cb_im;
+    double cc_re, cc_im;
     double *partials;        // [grid][B][4] (LAST, MOM0, MOM)
     // optional: process only the rows of the patches plist[0..pcount) of a
     // patch-reordered H (patch q: rows patch_ptr[q] .. patch_ptr[q+1]-1, at most

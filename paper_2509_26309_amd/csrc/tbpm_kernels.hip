@@ -2,7 +2,9 @@
 //
 // The hot kernel is one Chebyshev term (TBPLaS 2.0, "Migration to C++"): the
 // sparse product with H fused with the three-term recurrence y <- 2(H/rho)x - y
-// and the coefficient accumulation out <- out + c_m y.  The work is bound by
+// and, in every third launch, the accumulation of three terms into out (a
+// launch has y before and after, and x, of its rows at hand; accumulating each
+// term by itself moved 5 vector passes a term against 11/3).  The work is bound by
 // HBM bandwidth (about 0.3 flop per byte), so the kernels use no matrix cores:
 // they stream H once per term with non-temporal loads, gather x through L2,
 // and touch each vector element once.
@@ -60,6 +62,7 @@ __global__ __launch_bounds__(WG) void term_kernel(TermArgs a)
     const d2 ca = d2{a.ca_re, a.ca_im};
     const d2 cb = d2{a.cb_re, a.cb_im};
     const bool owner = (B > 1) || (lr == 0);
+    const d2 cc = d2{a.cc_re, a.cc_im};
     // Clenshaw (FIRST / MID / LAST kinds): no out; psi enters with c_a (c_b in FIRST)
     constexpr bool CLK = KIND == K_FIRST || KIND == K_MID || KIND == K_LAST;
     const bool cl = CLK && a.cl != 0;
@@ -94,10 +97,16 @@ __global__ __launch_bounds__(WG) void term_kernel(TermArgs a)
             } else {
                 if (use_y)
                     yo = ld_stream(y + e);
-                if (cl)
-                    qo = ld_stream(psi + e);
-                else
-                    oo = ld_stream(out + e);
+                if constexpr (KIND == K_SET) {
+                    xo = x[e];
+                } else if constexpr (KIND != K_SKIP) {
+                    if (cl) {
+                        qo = ld_stream(psi + e);
+                    } else {
+                        oo = ld_stream(out + e);
+                        xo = x[e];
+                    }
+                }
                 if constexpr (KIND == K_LAST)
                     po = ld_stream(psi0 + e);
             }
@@ -188,10 +197,17 @@ __global__ __launch_bounds__(WG) void term_kernel(TermArgs a)
                     dim += p.x * o.y - p.y * o.x;
                     nrm += o.x * o.x + o.y * o.y;
                 }
+            } else if constexpr (KIND == K_SKIP) {
+                st_stream(E::from_d(s - E::to_d(yo)), y + e);
             } else {
                 const d2 yn = s - E::to_d(yo);
-                st_stream(E::from_d(yn), y + e);
-                const T os = E::from_d(E::to_d(oo) + cmul(ca, yn));
+                if constexpr (KIND != K_LAST)       // nothing reads the last term
+                    st_stream(E::from_d(yn), y + e);
+                // the series' terms at hand, oldest first
+                d2 on = cmul(cc, E::to_d(yo)) + cmul(cb, E::to_d(xo));
+                if constexpr (KIND != K_SET)
+                    on = E::to_d(oo) + on;
+                const T os = E::from_d(on + cmul(ca, yn));
                 st_stream(os, out + e);
                 if constexpr (KIND == K_LAST) {
                     const d2 p = E::to_d(po);
@@ -265,6 +281,12 @@ static hipError_t launch_kind(int kind, const TermArgs &a, int grid, hipStream_t
         break;
     case K_MID:
         hipLaunchKernelGGL((term_kernel<T, FMT, B, LR, K_MID, W>), dim3(grid), dim3(WG), 0, st, a);
+        break;
+    case K_SKIP:
+        hipLaunchKernelGGL((term_kernel<T, FMT, B, LR, K_SKIP, W>), dim3(grid), dim3(WG), 0, st, a);
+        break;
+    case K_SET:
+        hipLaunchKernelGGL((term_kernel<T, FMT, B, LR, K_SET, W>), dim3(grid), dim3(WG), 0, st, a);
         break;
     case K_MOM0:
         hipLaunchKernelGGL((term_kernel<T, FMT, B, LR, K_MOM0, W>), dim3(grid), dim3(WG), 0, st, a);
@@ -361,8 +383,8 @@ __device__ __forceinline__ f2 down(d2 v) { return f2{(float)v.x, (float)v.y}; }
 // the row's x, y, out, psi0 and psi operands as loaded for KIND; yp, op the
 // row's y and out (two vectors each); dots accumulate into dre/dim/nrm.
 template <int KIND>
-__device__ __forceinline__ void spmm2_update(d2 s0, d2 s1, f4 xo, f4 yo, f4 oo, f4 po, f4 qo, d2 ca, d2 cb, bool cl,
-                                             bool use_y, f4 *yp, f4 *op, double (&dre)[2], double (&dim)[2],
+__device__ __forceinline__ void spmm2_update(d2 s0, d2 s1, f4 xo, f4 yo, f4 oo, f4 po, f4 qo, d2 ca, d2 cb, d2 cc,
+                                             bool cl, bool use_y, f4 *yp, f4 *op, double (&dre)[2], double (&dim)[2],
                                              double (&nrm)[2])
 {
     if constexpr (KIND == K_MOM0 || KIND == K_MOM) {
@@ -407,11 +429,21 @@ __device__ __forceinline__ void spmm2_update(d2 s0, d2 s1, f4 xo, f4 yo, f4 oo, 
                 nrm[q] += o.x * o.x + o.y * o.y;
             }
         }
+    } else if constexpr (KIND == K_SKIP) {
+        st_stream(join2(down(s0 - up(lo2(yo))), down(s1 - up(hi2(yo)))), yp);
     } else {
         const d2 y0 = s0 - up(lo2(yo)), y1 = s1 - up(hi2(yo));
-        st_stream(join2(down(y0), down(y1)), yp);
-        const f2 os0 = down(up(lo2(oo)) + cmul(ca, y0));
-        const f2 os1 = down(up(hi2(oo)) + cmul(ca, y1));
+        if constexpr (KIND != K_LAST)               // nothing reads the last term
+            st_stream(join2(down(y0), down(y1)), yp);
+        // the series' terms at hand, oldest first
+        d2 o0 = cmul(cc, up(lo2(yo))) + cmul(cb, up(lo2(xo)));
+        d2 o1 = cmul(cc, up(hi2(yo))) + cmul(cb, up(hi2(xo)));
+        if constexpr (KIND != K_SET) {
+            o0 = up(lo2(oo)) + o0;
+            o1 = up(hi2(oo)) + o1;
+        }
+        const f2 os0 = down(o0 + cmul(ca, y0));
+        const f2 os1 = down(o1 + cmul(ca, y1));
         st_stream(join2(os0, os1), op);
         if constexpr (KIND == K_LAST) {
             const f2 os[2] = {os0, os1};
@@ -445,6 +477,7 @@ __global__ __launch_bounds__(WG) void spmm2_kernel(TermArgs a)
     const int32_t *__restrict__ col = a.col;
     const d2 ca = d2{a.ca_re, a.ca_im};
     const d2 cb = d2{a.cb_re, a.cb_im};
+    const d2 cc = d2{a.cc_re, a.cc_im};
     constexpr bool CLK = KIND == K_FIRST || KIND == K_MID || KIND == K_LAST;
     const bool cl = CLK && a.cl != 0;                  // Clenshaw, as in term_kernel
     const bool use_y = !cl || a.no_y == 0;
@@ -474,10 +507,16 @@ __global__ __launch_bounds__(WG) void spmm2_kernel(TermArgs a)
         } else {
             if (use_y)
                 yo = ld_stream(reinterpret_cast<const f4 *>(y + e));
-            if (cl)
-                qo = ld_stream(reinterpret_cast<const f4 *>(psi + e));
-            else
-                oo = ld_stream(reinterpret_cast<const f4 *>(out + e));
+            if constexpr (KIND == K_SET) {
+                xo = *reinterpret_cast<const f4 *>(x + e);
+            } else if constexpr (KIND != K_SKIP) {
+                if (cl) {
+                    qo = ld_stream(reinterpret_cast<const f4 *>(psi + e));
+                } else {
+                    oo = ld_stream(reinterpret_cast<const f4 *>(out + e));
+                    xo = *reinterpret_cast<const f4 *>(x + e);
+                }
+            }
             if constexpr (KIND == K_LAST)
                 po = ld_stream(reinterpret_cast<const f4 *>(psi0 + e));
         }
@@ -529,7 +568,7 @@ __global__ __launch_bounds__(WG) void spmm2_kernel(TermArgs a)
             }
         }
         if (live)
-            spmm2_update<KIND>(up(acc0) * a.scale, up(acc1) * a.scale, xo, yo, oo, po, qo, ca, cb, cl, use_y,
+            spmm2_update<KIND>(up(acc0) * a.scale, up(acc1) * a.scale, xo, yo, oo, po, qo, ca, cb, cc, cl, use_y,
                                reinterpret_cast<f4 *>(y + e), out ? reinterpret_cast<f4 *>(out + e) : nullptr, dre, dim,
                                nrm);
     }
@@ -581,6 +620,12 @@ static hipError_t launch_spmm2_kind(int kind, const TermArgs &a, int grid, hipSt
         break;
     case K_MID:
         hipLaunchKernelGGL((spmm2_kernel<FMT, B, K_MID, W>), dim3(grid), dim3(WG), 0, st, a);
+        break;
+    case K_SKIP:
+        hipLaunchKernelGGL((spmm2_kernel<FMT, B, K_SKIP, W>), dim3(grid), dim3(WG), 0, st, a);
+        break;
+    case K_SET:
+        hipLaunchKernelGGL((spmm2_kernel<FMT, B, K_SET, W>), dim3(grid), dim3(WG), 0, st, a);
         break;
     case K_MOM0:
         hipLaunchKernelGGL((spmm2_kernel<FMT, B, K_MOM0, W>), dim3(grid), dim3(WG), 0, st, a);
@@ -686,6 +731,7 @@ __global__ __launch_bounds__(PSPMM_WG) void patch_spmm_kernel(TermArgs a)
     constexpr int TROWS = pspmm_rows(B);       // rows staged per workgroup
     constexpr int NSUB = pspmm_nsub(B);
     constexpr bool DOTS = KIND == K_LAST || KIND == K_MOM0 || KIND == K_MOM;
+    constexpr bool LATE_PSI = KIND == K_LAST && W >= 12;   // held from the start it costs a wave per SIMD
     __shared__ f4 xs[TROWS * RC];              // x of the run's rows, [row][RC]
     __shared__ f2 vtab[DICT ? 256 : 1];        // value table (DICT: H entries are one-byte indices)
     __shared__ int32_t hrow[PSPMM_HMAX];       // the patch's halo rows (local columns >= the patch's rows)
@@ -713,6 +759,7 @@ __global__ __launch_bounds__(PSPMM_WG) void patch_spmm_kernel(TermArgs a)
     const f4 *__restrict__ psi = static_cast<const f4 *>(a.psi);
     const d2 ca = d2{a.ca_re, a.ca_im};
     const d2 cb = d2{a.cb_re, a.cb_im};
+    const d2 cc = d2{a.cc_re, a.cc_im};
     constexpr bool CLK = KIND == K_FIRST || KIND == K_MID || KIND == K_LAST;
     const bool cl = CLK && a.cl != 0;
     const bool use_y = !cl || a.no_y == 0;
@@ -810,10 +857,12 @@ __global__ __launch_bounds__(PSPMM_WG) void patch_spmm_kernel(TermArgs a)
                 yo[j] = ld_stream(y + e + j);
             } else {
                 yo[j] = ld_stream(src_y + e + j);
-                const f4 o = ld_stream(src_o + e + j);
-                qo[j] = o;
-                oo[j] = o;
-                if constexpr (KIND == K_LAST)
+                if constexpr (KIND != K_SKIP && KIND != K_SET) {
+                    const f4 o = ld_stream(src_o + e + j);
+                    qo[j] = o;
+                    oo[j] = o;
+                }
+                if constexpr (KIND == K_LAST && !LATE_PSI)
                     po[j] = ld_stream(psi0 + e + j);
             }
         }
@@ -847,11 +896,21 @@ __global__ __launch_bounds__(PSPMM_WG) void patch_spmm_kernel(TermArgs a)
                 cmac(acc[j][1], vg, hi2(xv));
             }
         }
+        if constexpr (KIND == K_MID || KIND == K_SET || KIND == K_LAST) {
+            // x of the row for the series, read last (registers)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                xo[j] = xs[lic * RC + c0 + j];
+                if constexpr (LATE_PSI)
+                    po[j] = ld_stream(psi0 + e + j);
+            }
+        }
         if (live) {
 #pragma unroll
             for (int j = 0; j < NC; ++j)
                 spmm2_update<KIND>(up(acc[j][0]) * a.scale, up(acc[j][1]) * a.scale, xo[j], yo[j], oo[j], po[j], qo[j],
-                                   ca, cb, cl, use_y, y + e + j, out ? out + e + j : nullptr, dre[j], dim[j], nrm[j]);
+                                   ca, cb, cc, cl, use_y, y + e + j, out ? out + e + j : nullptr, dre[j], dim[j], nrm[j]);
         }
     };
     for (int r0 = 0; r0 < cnt; r0 += 2 * ROWS) {
@@ -917,6 +976,12 @@ static hipError_t launch_patch_spmm_w(int kind, const TermArgs &a, hipStream_t s
         break;
     case K_MID:
         hipLaunchKernelGGL((patch_spmm_kernel<B, K_MID, W, DICT>), grid, dim3(PSPMM_WG), 0, st, a);
+        break;
+    case K_SKIP:
+        hipLaunchKernelGGL((patch_spmm_kernel<B, K_SKIP, W, DICT>), grid, dim3(PSPMM_WG), 0, st, a);
+        break;
+    case K_SET:
+        hipLaunchKernelGGL((patch_spmm_kernel<B, K_SET, W, DICT>), grid, dim3(PSPMM_WG), 0, st, a);
         break;
     case K_MOM0:
         hipLaunchKernelGGL((patch_spmm_kernel<B, K_MOM0, W, DICT>), grid, dim3(PSPMM_WG), 0, st, a);
