@@ -646,6 +646,7 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         pa.patch_ptr = ham->patch_ptr;
         pa.halo_ptr = ham->halo_ptr;
         pa.halo_rows = ham->halo_rows;
+        pa.max_halo = ham->max_halo;
         pa.hcol = ham->hcol;
         pa.hval = ham->hval;
         pa.vidx = ham->vidx;
@@ -850,6 +851,7 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         pa.patch_ptr = ham->patch_ptr;
         pa.halo_ptr = ham->halo_ptr;
         pa.halo_rows = ham->halo_rows;
+        pa.max_halo = ham->max_halo;
         pa.hcol = ham->hcol;
         pa.hval = ham->hval;
         pa.vidx = ham->vidx;
@@ -864,7 +866,6 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         pa.scale_b = 2.0 / rescale;
         pa.partials = partials;
         pa.B = B;
-        pa.max_halo = ham->max_halo;
         while (m < M) {                                 // an even number of terms remains
             const bool last = (m + 2 == M);
             if (prof && last && prof->ev[2])
@@ -942,6 +943,7 @@ tbpm_status apply_series_cross(const tbpm_ham *ham, hipStream_t st, const double
     pa.patch_ptr = ham->patch_ptr;
     pa.halo_ptr = ham->halo_ptr;
     pa.halo_rows = ham->halo_rows;
+    pa.max_halo = ham->max_halo;
     pa.hcol = ham->hcol;
     pa.hval = ham->hval;
     pa.vidx = ham->vidx;

@@ -1044,9 +1044,13 @@ hipError_t launch_term(int kind, int dtype, int fmt, const TermArgs &a, const Ke
 // Rows are renumbered into patches (compact regions of the sparsity graph,
 // contiguous in the new order) with halos (rows outside a patch referenced by
 // it).  One workgroup owns one patch:
-//   phase A: y_m = scale H x_{m-1} - y_{m-2} for the patch rows (their H row
-//            stays in registers) and for the halo rows, into LDS; patch rows
-//            also to yout;
+//   loads:   x_{m-1} of the patch rows and of the halo rows into LDS, the rows'
+//            y_{m-2} and H into registers; the halo rows' indexes and H go
+//            first, then the vectors they lead to, so a patch waits for memory
+//            about three times in a row (bounds, indexes, halo vectors);
+//   phase A: y_m = scale H x_{m-1} - y_{m-2} for the patch rows, every gather
+//            from LDS, and for the halo rows (gathers from L2), into LDS;
+//            patch rows also to yout;
 //   phase B: x_{m+1} = scale H y_m - x_{m-1} for the patch rows, gathering y_m
 //            from LDS.
 // The series out = sum_m c_m p_m takes its terms in every other pair: a pair
@@ -1055,9 +1059,18 @@ hipError_t launch_term(int kind, int dtype, int fmt, const TermArgs &a, const Ke
 // series (out written, not read), and LAST ends one: y_m stays on chip and
 // x_{m+1} is not stored, since nothing reads them after it.
 // H is read once for two terms (plus the halo rows' H), out is touched once
-// in four, and y_m is not read back from HBM.  Inputs (x_{m-1}, y_{m-2}) and outputs
-// (y_m, x_{m+1}) are different buffers, since a halo row of one patch is a
-// patch row of another.
+// in four, and y_m is not read back from HBM.  Inputs (x_{m-1}, y_{m-2}) and
+// outputs (y_m, x_{m+1}) are different buffers, since a halo row of one patch
+// is a patch row of another.
+// A patch is a chain of memory latencies, so until memory is saturated the
+// chain's length sets the pace: with x gathered from L2 after the columns, the
+// halo rows' H read after phase A's rows and out read in phase B (six waits) a
+// patch took 12.6 us at two workgroups a CU whether its vectors came from HBM
+// or from the last-level cache.  Graphene, complex128, value table, before and
+// now: moment pair on 2.1M rows 51.7 -> 41.5 us; middle pair on 8.4M rows 201
+// -> 183 us with out (973 MB, 5.3 TB/s) and 140 us without (705 MB, 5.0 TB/s);
+// on 295k rows, where one wave of workgroups holds every patch, 11.4 -> 9.4
+// and 7.8 us.
 //
 // The Clenshaw modes run the same two phases on the backward recurrence
 // b_m = c_m psi + scale H b_m+1 - b_m+2: phase A forms b_m (x = b_m+1,
@@ -1066,7 +1079,7 @@ hipError_t launch_term(int kind, int dtype, int fmt, const TermArgs &a, const Ke
 // writes of b_m, b_m-1 instead of the forward pair's extra read and write of
 // out.
 
-template <typename T, int W, int NT, int R, int MODE, bool DICT>
+template <typename T, int W, int NT, int MODE, bool DICT>
 __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
 {
     constexpr bool LAST = MODE == PAIR_LAST;
@@ -1080,16 +1093,18 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
     constexpr bool SKIP = MODE == PAIR_SKIP;             // no series terms
     constexpr bool SET = MODE == PAIR_SET || FST;        // the series starts here: out is not read
     constexpr bool DOTS = LAST || MOM || CLL || CRS;
+    constexpr bool NOY = first || FST;                   // no y_{m-2}
     constexpr int NV = MOM ? 6 : 3;                 // partial sums per workgroup
     using E = Elem<T>;
     using A = typename E::acc;
+    constexpr int R = 2;                            // rows per lane
     constexpr int S = NT * R;
-    constexpr int HMAX = pair_halo_max(S);
-    __shared__ T ylds[S + HMAX];
-    __shared__ int32_t hidx[HMAX];
+    constexpr int NW = (W + 3) / 4;                 // column (and index) words per row
+    extern __shared__ __attribute__((aligned(16))) char pair_lds[];
+    T *xl = reinterpret_cast<T *>(pair_lds);        // x_{m-1}: patch rows, then halo rows
+    T *yl = xl + (S + a.max_halo);                  // y_m, the same rows
     __shared__ double red[NT / 64][NV];
-    __shared__ T vtab[DICT ? 256 : 1];          // value table (DICT: H entries are one-byte indices)
-    constexpr int NW = (W + 3) / 4;             // index words per row
+    __shared__ T vtab[DICT ? 256 : 1];              // value table (DICT: H entries are one-byte indices)
 
     // one patch per workgroup; the patches of XCD (blockIdx % 8) are contiguous
     // (in the list order when only listed patches are processed)
@@ -1100,15 +1115,16 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
         return;                                     // uniform over the workgroup
     const int64_t patch = a.plist ? (int64_t)a.plist[pidx] : pidx;
     const int64_t base = a.patch_ptr[patch];
-    const int cnt = a.patch_ptr[patch + 1] - (int)base;
+    const int cnt = min(a.patch_ptr[patch + 1] - (int)base, S);
     const int hb = a.halo_ptr[patch];
-    const int hc = min(a.halo_ptr[patch + 1] - hb, HMAX);
+    const int hc = min(a.halo_ptr[patch + 1] - hb, a.max_halo);
     const T *__restrict__ xin = static_cast<const T *>(a.xin);
     const T *__restrict__ yin = static_cast<const T *>(a.yin);
     T *__restrict__ yout = static_cast<T *>(a.yout);
     T *__restrict__ xout = static_cast<T *>(a.xout);
     T *__restrict__ out = static_cast<T *>(a.out);
     const T *__restrict__ val = static_cast<const T *>(a.val);
+    const T *__restrict__ vdiag = static_cast<const T *>(a.vdiag);
     const uint64_t *__restrict__ lcol = a.lcol;
     const int64_t ld = a.ld;
     const double scale = a.scale;
@@ -1118,57 +1134,138 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
     const d2 c1 = d2{a.c1_re, a.c1_im};
     const d2 cx = d2{a.cx_re, a.cx_im};
     const d2 cy = d2{a.cy_re, a.cy_im};
+    const int t = threadIdx.x;
 
-    // the halo list maps local column indices >= cnt to rows
-    for (int h = threadIdx.x; h < hc; h += NT)
-        hidx[h] = a.halo_rows[hb + h];
-    const T *__restrict__ vdiag = static_cast<const T *>(a.vdiag);
-    if constexpr (DICT) {
-        for (int i = threadIdx.x; i < 256; i += NT)
-            vtab[i] = static_cast<const T *>(a.vtab)[i];
-    }
-
-    // phase A, patch rows: lane t owns rows t, t + NT, ...; H's columns are
-    // patch-local (2 bytes a slot, four to a word): l < cnt is row base + l,
-    // else halo entry l - cnt.
-    // Values: v, or (DICT) index words vw (slot s in byte s % 4 of word s / 4)
-    // into the table, index 255 taking the row's diagonal dg
-    int c[R][W];
-    T v[R][W];
-    uint32_t vw[R][NW];
-    T dg[R];
-    T yo[R], xo[R], po[R], oo[R];
-    d2 ym[R];
+    // H of a halo row (stored contiguously per patch, global columns), and what
+    // its y_m needs besides: indexes first, the vectors they lead to afterwards
+    struct HaloRow {
+        int32_t r;                                  // the row
+        int32_t c[W];
+        T v[DICT ? 1 : W];
+        uint32_t w[DICT ? NW : 1];
+        T d, x, y, p;                               // diagonal, x, y_{m-2}, psi or out
+        T xv[W];                                    // x at its columns
+    };
+    auto halo_index = [&](int h, HaloRow &q) {
+        const int64_t g = (int64_t)hb + h;
+        q.r = a.halo_rows[g];
+        if constexpr (!CLS) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int li = threadIdx.x + r * NT;
-        const int64_t row = base + (li < cnt ? li : cnt - 1);
-        uint64_t cw[NW];
+            for (int s = 0; s < W; ++s)
+                q.c[s] = ld_stream(a.hcol + (int64_t)s * a.ldh + g);
+            if constexpr (DICT) {
 #pragma unroll
-        for (int q = 0; q < NW; ++q)
-            cw[q] = ld_stream(lcol + (int64_t)q * ld + row);
+                for (int k = 0; k < NW; ++k)
+                    q.w[k] = ld_stream(a.hvidx + (int64_t)k * a.ldh + g);
+            } else {
+#pragma unroll
+                for (int s = 0; s < W; ++s)
+                    q.v[s] = ld_stream(static_cast<const T *>(a.hval) + (int64_t)s * a.ldh + g);
+            }
+        }
+    };
+    auto halo_vectors = [&](HaloRow &q) {
+        q.x = xin[q.r];
+        if constexpr (!CLS) {
+#pragma unroll
+            for (int s = 0; s < W; ++s)
+                q.xv[s] = xin[q.c[s]];
+            if constexpr (!NOY)
+                q.y = yin[q.r];
+            if constexpr (CL && !first)
+                q.p = psi[q.r];
+            if constexpr (CRS)
+                q.p = out[q.r];
+            if constexpr (DICT)
+                q.d = diag_of(vdiag, a.vdiag_real, q.r);
+        }
+    };
+    auto halo_y = [&](const HaloRow &q) -> T {      // (the value table in LDS)
+        A acc{0, 0};
 #pragma unroll
         for (int s = 0; s < W; ++s) {
-            c[r][s] = (int)((cw[s / 4] >> (16 * (s % 4))) & 0xFFFFull);
-            if constexpr (!DICT)
-                v[r][s] = ld_stream(val + (int64_t)s * ld + row);
+            T v;
+            if constexpr (DICT) {
+                const uint32_t k = (q.w[s / 4] >> (8 * (s % 4))) & 255u;
+                v = k == 255u ? q.d : vtab[k];
+            } else {
+                v = q.v[s];
+            }
+            cmac(acc, (A)v, (A)q.xv[s]);
         }
+        const d2 hx = E::acc_to_d(acc) * scale;
+        if constexpr (CL) {
+            return E::from_d((first ? cmul(ka, hx) : hx - E::to_d(q.y)) + cmul(c0, E::to_d(first ? q.x : q.p)));
+        } else if constexpr (FST) {
+            return E::from_d(hx);
+        } else if constexpr (CRS) {
+            const d2 yd = E::to_d(q.y);
+            return E::from_d(((E::to_d(q.p) + cmul(cy, yd)) + cmul(cx, E::to_d(q.x))) + cmul(c0, hx - yd));
+        } else {
+            return E::from_d(hx - E::to_d(q.y));
+        }
+    };
+
+    // Loads, none waiting for another but the halo's: lane t has halo row t and
+    // patch rows t, t + NT.  H's columns are patch-local (2 bytes a slot, four
+    // to a word): l < cnt is row base + l, else halo entry l - cnt.  Values: v,
+    // or (DICT) index words vw (slot s in byte s % 4 of word s / 4) into the
+    // table, index 255 taking the row's diagonal dg.
+    HaloRow hr;
+    if (t < hc)
+        halo_index(t, hr);
+    __builtin_amdgcn_sched_barrier(0);
+    uint64_t cw[R][NW];
+    T v[R][DICT ? 1 : W];
+    uint32_t vw[R][DICT ? NW : 1];
+    T dg[R];
+    T xs[R], yo[R], po[R], oo[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int li = t + r * NT;
+        const int64_t row = base + (li < cnt ? li : cnt - 1);
+        xs[r] = xin[row];
+        if constexpr (!NOY)
+            yo[r] = ld_stream(yin + row);
+#pragma unroll
+        for (int q = 0; q < NW; ++q)
+            cw[r][q] = ld_stream(lcol + (int64_t)q * ld + row);
         if constexpr (DICT) {
 #pragma unroll
             for (int q = 0; q < NW; ++q)
                 vw[r][q] = ld_stream(a.vidx + (int64_t)q * ld + row);
             dg[r] = diag_of(vdiag, a.vdiag_real, row);
+        } else {
+#pragma unroll
+            for (int s = 0; s < W; ++s)
+                v[r][s] = ld_stream(val + (int64_t)s * ld + row);
         }
-        yo[r] = (first || FST) ? T{} : ld_stream(yin + row);
-        if constexpr (!CLS)
-            xo[r] = xin[row];                       // x_{m-1} of the row, for phase B
         if constexpr (CRS)
             oo[r] = ld_stream(out + row);           // the step's accumulated series
-        if constexpr (CL)
-            po[r] = first ? xo[r] : ld_stream(psi + row);
+        if constexpr (CL && !first)
+            po[r] = ld_stream(psi + row);
     }
-    __syncthreads();                                // hidx (and the value table) complete
-    // the value of slot s of a patch row (after the barrier: the table is in LDS)
+    if constexpr (DICT) {
+        for (int i = t; i < 256; i += NT)
+            vtab[i] = static_cast<const T *>(a.vtab)[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (t < hc)
+        halo_vectors(hr);
+    // x_{m-1} of patch and halo rows into LDS
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int li = t + r * NT;
+        if (li < cnt)
+            xl[li] = xs[r];
+    }
+    if (t < hc)
+        xl[cnt + t] = hr.x;
+    for (int h = t + NT; h < hc; h += NT)           // halos larger than the workgroup
+        xl[cnt + h] = xin[a.halo_rows[hb + h]];
+    __syncthreads();                                // x (and the value table) complete
+
+    // the value of slot s and its local column
     auto hv = [&](int r, int s) -> T {
         if constexpr (DICT) {
             const uint32_t k = (vw[r][s / 4] >> (8 * (s % 4))) & 255u;
@@ -1177,149 +1274,94 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
             return v[r][s];
         }
     };
+    auto lc = [&](int r, int s) -> int { return (int)((cw[r][s / 4] >> (16 * (s % 4))) & 0xFFFFull); };
+
+    // phase A: y_m of the halo rows and of the patch rows
+    if constexpr (!CLS) {
+        if (t < hc)
+            yl[cnt + t] = halo_y(hr);
+        for (int h = t + NT; h < hc; h += NT) {
+            halo_index(h, hr);
+            halo_vectors(hr);
+            yl[cnt + h] = halo_y(hr);
+        }
+    }
+    if constexpr (!SET && !SKIP && !CL && !CRS && !MOM) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {               // for phase B
+            const int li = t + r * NT;
+            oo[r] = ld_stream(out + base + (li < cnt ? li : cnt - 1));
+        }
+    }
+    d2 ym[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        T xv[W];
-#pragma unroll
-        for (int s = 0; s < W; ++s) {
-            const int l = c[r][s];
-            xv[s] = xin[l < cnt ? base + l : (int64_t)hidx[l - cnt]];
-        }
+        const int li = t + r * NT;
         A acc{0, 0};
 #pragma unroll
         for (int s = 0; s < W; ++s)
-            cmac(acc, (A)hv(r, s), (A)xv[s]);
+            cmac(acc, (A)hv(r, s), (A)xl[lc(r, s)]);
+        const d2 hx = E::acc_to_d(acc) * scale;
         if constexpr (CL) {
-            const d2 hx = E::acc_to_d(acc) * scale;
-            ym[r] = (first ? cmul(ka, hx) : hx - E::to_d(yo[r])) + cmul(c0, E::to_d(po[r]));
+            const d2 pd = E::to_d(first ? xl[li < cnt ? li : 0] : po[r]);
+            ym[r] = (first ? cmul(ka, hx) : hx - E::to_d(yo[r])) + cmul(c0, pd);
         } else if constexpr (FST) {
-            ym[r] = E::acc_to_d(acc) * scale;       // p_1 = (1/rho) H psi
+            ym[r] = hx;                             // p_1 = (1/rho) H psi
         } else if constexpr (CRS) {
             // psi(t + dt) = out + the last terms of the series, as stored (it starts the next step)
             const d2 yd = E::to_d(yo[r]);
-            ym[r] = E::to_d(E::from_d(((E::to_d(oo[r]) + cmul(cy, yd)) + cmul(cx, E::to_d(xo[r]))) +
-                                      cmul(c0, E::acc_to_d(acc) * scale - yd)));
+            ym[r] = E::to_d(E::from_d(((E::to_d(oo[r]) + cmul(cy, yd)) + cmul(cx, E::to_d(xl[li < cnt ? li : 0]))) +
+                                      cmul(c0, hx - yd)));
         } else {
-            ym[r] = E::acc_to_d(acc) * scale - E::to_d(yo[r]);
+            ym[r] = hx - E::to_d(yo[r]);
         }
         if constexpr (MOM)
             ym[r] = E::to_d(E::from_d(ym[r]));      // the stored value enters the inner products
-        const int li = threadIdx.x + r * NT;
         if (li < cnt) {
             const T ys = E::from_d(ym[r]);
             if constexpr (!CLS)
-                ylds[li] = ys;
-            if constexpr (!CLL && !LAST)            // the last pair's y_m stays on chip
+                yl[li] = ys;
+            if constexpr (!CLL && !LAST)            // b_1 of a Clenshaw series and the last pair's y_m stay on chip
                 st_stream(ys, yout + base + li);
         }
     }
     if constexpr (CLS)
-        return;                                     // one product: no halo, no second phase
-
-    // phase A, halo rows (their H rows are stored contiguously per patch)
-    const int32_t *__restrict__ hcol = a.hcol;
-    const T *__restrict__ hval = static_cast<const T *>(a.hval);
-    for (int h = threadIdx.x; h < hc; h += NT) {
-        const int64_t rh = hidx[h];
-        const int64_t g = (int64_t)hb + h;
-        int32_t ch[W];
-        T vh[W];
-#pragma unroll
-        for (int s = 0; s < W; ++s)
-            ch[s] = ld_stream(hcol + (int64_t)s * a.ldh + g);
-        if constexpr (DICT) {
-            uint32_t hw[NW];
-#pragma unroll
-            for (int q = 0; q < NW; ++q)
-                hw[q] = ld_stream(a.hvidx + (int64_t)q * a.ldh + g);
-            const T dh = diag_of(vdiag, a.vdiag_real, rh);
-#pragma unroll
-            for (int s = 0; s < W; ++s) {
-                const uint32_t k = (hw[s / 4] >> (8 * (s % 4))) & 255u;
-                vh[s] = k == 255u ? dh : vtab[k];
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < W; ++s)
-                vh[s] = ld_stream(hval + (int64_t)s * a.ldh + g);
-        }
-        const T yh = (first || FST) ? T{} : yin[rh];
-        T xv[W];
-#pragma unroll
-        for (int s = 0; s < W; ++s)
-            xv[s] = xin[ch[s]];
-        A acc{0, 0};
-#pragma unroll
-        for (int s = 0; s < W; ++s)
-            cmac(acc, (A)vh[s], (A)xv[s]);
-        if constexpr (CL) {
-            const d2 hx = E::acc_to_d(acc) * scale;
-            const d2 ph = E::to_d(first ? xin[rh] : psi[rh]);
-            ylds[cnt + h] = E::from_d((first ? cmul(ka, hx) : hx - E::to_d(yh)) + cmul(c0, ph));
-        } else if constexpr (FST) {
-            ylds[cnt + h] = E::from_d(E::acc_to_d(acc) * scale);
-        } else if constexpr (CRS) {
-            const d2 yd = E::to_d(yh);
-            ylds[cnt + h] = E::from_d(((E::to_d(out[rh]) + cmul(cy, yd)) + cmul(cx, E::to_d(xin[rh]))) +
-                                      cmul(c0, E::acc_to_d(acc) * scale - yd));
-        } else {
-            ylds[cnt + h] = E::from_d(E::acc_to_d(acc) * scale - E::to_d(yh));
-        }
-    }
+        return;                                     // one product: no second phase
     __syncthreads();                                // y_m of patch and halo in LDS
 
     // phase B
     const double sb = (CL || FST || CRS) ? a.scale_b : scale;
-    // LAST: <psi0|out>, <out|out>.  MOM: with x = p_m (xin), y = p_m+1, z = p_m+2:
-    // <x|y>, <x|x>, <y|z>, <y|y>
+    // LAST, CLL, CRS: <psi0|out>, <out|out>.  MOM: with x = p_m (xin), y = p_m+1,
+    // z = p_m+2: <x|y>, <x|x>, <y|z>, <y|y>
     double sum[NV];
 #pragma unroll
     for (int q = 0; q < NV; ++q)
         sum[q] = 0.0;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int li = threadIdx.x + r * NT;
+        const int li = t + r * NT;
         if (li < cnt) {
             const int64_t row = base + li;
             A acc{0, 0};
 #pragma unroll
             for (int s = 0; s < W; ++s)
-                cmac(acc, (A)hv(r, s), (A)ylds[c[r][s]]);   // ylds: patch rows, then halo rows
+                cmac(acc, (A)hv(r, s), (A)yl[lc(r, s)]);    // patch rows, then halo rows
+            const d2 hy = E::acc_to_d(acc) * sb;
+            const d2 xd = E::to_d(xl[li]);
             d2 xn;
-            if constexpr (CL) {
-                const d2 hy = E::acc_to_d(acc) * sb;
-                const d2 xd = E::to_d(xo[r]);
-                xn = (first ? hy - cmul(ka, xd) : hy - xd) + cmul(c1, E::to_d(po[r]));
-            } else if constexpr (CRS) {
-                xn = E::acc_to_d(acc) * sb;         // p_1 of the next step
-            } else {
-                xn = E::acc_to_d(acc) * sb - E::to_d(xo[r]);
-            }
-            const T xs = E::from_d(xn);
+            if constexpr (CL)
+                xn = (first ? hy - cmul(ka, xd) : hy - xd) + cmul(c1, first ? xd : E::to_d(po[r]));
+            else if constexpr (CRS)
+                xn = hy;                            // p_1 of the next step
+            else
+                xn = hy - xd;
+            const T xs2 = E::from_d(xn);
             if constexpr (!LAST)
-                st_stream(xs, xout + row);
+                st_stream(xs2, xout + row);
             if constexpr (SKIP)
                 continue;
-            if constexpr (CRS) {                    // sums of psi(t + dt)
-                const d2 p = E::to_d(ld_stream(static_cast<const T *>(a.psi0) + row));
-                const d2 o = ym[r];
-                sum[0] += p.x * o.x + p.y * o.y;
-                sum[1] += p.x * o.y - p.y * o.x;
-                sum[2] += o.x * o.x + o.y * o.y;
-                continue;
-            }
-            if constexpr (CL) {
-                if constexpr (CLL) {                // O = psi(t + dt): <psi0|O>, <O|O>
-                    const d2 p = E::to_d(ld_stream(static_cast<const T *>(a.psi0) + row));
-                    const d2 o = E::to_d(xs);
-                    sum[0] += p.x * o.x + p.y * o.y;
-                    sum[1] += p.x * o.y - p.y * o.x;
-                    sum[2] += o.x * o.x + o.y * o.y;
-                }
-                continue;
-            }
             if constexpr (MOM) {
-                const d2 xd = E::to_d(xo[r]), yd = ym[r], zd = E::to_d(E::from_d(xn));
+                const d2 yd = ym[r], zd = E::to_d(xs2);
                 sum[0] += xd.x * yd.x + xd.y * yd.y;
                 sum[1] += xd.x * yd.y - xd.y * yd.x;
                 sum[2] += xd.x * xd.x + xd.y * xd.y;
@@ -1328,20 +1370,27 @@ __global__ __launch_bounds__(NT) void pair_kernel(PairArgs a)
                 sum[5] += yd.x * yd.x + yd.y * yd.y;
                 continue;
             }
-            // the series' terms of the pair's rows, oldest first
-            d2 on = cmul(cx, E::to_d(xo[r]));
-            if constexpr (!FST)
-                on = cmul(cy, E::to_d(yo[r])) + on;
-            if constexpr (!SET)
-                on = E::to_d(ld_stream(out + row)) + on;
-            on = (on + cmul(c0, ym[r])) + cmul(c1, xn);
-            const T os = E::from_d(on);
-            st_stream(os, out + row);
-            if constexpr (LAST) {
-                if (!a.psi0)                        // a series without correlation sums
+            d2 o;                                   // psi(t + dt), where the launch forms it
+            if constexpr (CRS) {
+                o = ym[r];
+            } else if constexpr (CL) {
+                o = E::to_d(xs2);
+            } else {
+                // the series' terms of the pair's rows, oldest first
+                d2 on = cmul(cx, xd);
+                if constexpr (!FST)
+                    on = cmul(cy, E::to_d(yo[r])) + on;
+                if constexpr (!SET)
+                    on = E::to_d(oo[r]) + on;
+                on = (on + cmul(c0, ym[r])) + cmul(c1, xn);
+                const T os = E::from_d(on);
+                st_stream(os, out + row);
+                o = E::to_d(os);
+            }
+            if constexpr (DOTS) {
+                if (LAST && !a.psi0)                // a series without correlation sums
                     continue;
                 const d2 p = E::to_d(ld_stream(static_cast<const T *>(a.psi0) + row));
-                const d2 o = E::to_d(os);
                 sum[0] += p.x * o.x + p.y * o.y;
                 sum[1] += p.x * o.y - p.y * o.x;
                 sum[2] += o.x * o.x + o.y * o.y;
@@ -1400,45 +1449,46 @@ bool pair_supported(int w, int patch_rows)
 int pair_grid(int64_t npatch) { return (int)((npatch + NXCD - 1) / NXCD * NXCD); }
 
 // 2048-row patches: 1024 lanes with 2 rows each; 1024-row patches: 512 lanes
-// with 2 rows each (two workgroups per CU overlap each other's barriers)
+// with 2 rows each.  LDS: x and y_m of a patch and of the plan's largest halo.
 template <typename T, int W, int R, bool DICT>
 static hipError_t launch_pair_w(int mode, const PairArgs &a, hipStream_t st)
 {
-    const int g = pair_grid(a.plist ? a.pcount : a.npatch);
+    const dim3 g(pair_grid(a.plist ? a.pcount : a.npatch));
     constexpr int NT = R == 2 ? 1024 : 512;
+    const size_t one = (size_t)(2 * NT + a.max_halo) * sizeof(T);
     switch (mode) {
     case PAIR_LAST:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_LAST, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_LAST, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_MOM:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_MOM, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_MOM, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_CL:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_CL, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_CL, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_CL_LAST:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_CL_LAST, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_CL_LAST, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_CL_SINGLE:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_CL_SINGLE, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_CL_SINGLE, DICT>), g, dim3(NT), one, st, a);
         break;
     case PAIR_CL_FIRST:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_CL_FIRST, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_CL_FIRST, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_FIRST:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_FIRST, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_FIRST, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_CROSS:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_CROSS, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_CROSS, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_SKIP:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_SKIP, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_SKIP, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     case PAIR_SET:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_SET, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_SET, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     default:
-        hipLaunchKernelGGL((pair_kernel<T, W, NT, 2, PAIR_MID, DICT>), dim3(g), dim3(NT), 0, st, a);
+        hipLaunchKernelGGL((pair_kernel<T, W, NT, PAIR_MID, DICT>), g, dim3(NT), 2 * one, st, a);
         break;
     }
     return hipGetLastError();
@@ -1928,6 +1978,7 @@ hipError_t launch_pair(int mode, int dtype, const PairArgs &a, int patch_rows, h
     if (a.B > 1)
         return launch_bpair(mode, dtype, a, patch_rows, st);
     if (!pair_supported(a.w, patch_rows) || !a.lcol || a.npatch <= 0 || mode < PAIR_MID || mode > PAIR_SET ||
+        a.max_halo < 0 || a.max_halo > pair_halo_max(patch_rows) ||
         (mode == PAIR_CROSS && (!a.out || !a.partials || !a.psi0)) ||
         (mode == PAIR_LAST && a.psi0 && !a.partials) ||
         (mode == PAIR_MOM && !a.partials2) || (a.plist && (a.pcount <= 0 || a.pcount > a.npatch)))

@@ -344,6 +344,7 @@ struct MomentRun {
                 pa.patch_ptr = ham->patch_ptr;
                 pa.halo_ptr = ham->halo_ptr;
                 pa.halo_rows = ham->halo_rows;
+                pa.max_halo = ham->max_halo;
                 pa.hcol = ham->hcol;
                 pa.hval = ham->hval;
                 pa.vidx = ham->vidx;
