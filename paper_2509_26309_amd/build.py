@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtbpm.so")
-SOURCES = ["tbpm_kernels.hip", "tbpm_support.hip", "tbpm_bessel.cpp", "tbpm_patch.cpp", "tbpm_engine.cpp",
+SOURCES = ["tbpm_kernels.hip", "tbpm_support.hip", "tbpm_steps.hip", "tbpm_plan.cpp", "tbpm_bessel.cpp", "tbpm_patch.cpp", "tbpm_engine.cpp",
            "tbpm_api.cpp", "tbpm_server.cpp", "tbpm_moments.cpp", "tbpm_response.cpp", "tbpm_noalloc.hip",
            "tbpm_host.cpp"]
 # packed FP32 instructions stay off: the compiler is told not to form them

@@ -527,6 +527,8 @@ tbpm_status tbpm_build_csr(tbpm_ctx *ctx, const tbpm_csr *csr, int32_t dtype, in
     if (e == hipSuccess)
         e = hipStreamSynchronize(st);
     cleanup();
+    if (e == hipSuccess)
+        e = tbpm::build_steps(ham, st);
     if (e != hipSuccess) {
         tbpm_ham_destroy(ham);
         return set_err(ctx, TBPM_ERR_HIP, std::string("H conversion: ") + hipGetErrorString(e));
@@ -590,6 +592,7 @@ tbpm_status tbpm_ham_destroy(tbpm_ham *ham)
     ctx->dev_free(ham->hvidx);
     ctx->dev_free(ham->vtab);
     ctx->dev_free(ham->vdiag);
+    free_steps(ham);
     delete ham;
     return TBPM_OK;
 }

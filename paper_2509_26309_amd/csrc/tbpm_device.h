@@ -48,6 +48,17 @@ __device__ __forceinline__ T ld_stream(const T *p)
     return __builtin_nontemporal_load(p);
 }
 
+// the per-row diagonal value of a value table (index 255): complex, or its
+// real part alone with an imaginary part of +0; 0 without a per-row diagonal
+template <typename T>
+__device__ __forceinline__ T diag_value(const T *vdiag, int32_t real, int64_t row)
+{
+    using Re = decltype(T{}.x);
+    if (!vdiag)
+        return T{};
+    return real ? T{reinterpret_cast<const Re *>(vdiag)[row], Re(0)} : vdiag[row];
+}
+
 // Tiles of XCD (blockIdx % 8) form one contiguous slab that the XCD sweeps
 // front to back.  Within it, block j of that XCD takes runs of `run`
 // consecutive tiles: run j, run j + nbx, ...; run is the block's share of the

@@ -199,16 +199,43 @@ tbpm_status Job::setup(tbpm_ctx *c, const tbpm_ham *h, const tbpm_params *prm, h
         pairs = any_single || any_block;
         max_grid = std::max<int64_t>(max_grid, ham->npatch);
     }
-    cross = pairs && any_single && !clenshaw && M >= 6 && M % 2 == 0;
+    // several products per launch, where H has a plan for it (kernel timing is
+    // by term, so it keeps the term kernels)
+    cross_ok = pairs && any_single && !clenshaw && M >= 6 && M % 2 == 0;
+    steps = !clenshaw && !ctx->profiling && steps_apply(ham, M, blocks);
+    if (steps)
+        max_grid = std::max<int64_t>(max_grid, ham->steps.ntiles);
+    cross = cross_ok && !steps;
     return TBPM_OK;
+}
+
+int Job::vectors() const
+{
+    if (steps) {
+        // psi0, P and O, the roles' third vector, and what a series of several launches passes on
+        const int launches = (M - 1 + ham->steps.depth - 1) / ham->steps.depth;
+        return launches == 1 ? 4 : launches == 2 ? 5 : 6;
+    }
+    return cross ? 7 : pairs ? 6 : 4;               // psi0 + three (five, six) rotating vectors
+}
+
+size_t Job::sums() const { return (size_t)max_grid * (size_t)bmax * 4 * (steps ? GRAPH_STEPS : 1); }
+
+bool Job::without_steps()
+{
+    if (!steps)
+        return false;
+    steps = false;
+    cross = cross_ok;
+    return true;
 }
 
 size_t Job::footprint() const
 {
     const size_t n = (size_t)ham->n;
     const size_t nt1 = (size_t)p.num_time_steps + 1;
-    size_t b = (cross ? 7 : pairs ? 6 : 4) * n * (size_t)bmax * elem;   // psi0 + three (five, six) rotating vectors
-    b += (size_t)max_grid * (size_t)bmax * 4 * sizeof(double);
+    size_t b = (size_t)vectors() * n * (size_t)bmax * elem;
+    b += sums() * sizeof(double);
     b += nt1 * (size_t)bmax * 3 * sizeof(double);          // corr (complex) + norms
     b += sites.size() * (nt1 * 2 * sizeof(double) + sizeof(int64_t));
     if (given_states || final_states || !snap_steps.empty() || !qe_energies.empty())
@@ -224,7 +251,7 @@ size_t Job::arena_need() const
     const size_t n = (size_t)ham->n;
     const size_t vb_bytes = align256(n * (size_t)bmax * elem);
     const size_t nt1 = (size_t)p.num_time_steps + 1;
-    return (cross ? 7 : pairs ? 6 : 4) * vb_bytes + align256((size_t)max_grid * bmax * 4 * sizeof(double)) +
+    return (size_t)vectors() * vb_bytes + align256(sums() * sizeof(double)) +
            align256(nt1 * bmax * 2 * sizeof(double)) + align256(nt1 * bmax * sizeof(double)) + align256(256);
 }
 
@@ -252,20 +279,14 @@ tbpm_status Job::allocate()
     va = take(vb_bytes);
     vb = take(vb_bytes);
     vc = take(vb_bytes);
-    partials = (double *)take((size_t)max_grid * bmax * 4 * sizeof(double));
+    partials = (double *)take(sums() * sizeof(double));
     corr_dev = (double *)take(nt1 * bmax * 2 * sizeof(double));
     norms_dev = (double *)take(nt1 * bmax * sizeof(double));
     div_flag = (int32_t *)take(256);
     bool ok = psi0 && va && vb && vc && partials && corr_dev && norms_dev && div_flag;
-    if (ok && pairs) {
-        vd = take(vb_bytes);
-        ve = take(vb_bytes);
-        ok = vd && ve;
-    }
-    if (ok && cross) {
-        vf = take(vb_bytes);
-        ok = vf != nullptr;
-    }
+    void **more[] = {&vd, &ve, &vf};
+    for (int i = 4; ok && i < vectors(); ++i)
+        ok = (*more[i - 4] = take(vb_bytes)) != nullptr;
     if (ok && !sites.empty()) {
         site_dev = (double *)ctx->dev_alloc(sites.size() * nt1 * 2 * sizeof(double));
         sites_dev = (int64_t *)ctx->dev_alloc(sites.size() * sizeof(int64_t));
@@ -281,6 +302,8 @@ tbpm_status Job::allocate()
     }
     if (!ok) {
         release();
+        if (!arena && without_steps())              // the term kernels may take fewer vectors
+            return allocate();
         return fail(arena ? TBPM_ERR_TOO_LARGE : TBPM_ERR_OOM,
                     arena ? "the propagation buffers exceed the scratch area"
                           : "device allocation of the propagation buffers failed");
@@ -361,29 +384,36 @@ tbpm_status Job::open_block()
     Q = vb;
     O = vc;
     first_done = false;
-    if (!site_states.empty()) {
-        SiteRows sr{};
-        for (int b = 0; b < B; ++b)
-            sr.r[b] = site_states[(size_t)r0 + b];
-        JOB_HIP(launch_init_sites(ham->dtype, psi0, P, n, B, sr, st));
-    } else if (given_states) {
+    const int32_t *perm = ham->patched ? ham->old_of_new : nullptr;
+    if (given_states)
         JOB_HIP(hipMemcpyAsync(states_dev, given_states + (size_t)r0 * n * 2, (size_t)B * n * 16,
                                hipMemcpyHostToDevice, st));
-        JOB_HIP(launch_pack_states(ham->dtype, states_dev, psi0, P, n, B, ham->patched ? ham->old_of_new : nullptr,
-                                   st));
-    } else {
-        JOB_HIP(launch_init_random(ham->dtype, psi0, P, n, B, p.seed, (int64_t)p.first_vector + r0,
-                                   ham->patched ? ham->old_of_new : nullptr, st));
+    // groups of BV interleaved vectors: the whole block, or (steps) single vectors
+    const int BV = group();
+    for (int b = 0; b < B; b += BV) {
+        if (!site_states.empty()) {
+            SiteRows sr{};
+            for (int q = 0; q < BV; ++q)
+                sr.r[q] = site_states[(size_t)r0 + b + q];
+            JOB_HIP(launch_init_sites(ham->dtype, vec(psi0, b), vec(P, b), n, BV, sr, st));
+        } else if (given_states) {
+            JOB_HIP(launch_pack_states(ham->dtype, states_dev + (size_t)b * n * 2, vec(psi0, b), vec(P, b), n, BV, perm,
+                                       st));
+        } else {
+            JOB_HIP(launch_init_random(ham->dtype, vec(psi0, b), vec(P, b), n, BV, p.seed,
+                                       (int64_t)p.first_vector + r0 + b, perm, st));
+        }
+        // C(t_0) = <psi0|psi0>
+        JOB_HIP(launch_dot_partials(ham->dtype, vec(psi0, b), vec(P, b), n, BV, partials, dot_grid, st));
+        JOB_HIP(launch_reduce(partials, dot_grid, BV, corr_dev + 2 * b, norms_dev + b, st, p.norm_tol, div_flag));
+        if (!sites.empty())
+            JOB_HIP(launch_ldos_gather(ham->dtype, vec(psi0, b), vec(P, b), n, BV, sites_dev, (int)sites.size(),
+                                       site_dev, p.num_time_steps + 1, 0, st));
     }
-    // C(t_0) = <psi0|psi0>
-    JOB_HIP(launch_dot_partials(ham->dtype, psi0, P, n, B, partials, dot_grid, st));
-    JOB_HIP(launch_reduce(partials, dot_grid, B, corr_dev, norms_dev, st, p.norm_tol, div_flag));
-    if (!sites.empty())
-        JOB_HIP(launch_ldos_gather(ham->dtype, psi0, P, n, B, sites_dev, (int)sites.size(), site_dev,
-                                   p.num_time_steps + 1, 0, st));
     if (graph_mode)
         JOB_HIP(launch_set_counter(kstep, 1, st));
     k = 0;
+    pending = 0;
     block_open = true;
     return emit_outputs();
 }
@@ -580,10 +610,103 @@ static int term_kind(const double *c, int m, int M, int &held, bool last_sums, T
     return kind;
 }
 
+// Modelled time of the M - 1 products of a step for a block of B vectors by the
+// term kernels, in microseconds: launches of 2.9 us (plain ELL; the graph's
+// rate) or 6.5 us (a patch's chain of latencies) at least, else their bytes at
+// the rates these kernels reach (5.0, staged 4.8, block pairs 4.1 TB/s).
+static double terms_us(const tbpm_ham *ham, int M, int B)
+{
+    const double n = (double)ham->n, e = ham->dtype == TBPM_C128 ? 16.0 : 8.0;
+    const int nw = (ham->ell_w + 3) / 4;
+    const double products = M - 1;
+    if (!ham->patched)
+        return products * std::max(2.9, n * (ham->ell_w * (e + 4.0) + 11.0 / 3.0 * e * B) / 5.0e6);
+    const double h = 8.0 * nw + (ham->vidx ? 4.0 * nw + (ham->vdiag ? e / 2 : 0.0) : ham->ell_w * e);
+    if (B == 1)
+        return products / 2 * std::max(6.5, n * (h + 5.0 * e) / 5.0e6);
+    if (block_pairs(ham, B))
+        return products / 2 * std::max(6.5, n * (h + 5.0 * e * B) / 4.1e6);
+    return products * std::max(6.5, n * (h + 11.0 / 3.0 * e * B) / 4.8e6);
+}
+
+bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, int>> &blocks)
+{
+    const tbpm_ham::StepPlan &p = ham->steps;
+    if (p.ntiles == 0 || M < 2)
+        return false;
+    double tiles = 0.0, terms = 0.0;
+    for (auto &blk : blocks) {
+        tiles += (double)((M - 1 + p.depth - 1) / p.depth) *
+                 std::max(1.0, (double)p.ntiles * blk.second / STEP_SLOTS) * p.tile_us;
+        terms += terms_us(ham, M, blk.second);
+    }
+    return tiles < terms;
+}
+
+// The series in launches of several products (tbpm_steps.hip): P -> (Q, S1),
+// then back and forth between (Q, S1) and (P, S2), the series in O throughout.
+static tbpm_status apply_series_steps(const tbpm_ham *ham, hipStream_t st, int B, const double *c, int M,
+                                      double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
+                                      double *partials, int *nblk, SeriesProfile *prof, std::string &err)
+{
+    const tbpm_ham::StepPlan &p = ham->steps;
+    StepArgs a{};
+    a.clo_ptr = p.clo_ptr;
+    a.layer = p.layer;
+    a.rows = p.rows;
+    a.lcol = p.lcol;
+    a.lde = p.lde;
+    a.depth = p.depth;
+    a.max_rows = p.max_rows;
+    a.ntiles = p.ntiles;
+    a.val = ham->val;
+    a.vsel = p.vsel;
+    a.vtab = ham->vtab;
+    a.vdiag = ham->vdiag;
+    a.vdiag_real = ham->vdiag_real;
+    a.table_size = ham->vtab ? ham->table_size : 0;
+    a.ld = ham->ell_ld;
+    a.w = ham->ell_w;
+    a.B = B;
+    a.stride = ham->n;
+    a.self = p.self;
+    a.out = bf.O;
+    a.partials = partials;
+    a.scale1 = 1.0 / rescale;
+    a.scale = 2.0 / rescale;
+    // launches of nearly equal length
+    const int launches = (M - 1 + p.depth - 1) / p.depth;
+    void *x[2] = {bf.Q, bf.P}, *y[2] = {bf.S1, bf.S2};
+    int m = 0;                                       // newest term formed
+    for (int i = 0; i < launches; ++i) {
+        const bool last = i + 1 == launches;
+        a.count = (M - 1 - m + launches - i - 1) / (launches - i);
+        a.x = i == 0 ? bf.P : x[(i - 1) % 2];
+        a.y = i == 0 ? nullptr : y[(i - 1) % 2];
+        a.xout = last ? nullptr : x[i % 2];
+        a.yout = last ? nullptr : y[i % 2];
+        a.psi0 = last && dots ? psi0 : nullptr;
+        for (int j = 0; j <= a.count; ++j) {
+            a.c[j][0] = c[2 * (m + j)];
+            a.c[j][1] = c[2 * (m + j) + 1];
+        }
+        const hipError_t e = launch_steps(ham->dtype, p.real, a, st);
+        if (e != hipSuccess) {
+            err = std::string("several products per launch: ") + hipGetErrorString(e);
+            return TBPM_ERR_HIP;
+        }
+        m += a.count;
+        if (prof)
+            prof->launches[K_MID] += 1;
+    }
+    *nblk = (int)p.ntiles;
+    return TBPM_OK;
+}
+
 // O = sum_{m<M} c_m T_m(H/rho) P (see tbpm_engine.h).
 tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape &shape, bool pairs, bool clenshaw,
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
-                         double *partials, int *nblk, SeriesProfile *prof, std::string &err, bool skip_first)
+                         double *partials, int *nblk, SeriesProfile *prof, std::string &err, bool skip_first, bool steps)
 {
 #define SER_HIP(expr)                                                                        \
     do {                                                                                     \
@@ -597,6 +720,8 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
         err = "a series needs at least two terms";
         return TBPM_ERR_ARG;
     }
+    if (steps)
+        return apply_series_steps(ham, st, shape.B, c, M, rescale, bf, dots, psi0, partials, nblk, prof, err);
     const int B = shape.B;
     const int64_t n = ham->n;
     const int kind_last = dots ? K_LAST : K_MID;
@@ -1090,8 +1215,9 @@ tbpm_status Job::step()
             s2 = spare[1];
         }
         SeriesBufs bf{P, Q, O, s1, s2};
-        s = apply_series(ham, st, shape, pairs, clenshaw, coeff.data(), M, p.rescale, bf, true, psi0, partials,
-                         &nblk, prof, err, cross && first_done);
+        double *sum = partials + (steps ? (size_t)pending * (size_t)ham->steps.ntiles * (size_t)B * 4 : 0);
+        s = apply_series(ham, st, shape, pairs, clenshaw, coeff.data(), M, p.rescale, bf, true, psi0, sum, &nblk,
+                         prof, err, cross && first_done, steps);
     }
     if (s != TBPM_OK)
         return fail(s, err);
@@ -1106,14 +1232,21 @@ tbpm_status Job::step()
         nblk = dot_grid;
     }
     ++k;
-    if (graph_mode)
+    if (steps) {
+        if (++pending == GRAPH_STEPS || k == p.num_time_steps) {
+            tbpm_status fs = flush_sums();
+            if (fs != TBPM_OK)
+                return fs;
+        }
+    } else if (graph_mode)
         JOB_HIP(launch_reduce_step(partials, nblk, B, corr_dev, norms_dev, kstep, st, p.norm_tol, div_flag));
     else
         JOB_HIP(launch_reduce(partials, nblk, B, corr_dev + (size_t)k * B * 2, norms_dev + (size_t)k * B, st,
                               p.norm_tol, div_flag));
     if (!sites.empty())
-        JOB_HIP(launch_ldos_gather(ham->dtype, psi0, psi_next, n, B, sites_dev, (int)sites.size(), site_dev,
-                                   p.num_time_steps + 1, k, st));
+        for (int b = 0; b < B; b += group())
+            JOB_HIP(launch_ldos_gather(ham->dtype, vec(psi0, b), vec(psi_next, b), n, group(), sites_dev,
+                                       (int)sites.size(), site_dev, p.num_time_steps + 1, k, st));
     if (xs) {
         // psi(t_k) in Pn; the next step's p_1 and partial series in Qn, On
         P = Pn;
@@ -1131,6 +1264,18 @@ tbpm_status Job::step()
         O = oldQ;
     }
     return emit_outputs();
+}
+
+tbpm_status Job::flush_sums()
+{
+    if (pending == 0)
+        return TBPM_OK;
+    const int count = pending;
+    pending = 0;
+    JOB_HIP(launch_reduce_steps(partials, ham->steps.ntiles * (int64_t)shape.B * 4, (int)ham->steps.ntiles, shape.B,
+                                corr_dev, norms_dev, graph_mode ? kstep : nullptr, k - count + 1, count, st, p.norm_tol,
+                                div_flag));
+    return TBPM_OK;
 }
 
 tbpm_status Job::close_block()
@@ -1158,8 +1303,8 @@ tbpm_status Job::close_block()
     if (final_states) {
         const int64_t n = ham->n;
         for (int b = 0; b < B; ++b)
-            JOB_HIP(launch_unpack_state(ham->dtype, P, states_dev + (size_t)b * n * 2, n, B, b,
-                                        ham->patched ? ham->old_of_new : nullptr, st));
+            JOB_HIP(launch_unpack_state(ham->dtype, vec(P, b - b % group()), states_dev + (size_t)b * n * 2, n, group(),
+                                        b % group(), ham->patched ? ham->old_of_new : nullptr, st));
         JOB_HIP(hipMemcpyAsync(final_states + (size_t)r0 * n * 2, states_dev, (size_t)B * n * 16,
                                hipMemcpyDeviceToHost, st));
     }
@@ -1201,7 +1346,7 @@ tbpm_status Job::advance(int max_steps)
             // captured from the current roles, or capture one while there is room
             const bool roles = !first_done && (graph_B != shape.B || (int)graphs.size() < MAX_GRAPHS ||
                                                find_graph() >= 0);
-            if (graph_mode && roles && p.num_time_steps - k >= GRAPH_STEPS && max_steps - done >= GRAPH_STEPS) {
+            if (graph_mode && roles && pending == 0 && p.num_time_steps - k >= GRAPH_STEPS && max_steps - done >= GRAPH_STEPS) {
                 tbpm_status s = graph_steps();
                 if (s != TBPM_OK)
                     return s;
@@ -1213,8 +1358,10 @@ tbpm_status Job::advance(int max_steps)
                 return s;
             ++done;
         }
-        if (k < p.num_time_steps)
-            return TBPM_PENDING;
+        if (k < p.num_time_steps) {
+            tbpm_status s = flush_sums();
+            return s == TBPM_OK ? TBPM_PENDING : s;
+        }
         tbpm_status s = close_block();
         if (s != TBPM_OK)
             return s;

@@ -35,6 +35,8 @@ struct Job {
     // the next step's term 1; that next step then runs its terms 2..M-1 in
     // pairs.  first_done: the previous step's last launch applied this step's
     // term 1.  Roles: psi(t_k) in P, Q and O the first two other vectors.
+    bool steps = false;              // several products per launch (forward recurrence)
+    bool cross_ok = false;
     bool cross = false;
     bool first_done = false;
     bool clenshaw = false;              // series by the backward recurrence (TBPM_SERIES_CLENSHAW)
@@ -129,6 +131,10 @@ struct Job {
     ~Job();
     // validate, compute coefficients and the block plan; no device work
     tbpm_status setup(tbpm_ctx *c, const tbpm_ham *h, const tbpm_params *prm, hipStream_t stream);
+    // turns `steps` off where its vectors do not fit; false if it was off
+    bool without_steps();
+    int vectors() const;             // of n x bmax elements, psi0 among them
+    size_t sums() const;             // doubles of the partial sums: one step's, or (steps) a group of steps'
     // device bytes allocate() will take
     size_t footprint() const;
     tbpm_status allocate();
@@ -148,6 +154,11 @@ struct Job {
     tbpm_status finish(double *corr, double *norms, double *ldos, double *corr_mean = nullptr);
 
   private:
+    // vectors of the current block that are interleaved, and the start of the
+    // group that vector b (a multiple of it) begins: blocks run by `steps` hold
+    // their vectors one after another
+    int group() const { return steps ? 1 : shape.B; }
+    void *vec(void *base, int b) const { return static_cast<char *>(base) + (size_t)b * (size_t)ham->n * elem; }
     void spare_buffers(void *out[3]) const;   // the rotating vectors not in P, Q, O (fixed order)
     void set_roles(void *psi);                 // P = psi; Q, O = the first two other vectors
     tbpm_status emit_outputs();      // snapshots / quasi-eigenstate terms of psi(t_k) (in P)
@@ -155,6 +166,8 @@ struct Job {
     tbpm_status open_block();
     tbpm_status close_block();
     tbpm_status step();
+    tbpm_status flush_sums();        // reduces the partial sums of the steps since the last call (steps)
+    int pending = 0;                 // those steps
     tbpm_status fail(tbpm_status s, const std::string &msg);
 };
 
@@ -180,7 +193,10 @@ struct SeriesProfile {
 tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape &shape, bool pairs, bool clenshaw,
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
                          double *partials, int *nblk, SeriesProfile *prof, std::string &err,
-                         bool skip_first = false);
+                         bool skip_first = false, bool steps = false);
+// whether a series of M terms on blocks of these (first vector, width) takes less
+// time by several products per launch on `ham` (steps above)
+bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, int>> &blocks);
 // A time step of one vector on patch-reordered H whose successor follows it
 // (forward recurrence, M even >= 6): a pair of terms 1 and 2 from P (p_1 to
 // Q, p_2 to spare[0], the series to O), the pairs of terms 3..M-2, and a

@@ -187,6 +187,50 @@ bool bpair_supported(int dtype, int B, int w, int patch_rows, int max_halo);
 
 hipError_t launch_pair(int mode, int dtype, const PairArgs &a, int patch_rows, hipStream_t st);
 int pair_grid(int64_t npatch);
+
+// Several products per launch (tbpm_steps.hip): `count` terms of a series on
+// every tile of a plan, each vector of the block by itself.
+//   start (y null): p_0 = x; out = sum_{j <= count} c[j] p_j, p_1 = scale1 H p_0,
+//                   p_j+1 = scale H p_j - p_j-1;
+//   go on:          x = p_m, y = p_m-1; out += sum_{1 <= j <= count} c[j] p_m+j.
+// out is read and written by row, so it may be any vector but x and y (or
+// xout, yout: p of the last product and the one before it, null at the end of
+// the series).  psi0: per-tile partial sums of <psi0|out>, <out|out> at
+// partials[tile][b][4].
+constexpr double STEP_SLOTS = 512.0;       // workgroups of the step kernel that run at a time (two a CU)
+constexpr int STEP_DEPTH = 19;             // products a plan may reach (a time step's at the default truncation)
+struct StepArgs {
+    const int32_t *clo_ptr, *layer, *rows; // the plan (StepPlan)
+    const uint64_t *lcol;
+    const uint32_t *vsel;
+    int64_t lde;
+    int32_t depth, max_rows;
+    int64_t ntiles;
+    const void *val;                       // ELL values [w][ld], or (vtab non-null) the value table
+    const void *vtab, *vdiag;
+    int64_t ld;
+    int32_t w, table_size, vdiag_real, B, count, self;
+    int64_t stride;                        // between the block's vectors
+    const void *x, *y;
+    void *xout, *yout, *out;
+    const void *psi0;
+    double *partials;
+    double scale1, scale;
+    double c[STEP_DEPTH + 1][2];
+};
+// rows a closure may have for the step kernel of this precision and row length
+// (0: not compiled); real: every stored value has a zero imaginary part
+int step_closure_max(int dtype, int w, bool real);
+hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st);
+// closures of the tiles (rows tile_rows[tile_ptr[i] ..]) to `depth` hops: layer
+// counts and overflow flags; with rows non-null also the closures' rows, local
+// columns and value bytes at clo_ptr
+hipError_t launch_step_plan(const int32_t *col, int64_t ld, int w, int depth, int cap, int tiles,
+                            const int32_t *tile_ptr, const int32_t *tile_rows, int32_t *layer, int32_t *overflow,
+                            const int32_t *clo_ptr, int32_t *rows, uint64_t *lcol, uint32_t *vsel, int64_t lde,
+                            const uint32_t *vidx, bool self, hipStream_t st);
+hipError_t launch_step_facts(int dtype, const int32_t *col, const void *val, int64_t n, int64_t ld, int w,
+                             int32_t *flag, hipStream_t st);   // bit 0: complex values, bit 1: a row without its own column
 hipError_t launch_halo_ell(int dtype, const int32_t *col, const void *val, int64_t ld, int32_t w,
                            const int32_t *halo_rows, int64_t nhalo, int64_t ldh, int32_t *hcol, void *hval,
                            hipStream_t st);
@@ -213,6 +257,10 @@ hipError_t launch_reduce(const double *partials, int nblocks, int B, double *cor
 // advanced by one: corr[k][b], norms[k][b] for rows of B (graph-replayable)
 hipError_t launch_reduce_step(const double *partials, int nblocks, int B, double *corr, double *norms, int32_t *kstep,
                               hipStream_t st, double tol = 0.0, int32_t *flag = nullptr);
+// the reductions of `count` steps, step i from partials + i * stride into row k0 + i (kstep: from
+// the device counter instead, advanced by count)
+hipError_t launch_reduce_steps(const double *partials, int64_t stride, int nblocks, int B, double *corr, double *norms,
+                               int32_t *kstep, int64_t k0, int count, hipStream_t st, double tol, int32_t *flag);
 hipError_t launch_set_counter(int32_t *counter, int32_t value, hipStream_t st);
 // moments: partials of `count` consecutive MOM0/MOM launches (launch j at
 // partials + j * stride, [nblocks][B][4]) summed in a fixed order into
@@ -241,6 +289,9 @@ struct QeFactors {
 };
 hipError_t launch_qe_accumulate(int dtype, const void *psi, int64_t n, double *qe, int count, const QeFactors &f,
                                 hipStream_t st);
+// plan of several products per launch of a stored H (tbpm_plan.cpp)
+hipError_t build_steps(tbpm_ham *ham, hipStream_t st);
+void free_steps(tbpm_ham *ham);
 // analysis / conversion of an uploaded CSR (int64 row_ptr, int32 col, c128 val)
 hipError_t launch_csr_check(const int64_t *rp, const int32_t *col, const double *val, int64_t n, int64_t nnz,
                             unsigned long long *res /*[4]: flags, maxrow, gersh bits, maxabs bits*/,
@@ -334,6 +385,17 @@ struct tbpm_ham {
     std::vector<int32_t> h_patch_ptr;
     mutable std::vector<int32_t> h_ell_col;
     mutable std::mutex host_mu;
+    // tiles of several products per launch (empty: ntiles 0), device arrays
+    struct StepPlan {
+        int64_t ntiles = 0;
+        int32_t depth = 0, max_rows = 0;
+        double tile_us = 0.0;           // modelled time of a tile and launch (two workgroups a CU)
+        bool real = false, self = false;   // all values real; every row has a slot in its own column
+        int64_t lde = 0;                // closure entries of all tiles
+        int32_t *clo_ptr = nullptr, *layer = nullptr, *rows = nullptr;
+        uint64_t *lcol = nullptr;
+        uint32_t *vsel = nullptr;
+    } steps;
     double halo_fraction = 0.0;
     int32_t max_halo = 0;               // largest halo of a patch, in rows
     mutable std::atomic<int> users{0};   // queued or running requests using this H

@@ -93,6 +93,8 @@ extern "C" tbpm_status tbpm_propagate_dos_noalloc(tbpm_ctx *ctx, const tbpm_ham 
     job.direct_norms = norms;
     tbpm_status s = job.setup(ctx, ham, params, ctx->stream);
     if (s == TBPM_OK && job.arena_need() > NOALLOC_SCRATCH_BYTES)
+        (void)job.without_steps();                  // the term kernels may take fewer vectors
+    if (s == TBPM_OK && job.arena_need() > NOALLOC_SCRATCH_BYTES)
         s = job.fail_with(TBPM_ERR_TOO_LARGE,
                           "the propagation needs " + std::to_string(job.arena_need()) +
                               " bytes of device buffers; the allocation-free scratch area holds " +

@@ -40,6 +40,7 @@ struct ResponseRun {
     int max_grid = 8;
     bool pairs = false;
     bool clenshaw = false;
+    bool steps = false;
     KernelShape shape{};
     std::string error;
 
@@ -94,6 +95,7 @@ struct ResponseRun {
         shape = choose_shape(ham, 1, ctx->num_cu, p.lanes_per_row);
         pairs = ham->patched && pair_supported(ham->ell_w, ham->patch_rows);
         clenshaw = ctx->series.load() == TBPM_SERIES_CLENSHAW;
+        steps = !clenshaw && !ctx->profiling && steps_apply(ham, M, {{0, 1}});
         max_grid = std::max(shape.grid, op_dot_grid(ham->n));
         if (pairs)
             max_grid = std::max<int64_t>(max_grid, ham->npatch);
@@ -162,7 +164,7 @@ struct ResponseRun {
                     return fail(TBPM_ERR_HIP, "event record failed");
             }
             tbpm_status s = apply_series(ham, st, shape, pairs, clenshaw, c.data(), m, p.rescale, bf, false, nullptr,
-                                         partials, &nblk, timed ? &sp : nullptr, err);
+                                         partials, &nblk, timed ? &sp : nullptr, err, false, steps);
             if (timed)
                 profs.push_back(sp);
             return s == TBPM_OK ? s : fail(s, err);

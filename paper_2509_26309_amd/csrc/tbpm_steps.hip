@@ -1,0 +1,525 @@
+// Several Chebyshev products per launch on tiles of a sparse H (gfx950).
+//
+// A time step is 19 products with H.  One product per launch streams every
+// vector through memory each time; here a workgroup owns a tile of rows of one
+// vector and forms K consecutive products for it in one launch, with the rows
+// within K hops of the tile (its closure) recomputed on chip: product j of K
+// is formed for the rows within K - j hops.  p_m and p_m-1 of the closure live
+// in two LDS buffers that take turns (p_m+1 replaces p_m-1, one barrier a
+// product), H's rows (local columns, values) in registers for all K products,
+// and the series sum c_m p_m of the tile's own rows in FP64 registers.  So a
+// launch reads the closure's vectors once and writes the tile's once for K
+// products, at the price of the closure's extra rows.
+//
+// What bounds it: LDS bandwidth and issue rate (about one clock per CU for a
+// row and product: W gathers, an old value and a store of 16 bytes), no longer
+// memory.
+//
+// Plan (StepPlan): tiles of at most 1024 rows; per tile the closure's rows in
+// order of hop distance (the tile's own first, each layer ascending), the
+// number of rows within d hops for d <= depth, and 16-bit local columns of the
+// rows within depth - 1 hops, and a byte per slot that selects its value: its
+// value table index, or without a table its stored slot.  step_plan_kernel builds it on the device by
+// breadth-first search from the stored ELL columns.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "tbpm_device.h"
+
+namespace tbpm {
+
+constexpr int SWG = 1024;                  // lanes per workgroup
+constexpr int SP_CAP = 6144;               // most rows of a closure the plan kernel takes
+constexpr int SP_HASH = 16384;             // slots of its row -> local index table (LDS)
+
+// ---- the plan ----------------------------------------------------------------------------
+
+struct PlanArgs {
+    const int32_t *col;                    // stored ELL columns [w][ld]
+    int64_t ld;
+    int32_t w, depth, cap, fill;
+    const int32_t *tile_ptr, *tile_rows;   // the tiles' own rows
+    int32_t *layer;                        // [tiles][depth + 1]: rows within d hops
+    int32_t *overflow;                     // [tiles]: closure larger than cap
+    // fill: closures of tile i at entries clo_ptr[i] .. clo_ptr[i+1] - 1
+    const int32_t *clo_ptr;
+    int32_t *rows;
+    uint64_t *lcol;                        // word q of entry e at q * lde + e
+    uint32_t *vsel;                        // the same for value bytes, four a word
+    int64_t lde;
+    const uint32_t *vidx;                  // value table indexes of the rows, or null
+    int32_t self;                          // move the slot of the row's own column to the end
+};
+
+__device__ __forceinline__ int plan_slot(const int32_t *keys, int32_t c)
+{
+    int h = (int)(((uint32_t)c * 2654435761u) >> 18);
+    while (keys[h] != c)                   // c is in the table
+        h = (h + 1) & (SP_HASH - 1);
+    return h;
+}
+
+__global__ __launch_bounds__(SWG) void step_plan_kernel(PlanArgs a)
+{
+    __shared__ int32_t keys[SP_HASH];
+    __shared__ uint16_t at[SP_HASH];
+    __shared__ int32_t list[SP_CAP];
+    __shared__ int count;
+    const int t = threadIdx.x;
+    const int tile = blockIdx.x;
+    const int32_t *own = a.tile_rows + a.tile_ptr[tile];
+    const int n0 = min(a.tile_ptr[tile + 1] - a.tile_ptr[tile], SWG);
+    for (int i = t; i < SP_HASH; i += SWG)
+        keys[i] = -1;
+    if (t == 0)
+        count = n0;
+    __syncthreads();
+    // a new row's slot, or -1 when it is there already
+    auto insert = [&](int32_t c) -> bool {
+        int h = (int)(((uint32_t)c * 2654435761u) >> 18);
+        for (int tries = 0; tries < SP_HASH; ++tries) {
+            const int32_t old = atomicCAS(&keys[h], -1, c);
+            if (old == -1)
+                return true;
+            if (old == c)
+                return false;
+            h = (h + 1) & (SP_HASH - 1);
+        }
+        return false;
+    };
+    if (t < n0) {
+        list[t] = own[t];
+        insert(own[t]);
+    }
+    __syncthreads();
+    int32_t *layer = a.layer + (int64_t)tile * (a.depth + 1);
+    if (t == 0)
+        layer[0] = n0;
+    int f0 = 0, f1 = n0;                    // the newest layer
+    for (int d = 1; d <= a.depth; ++d) {
+        for (int i = f0 + t; i < f1; i += SWG) {
+            const int32_t r = list[i];
+            for (int s = 0; s < a.w; ++s) {
+                const int32_t c = a.col[(int64_t)s * a.ld + r];
+                if (*(volatile int *)&count <= a.cap && insert(c)) {
+                    const int p = atomicAdd(&count, 1);
+                    if (p < SP_CAP)
+                        list[p] = c;
+                }
+            }
+        }
+        __syncthreads();
+        const int found = count;
+        if (found > a.cap) {                // uniform
+            if (t == 0)
+                a.overflow[tile] = 1;
+            return;
+        }
+        // the layer in ascending row order: each row's rank among the layer's
+        int32_t mine[SP_CAP / SWG];
+        int rank[SP_CAP / SWG];
+#pragma unroll
+        for (int k = 0; k < SP_CAP / SWG; ++k) {
+            const int i = f1 + t + k * SWG;
+            rank[k] = 0;
+            mine[k] = i < found ? list[i] : 0;
+            if (i < found)
+                for (int j = f1; j < found; ++j)
+                    rank[k] += list[j] < mine[k] ? 1 : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < SP_CAP / SWG; ++k)
+            if (f1 + t + k * SWG < found)
+                list[f1 + rank[k]] = mine[k];
+        __syncthreads();
+        if (t == 0)
+            layer[d] = found;
+        f0 = f1;
+        f1 = found;
+    }
+    if (t == 0)
+        a.overflow[tile] = 0;
+    if (!a.fill)
+        return;
+    for (int i = t; i < f1; i += SWG)
+        at[plan_slot(keys, list[i])] = (uint16_t)i;
+    __syncthreads();
+    const int64_t e0 = a.clo_ptr[tile];
+    const int inner = f0;                   // rows within depth - 1 hops
+    for (int i = t; i < f1; i += SWG) {
+        a.rows[e0 + i] = list[i];
+        const int32_t r = list[i];
+        int from = a.w;                     // the slot that goes last
+        if (a.self)
+            for (int s = a.w - 1; s >= 0; --s)
+                from = a.col[(int64_t)s * a.ld + r] == r ? s : from;
+        uint64_t word = 0;
+        uint32_t sel = 0;
+        for (int s = 0; s < a.w; ++s) {
+            const int q = s == a.w - 1 && from < a.w ? from : s < from ? s : s + 1;     // the stored slot
+            const uint64_t l = i < inner ? at[plan_slot(keys, a.col[(int64_t)q * a.ld + r])] : 0;
+            const uint32_t k = a.vidx ? (a.vidx[(int64_t)(q / 4) * a.ld + r] >> (8 * (q % 4))) & 255u : (uint32_t)q;
+            word |= l << (16 * (s % 4));
+            sel |= k << (8 * (s % 4));
+            if (s % 4 == 3 || s == a.w - 1) {
+                a.lcol[(int64_t)(s / 4) * a.lde + e0 + i] = word;
+                a.vsel[(int64_t)(s / 4) * a.lde + e0 + i] = sel;
+                word = 0;
+                sel = 0;
+            }
+        }
+    }
+}
+
+// what the stored ELL allows: *flag |= 1 when some value has an imaginary part
+// other than +-0, |= 2 when some row has no slot in its own column
+template <typename T>
+__global__ __launch_bounds__(WG) void step_facts_kernel(const int32_t *col, const T *val, int64_t n, int64_t ld,
+                                                        int32_t w, int32_t *flag)
+{
+    int f = 0;
+    for (int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x; i < n; i += (int64_t)gridDim.x * WG) {
+        bool own = false;
+        for (int s = 0; s < w; ++s) {
+            f |= val[(int64_t)s * ld + i].y != 0 ? 1 : 0;
+            own = own || col[(int64_t)s * ld + i] == i;
+        }
+        f |= own ? 0 : 2;
+    }
+    f |= __shfl_xor(f, 32, 64);
+    f |= __shfl_xor(f, 16, 64);
+    f |= __shfl_xor(f, 8, 64);
+    f |= __shfl_xor(f, 4, 64);
+    f |= __shfl_xor(f, 2, 64);
+    f |= __shfl_xor(f, 1, 64);
+    if (threadIdx.x % 64 == 0 && f)
+        atomicOr(flag, f);
+}
+
+// ---- the products ------------------------------------------------------------------------
+
+constexpr int STW = 512;                   // lanes per workgroup: two workgroups a CU cover each other's loads
+constexpr int STW_OWN = 1024 / STW;        // rows of the tile per lane
+
+// Closure rows per lane: H's columns and values of a lane's rows, and their
+// p_m and p_m-1, take at most 92 (complex64: 72, its rows need more besides) of
+// the 128 registers that two workgroups leave, beyond which some row lengths
+// spill; two buffers of the closure's rows take at most half the LDS.
+template <typename T, int W, bool REAL>
+constexpr int step_rows()
+{
+    const int regs = 2 * ((W + 3) / 4) + W * (int)sizeof(T) / (REAL ? 8 : 4) + (int)sizeof(T) / 2;
+    const int k = (sizeof(T) == 16 ? 92 : 72) / regs;
+    const int most = sizeof(T) == 16 ? 5 : 6;
+    return k > most ? most : k < 2 ? 0 : k;        // 0: not compiled (a tile's 1024 rows take two)
+}
+
+// SELF: the plan has every row's entry in its own column (or a padding slot) in
+// its last slot, which reads the lane's register instead of LDS
+template <typename T, int W, bool REAL, bool SELF>
+__global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void step_kernel(StepArgs a)
+{
+    using E = Elem<T>;
+    using Re = decltype(T{}.x);
+    using V = typename std::conditional<REAL, Re, T>::type;
+    using A = typename E::acc;
+    constexpr int KR = step_rows<T, W, REAL>();
+    constexpr int NW = (W + 3) / 4;
+    constexpr int G = SELF ? W - 1 : W;             // slots gathered from LDS
+    extern __shared__ __attribute__((aligned(16))) char step_lds[];
+    T *pa = reinterpret_cast<T *>(step_lds);        // p_m of the closure
+    T *pb = pa + a.max_rows;                        // p_m+1
+    V *vtab = reinterpret_cast<V *>(pb + a.max_rows);   // value table
+    __shared__ double red[STW / 64][3];
+
+    const int64_t per = (a.ntiles + NXCD - 1) / NXCD;
+    const int64_t u = blockIdx.x / NXCD;
+    const int64_t tile = (int64_t)(blockIdx.x % NXCD) * per + u / a.B;
+    const int b = (int)(u % a.B);
+    if (u / a.B >= per || tile >= a.ntiles)
+        return;                                     // uniform over the workgroup
+    const int64_t e0 = a.clo_ptr[tile];
+    const int32_t *__restrict__ layer = a.layer + tile * (a.depth + 1);
+    const int K = a.count;                          // products of this launch (<= depth)
+    const int n0 = min(layer[0], STW * STW_OWN);
+    const int nk = min(layer[K], min(KR * STW, a.max_rows));
+    int lim = layer[K - 1];
+    const int t = threadIdx.x;
+    const int64_t shift = (int64_t)b * a.stride;    // the block's vectors lie one after another
+    const T *__restrict__ x = static_cast<const T *>(a.x) + shift;
+    const T *__restrict__ y = static_cast<const T *>(a.y) + shift;
+    const bool cont = a.y != nullptr;               // p_m-1 and the series so far exist
+
+    // H's local columns, value bytes and the rows of the lane's entries t, t + STW, ...
+    int32_t row[KR];
+    uint32_t cw[KR][2 * NW];                        // two 16-bit columns a word
+    uint32_t vw[KR][NW];
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+        const int e = t + k * STW;
+        row[k] = 0;
+        if (e < nk) {
+            row[k] = a.rows[e0 + e];
+#pragma unroll
+            for (int q = 0; q < NW; ++q) {
+                const uint64_t w = a.lcol[(int64_t)q * a.lde + e0 + e];
+                cw[k][2 * q] = (uint32_t)w;
+                cw[k][2 * q + 1] = (uint32_t)(w >> 32);
+                vw[k][q] = a.vsel[(int64_t)q * a.lde + e0 + e];
+            }
+        }
+    }
+    const bool table = a.vtab != nullptr;
+    if (table) {
+        for (int i = t; i < a.table_size; i += STW) {
+            const T h = static_cast<const T *>(a.vtab)[i];
+            if constexpr (REAL)
+                vtab[i] = h.x;
+            else
+                vtab[i] = h;
+        }
+        __syncthreads();
+    }
+    // vectors and diagonals of every row first, so that they are waited for
+    // together; then the values, row by row
+    V v[KR][W];
+    T own[KR], old[KR];                             // p_m and p_m-1 of the lane's rows
+    T so[STW_OWN];                                  // the series of the tile's rows so far
+    V dg[KR];                                       // the row's diagonal
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+        own[k] = old[k] = T{};
+        dg[k] = V{};
+        if (t + k * STW < nk) {
+            own[k] = x[row[k]];
+            if (cont)
+                old[k] = y[row[k]];
+            if (table && a.vdiag) {
+                const T h = diag_value(static_cast<const T *>(a.vdiag), a.vdiag_real, row[k]);
+                if constexpr (REAL)
+                    dg[k] = h.x;
+                else
+                    dg[k] = h;
+            }
+        }
+        if (k < STW_OWN) {
+            so[k < STW_OWN ? k : 0] = T{};
+            if (cont && t + k * STW < n0)
+                so[k < STW_OWN ? k : 0] = (static_cast<const T *>(a.out) + shift)[row[k]];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < KR; ++k) {
+        __builtin_amdgcn_sched_barrier(0);
+        const int e = t + k * STW;
+        if (e < nk) {
+#pragma unroll
+            for (int s = 0; s < W; ++s) {
+                const uint32_t i = (vw[k][s / 4] >> (8 * (s % 4))) & 255u;
+                if (table) {
+                    if (SELF && s < W - 1)          // never the diagonal
+                        v[k][s] = vtab[i];
+                    else
+                        v[k][s] = i == 255u ? dg[k] : vtab[min(i, 254u)];
+                } else {
+                    const T h = static_cast<const T *>(a.val)[(int64_t)i * a.ld + row[k]];
+                    if constexpr (REAL)
+                        v[k][s] = h.x;
+                    else
+                        v[k][s] = h;
+                }
+            }
+            pa[e] = own[k];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    // the series of the tile's own rows so far
+    d2 o[STW_OWN];
+#pragma unroll
+    for (int k = 0; k < STW_OWN; ++k) {
+        o[k] = d2{0.0, 0.0};
+        if (t + k * STW < n0)
+            o[k] = cont ? E::to_d(so[k]) : cmul(d2{a.c[0][0], a.c[0][1]}, E::to_d(own[k]));
+    }
+    __syncthreads();
+
+    for (int j = 1; j <= K; ++j) {
+        const int next = j < K ? layer[K - j - 1] : 0;
+        const double scale = (!cont && j == 1) ? a.scale1 : a.scale;
+        const d2 c{a.c[j][0], a.c[j][1]};
+#pragma unroll
+        for (int k = 0; k < KR; ++k) {
+            const int e = t + k * STW;
+            if (k * STW < lim) {                    // uniform
+                if (e < lim) {
+                    // the columns stay packed: without this the compiler unpacks
+                    // every one of them before the loop and runs out of registers
+#pragma unroll
+                    for (int q = 0; q < (G + 1) / 2; ++q)
+                        asm("" : "+v"(cw[k][q]));
+                    A acc{0, 0};
+                    if constexpr (SELF) {
+                        if constexpr (REAL)
+                            acc = A{v[k][W - 1] * own[k].x, v[k][W - 1] * own[k].y};
+                        else
+                            cmac(acc, (A)v[k][W - 1], (A)own[k]);
+                    }
+#pragma unroll
+                    for (int s = 0; s < G; ++s) {
+                        const T xv = pa[(cw[k][s / 2] >> (16 * (s % 2))) & 0xFFFFu];
+                        if constexpr (REAL) {
+                            acc.x += v[k][s] * xv.x;
+                            acc.y += v[k][s] * xv.y;
+                        } else {
+                            cmac(acc, (A)v[k][s], (A)xv);
+                        }
+                    }
+                    const d2 pn = E::acc_to_d(acc) * scale - E::to_d(old[k]);
+                    old[k] = own[k];
+                    own[k] = E::from_d(pn);
+                    pb[e] = own[k];
+                    if (k < STW_OWN && e < n0)
+                        o[k < STW_OWN ? k : 0] += cmul(c, pn);
+                }
+            }
+        }
+        lim = next;
+        __syncthreads();                            // p_m+1 complete; every read of p_m done
+        T *q = pa;
+        pa = pb;
+        pb = q;
+    }
+
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;            // <psi0|out>, <out|out> of the tile
+#pragma unroll
+    for (int k = 0; k < STW_OWN; ++k) {
+        if (t + k * STW < n0) {
+            const int64_t at = shift + row[k];
+            const T os = E::from_d(o[k]);
+            static_cast<T *>(a.out)[at] = os;
+            if (a.xout) {                           // the next launch goes on from p_m+K, p_m+K-1
+                static_cast<T *>(a.xout)[at] = own[k];
+                static_cast<T *>(a.yout)[at] = old[k];
+            }
+            if (a.psi0) {
+                const d2 p = E::to_d(static_cast<const T *>(a.psi0)[at]);
+                const d2 od = E::to_d(os);
+                s0 += p.x * od.x + p.y * od.y;
+                s1 += p.x * od.y - p.y * od.x;
+                s2 += od.x * od.x + od.y * od.y;
+            }
+        }
+    }
+    if (a.psi0) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            s0 += __shfl_xor(s0, off, 64);
+            s1 += __shfl_xor(s1, off, 64);
+            s2 += __shfl_xor(s2, off, 64);
+        }
+        if (t % 64 == 0) {
+            red[t / 64][0] = s0;
+            red[t / 64][1] = s1;
+            red[t / 64][2] = s2;
+        }
+        __syncthreads();
+        if (t < 3) {
+            double s = 0.0;
+            for (int w = 0; w < STW / 64; ++w)
+                s += red[w][t];
+            a.partials[(tile * a.B + b) * 4 + t] = s;
+        }
+    }
+}
+
+// ---- host ----------------------------------------------------------------------------------
+
+template <typename T, bool REAL>
+static int rows_of(int w)
+{
+    switch (w) {
+    case 3: return step_rows<T, 3, REAL>();
+    case 4: return step_rows<T, 4, REAL>();
+    case 5: return step_rows<T, 5, REAL>();
+    case 8: return step_rows<T, 8, REAL>();
+    case 12: return step_rows<T, 12, REAL>();
+    default: return 0;
+    }
+}
+
+int step_closure_max(int dtype, int w, bool real)
+{
+    const int k = dtype == TBPM_C128 ? (real ? rows_of<d2, true>(w) : rows_of<d2, false>(w))
+                                     : (real ? rows_of<f2, true>(w) : rows_of<f2, false>(w));
+    // two workgroups a CU: half of the 160 KiB, the table's 4 KiB and the sums apart
+    const int fit = (81920 - 4096 - 512) / (2 * (dtype == TBPM_C128 ? 16 : 8));
+    return std::min({k * STW, fit, SP_CAP});
+}
+
+template <typename T, int W, bool REAL, bool SELF>
+static hipError_t launch_w(const StepArgs &a, hipStream_t st)
+{
+    if constexpr (step_rows<T, W, REAL>() == 0) {
+        return hipErrorInvalidValue;
+    } else {
+        const int64_t per = (a.ntiles + NXCD - 1) / NXCD;
+        const size_t lds = (2 * (size_t)a.max_rows + (size_t)a.table_size) * sizeof(T);
+        hipLaunchKernelGGL((step_kernel<T, W, REAL, SELF>), dim3((unsigned)(per * NXCD * a.B)), dim3(STW), lds, st,
+                           a);
+        return hipGetLastError();
+    }
+}
+
+template <typename T, bool REAL>
+static hipError_t launch_t(const StepArgs &a, hipStream_t st)
+{
+    switch (a.w) {
+    case 3: return launch_w<T, 3, REAL, false>(a, st);
+    case 4: return a.self ? launch_w<T, 4, REAL, true>(a, st) : launch_w<T, 4, REAL, false>(a, st);
+    case 5: return a.self ? launch_w<T, 5, REAL, true>(a, st) : launch_w<T, 5, REAL, false>(a, st);
+    case 8: return launch_w<T, 8, REAL, false>(a, st);
+    case 12: return launch_w<T, 12, REAL, false>(a, st);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st)
+{
+    if (a.ntiles <= 0 || a.B < 1 || a.count < 1 || a.count > a.depth || a.depth > STEP_DEPTH || !a.rows || !a.lcol || !a.vsel ||
+        !a.layer || !a.x || !a.out || a.max_rows < 1 || a.max_rows > step_closure_max(dtype, a.w, real) ||
+        (a.xout && !a.yout) || (a.psi0 && !a.partials) || a.table_size < 0 || a.table_size > 256 ||
+        (a.vtab ? a.table_size < 1 : !a.val))
+        return hipErrorInvalidValue;
+    if (dtype == TBPM_C128)
+        return real ? launch_t<d2, true>(a, st) : launch_t<d2, false>(a, st);
+    return real ? launch_t<f2, true>(a, st) : launch_t<f2, false>(a, st);
+}
+
+hipError_t launch_step_plan(const int32_t *col, int64_t ld, int w, int depth, int cap, int tiles,
+                            const int32_t *tile_ptr, const int32_t *tile_rows, int32_t *layer, int32_t *overflow,
+                            const int32_t *clo_ptr, int32_t *rows, uint64_t *lcol, uint32_t *vsel, int64_t lde,
+                            const uint32_t *vidx, bool self, hipStream_t st)
+{
+    if (tiles <= 0 || depth < 1 || depth > STEP_DEPTH || cap < SWG || cap > SP_CAP || w < 1)
+        return hipErrorInvalidValue;
+    PlanArgs a{col, ld, w, depth, cap, rows ? 1 : 0, tile_ptr, tile_rows, layer, overflow, clo_ptr, rows, lcol, vsel, lde,
+               vidx, self ? 1 : 0};
+    hipLaunchKernelGGL(step_plan_kernel, dim3(tiles), dim3(SWG), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_facts(int dtype, const int32_t *col, const void *val, int64_t n, int64_t ld, int w,
+                             int32_t *flag, hipStream_t st)
+{
+    const int g = std::min(elem_grid(n), 2048);
+    if (dtype == TBPM_C128)
+        hipLaunchKernelGGL(step_facts_kernel<d2>, dim3(g), dim3(WG), 0, st, col, (const d2 *)val, n, ld, w, flag);
+    else
+        hipLaunchKernelGGL(step_facts_kernel<f2>, dim3(g), dim3(WG), 0, st, col, (const f2 *)val, n, ld, w, flag);
+    return hipGetLastError();
+}
+
+}  // namespace tbpm

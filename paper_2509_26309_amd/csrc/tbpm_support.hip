@@ -270,6 +270,36 @@ __global__ __launch_bounds__(RWG) void reduce_step_kernel(const double *partials
         kstep[0] = (int32_t)(k + 1);
 }
 
+// the reductions of `count` consecutive steps in one launch, one workgroup each
+// (launches of their own took longer than a small sample's whole step): step i
+// from partials + i * stride into row k0 + i, k0 from the device counter kstep
+// where there is one (advanced afterwards by add_counter_kernel)
+__global__ __launch_bounds__(RWG) void reduce_steps_kernel(const double *partials, int64_t stride, int nblocks, int B,
+                                                           double *corr, double *norms, const int32_t *kstep,
+                                                           int64_t k0, double tol, int32_t *flag)
+{
+    const int64_t k = (kstep ? kstep[0] : k0) + blockIdx.x;
+    reduce_rows(partials + (int64_t)blockIdx.x * stride, nblocks, B, corr + k * B * 2, norms + k * B, tol, flag);
+}
+
+__global__ void add_counter_kernel(int32_t *counter, int32_t by)
+{
+    if (threadIdx.x == 0)
+        counter[0] += by;
+}
+
+hipError_t launch_reduce_steps(const double *partials, int64_t stride, int nblocks, int B, double *corr, double *norms,
+                               int32_t *kstep, int64_t k0, int count, hipStream_t st, double tol, int32_t *flag)
+{
+    if (B < 1 || B > 64 || (B & (B - 1)) != 0 || count < 1)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(reduce_steps_kernel, dim3(count), dim3(RWG), 0, st, partials, stride, nblocks, B, corr, norms,
+                       kstep, k0, tol, flag);
+    if (kstep)
+        hipLaunchKernelGGL(add_counter_kernel, dim3(1), dim3(64), 0, st, kstep, count);
+    return hipGetLastError();
+}
+
 __global__ void set_counter_kernel(int32_t *counter, int32_t value)
 {
     if (threadIdx.x == 0)
