@@ -614,7 +614,7 @@ static int term_kind(const double *c, int m, int M, int &held, bool last_sums, T
 // term kernels, in microseconds: launches of 2.9 us (plain ELL; the graph's
 // rate) or 6.5 us (a patch's chain of latencies) at least, else their bytes at
 // the rates these kernels reach (5.0, staged 4.8, block pairs 4.1 TB/s).
-static double terms_us(const tbpm_ham *ham, int M, int B)
+double terms_us(const tbpm_ham *ham, int M, int B)
 {
     const double n = (double)ham->n, e = ham->dtype == TBPM_C128 ? 16.0 : 8.0;
     const int nw = (ham->ell_w + 3) / 4;

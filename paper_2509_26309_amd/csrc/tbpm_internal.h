@@ -222,13 +222,19 @@ struct StepArgs {
 // (0: not compiled); real: every stored value has a zero imaginary part
 int step_closure_max(int dtype, int w, bool real);
 hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st);
-// closures of the tiles (rows tile_rows[tile_ptr[i] ..]) to `depth` hops: layer
-// counts and overflow flags; with rows non-null also the closures' rows, local
+constexpr int STEP_CLOSURE = 6144;         // most rows of a closure that launch_step_plan takes (its cap)
+// closures of the tiles (tile[2 i], tile[2 i + 1]: first and number of their
+// rows in tile_rows) to `depth` hops: layer counts, the last of them 0 where the
+// closure is over the cap; with rows non-null also the closures' rows, local
 // columns and value bytes at clo_ptr
 hipError_t launch_step_plan(const int32_t *col, int64_t ld, int w, int depth, int cap, int tiles,
-                            const int32_t *tile_ptr, const int32_t *tile_rows, int32_t *layer, int32_t *overflow,
+                            const int32_t *tile, const int32_t *tile_rows, int32_t *layer,
                             const int32_t *clo_ptr, int32_t *rows, uint64_t *lcol, uint32_t *vsel, int64_t lde,
                             const uint32_t *vidx, bool self, hipStream_t st);
+// cuts each tile in two, in place: the first part has cuts[i] of its rows
+hipError_t launch_step_split(const int32_t *col, int64_t ld, int w, int tiles, const int32_t *tile, int32_t *tile_rows,
+                             int32_t *cuts, hipStream_t st);
+hipError_t launch_iota(int32_t *p, int64_t n, hipStream_t st);
 hipError_t launch_step_facts(int dtype, const int32_t *col, const void *val, int64_t n, int64_t ld, int w,
                              int32_t *flag, hipStream_t st);   // bit 0: complex values, bit 1: a row without its own column
 hipError_t launch_halo_ell(int dtype, const int32_t *col, const void *val, int64_t ld, int32_t w,
@@ -291,6 +297,8 @@ hipError_t launch_qe_accumulate(int dtype, const void *psi, int64_t n, double *q
                                 hipStream_t st);
 // plan of several products per launch of a stored H (tbpm_plan.cpp)
 hipError_t build_steps(tbpm_ham *ham, hipStream_t st);
+// modelled time (us) of M - 1 products for a block of B vectors by the term kernels (tbpm_engine.cpp)
+double terms_us(const tbpm_ham *ham, int M, int B);
 void free_steps(tbpm_ham *ham);
 // analysis / conversion of an uploaded CSR (int64 row_ptr, int32 col, c128 val)
 hipError_t launch_csr_check(const int64_t *rp, const int32_t *col, const double *val, int64_t n, int64_t nnz,

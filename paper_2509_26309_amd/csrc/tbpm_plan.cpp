@@ -1,15 +1,13 @@
 // Plans for several products with H per launch (tbpm_steps.hip): which rows
-// form a tile, and the closure of each tile to a number of hops.
+// form a tile, to how many hops, and the closure of each tile.
 //
 // Tiles are compact regions of the sparsity graph of at most 1024 rows: the
 // patches of a patch-reordered H, or (plain ELL) regions grown by breadth-first
 // search here.  A tile whose closure is too large for the kernel (patches of
-// several pieces, above all) is cut into its connected pieces, or in half.
-// The closures themselves are built on the device.
+// several pieces, above all) is cut in two until its parts fit.  Everything
+// per row happens on the device; the host sees a few numbers per tile.
 #include <algorithm>
-#include <cstdio>
-#include <cstdlib>
-#include <cstring>
+#include <cmath>
 #include <vector>
 
 #include "tbpm_internal.h"
@@ -18,27 +16,22 @@ namespace tbpm {
 
 namespace {
 
-struct Tiles {
-    std::vector<int32_t> ptr{0}, rows;
-    int64_t count() const { return (int64_t)ptr.size() - 1; }
-    void close() { ptr.push_back((int32_t)rows.size()); }
+struct Tile {
+    int32_t begin, count;               // rows: a range of the row list
+    int32_t size;                       // rows of its closure, 0: not known or too many
+    double products;                    // rows formed in all products of a launch
 };
 
-// the stored ELL columns, in host memory
-struct Columns {
-    std::vector<int32_t> c;
-    int64_t ld = 0;
-    int w = 0;
-};
-
-// breadth-first regions of at most `most` rows, one connected piece each
-void grow_tiles(const Columns &h, int64_t n, int most, Tiles &out)
+// breadth-first regions of at most `most` rows, one connected piece each, over
+// the stored ELL columns c [w][ld]; rows ascending within a tile
+void grow_tiles(const std::vector<int32_t> &c, int64_t ld, int w, int64_t n, int most, std::vector<int32_t> &rows,
+                std::vector<Tile> &tiles)
 {
     std::vector<uint8_t> taken((size_t)n, 0);
     std::vector<int32_t> queue;
     int64_t low = 0;
-    int32_t seed = -1;                      // an untaken neighbour of the previous tile
-    while ((int64_t)out.rows.size() < n) {
+    int32_t seed = -1;                  // an untaken neighbour of the previous tile
+    while ((int64_t)rows.size() < n) {
         if (seed < 0 || taken[(size_t)seed]) {
             while (taken[(size_t)low])
                 ++low;
@@ -48,8 +41,8 @@ void grow_tiles(const Columns &h, int64_t n, int most, Tiles &out)
         taken[(size_t)seed] = 1;
         seed = -1;
         for (size_t i = 0; i < queue.size(); ++i)
-            for (int s = 0; s < h.w; ++s) {
-                const int32_t u = h.c[(size_t)(s * h.ld + queue[i])];
+            for (int s = 0; s < w; ++s) {
+                const int32_t u = c[(size_t)(s * ld + queue[i])];
                 if (taken[(size_t)u])
                     continue;
                 if ((int)queue.size() >= most) {
@@ -61,46 +54,8 @@ void grow_tiles(const Columns &h, int64_t n, int most, Tiles &out)
                 queue.push_back(u);
             }
         std::sort(queue.begin(), queue.end());
-        out.rows.insert(out.rows.end(), queue.begin(), queue.end());
-        out.close();
-    }
-}
-
-// cuts rows[0..m) in two: its connected pieces in two groups of about equal
-// size, or a single piece in halves of breadth-first order
-void split_tile(const Columns &h, const int32_t *rows, int m, Tiles &out)
-{
-    auto find = [&](int32_t r) -> int {     // rows are ascending
-        const int32_t *p = std::lower_bound(rows, rows + m, r);
-        return p != rows + m && *p == r ? (int)(p - rows) : -1;
-    };
-    std::vector<uint8_t> taken((size_t)m, 0);
-    std::vector<int> queue;                 // piece after piece
-    size_t cut = 0;                         // end of the first group of pieces
-    for (int i0 = 0; i0 < m; ++i0) {
-        if (taken[(size_t)i0])
-            continue;
-        if (cut == 0 && 2 * queue.size() >= (size_t)m)
-            cut = queue.size();
-        size_t i = queue.size();
-        queue.push_back(i0);
-        taken[(size_t)i0] = 1;
-        for (; i < queue.size(); ++i)
-            for (int s = 0; s < h.w; ++s) {
-                const int j = find(h.c[(size_t)(s * h.ld + rows[queue[i]])]);
-                if (j >= 0 && !taken[(size_t)j]) {
-                    taken[(size_t)j] = 1;
-                    queue.push_back(j);
-                }
-            }
-    }
-    if (cut == 0)
-        cut = (size_t)(m + 1) / 2;
-    for (size_t b = 0, e = cut; b < (size_t)m; b = e, e = (size_t)m) {
-        std::sort(queue.begin() + (std::ptrdiff_t)b, queue.begin() + (std::ptrdiff_t)e);
-        for (size_t i = b; i < e; ++i)
-            out.rows.push_back(rows[queue[i]]);
-        out.close();
+        tiles.push_back({(int32_t)rows.size(), (int32_t)queue.size(), 0, 0.0});
+        rows.insert(rows.end(), queue.begin(), queue.end());
     }
 }
 
@@ -109,11 +64,258 @@ void split_tile(const Columns &h, const int32_t *rows, int m, Tiles &out)
 // products run at the rate of the LDS gathers.  Fitted on graphene, complex128
 // (depths 5, 7, 10: 15.8, 17.4, 20.8 us at 1565 to 1900 rows), and the AB
 // bilayer, complex64 (11.1 us at depth 5 and 1770 rows).
-double step_tile_us(int dtype, int w, double rows, double products)
+double tile_time(int dtype, int w, double rows, double products)
 {
     const bool c128 = dtype == TBPM_C128;
     return 3.0 + rows * (c128 ? 0.0045 : 0.0023) + products * (c128 ? 0.00067 : 0.00052) * (w + 4) / 8.0;
 }
+
+// of a time step at the default truncation (19 products), one vector
+double step_time(int depth, double tiles, double tile_us)
+{
+    return (double)((19 + depth - 1) / depth) * std::max(1.0, tiles / STEP_SLOTS) * tile_us;
+}
+
+class Builder {
+  public:
+    Builder(tbpm_ham *h, hipStream_t s) : ham(h), ctx(h->ctx), st(s) {}
+    ~Builder()
+    {
+        (void)hipStreamSynchronize(st);
+        for (void *q : held)
+            ctx->dev_free(q);
+    }
+    hipError_t run();
+
+  private:
+    tbpm_ham *ham;
+    tbpm_ctx *ctx;
+    hipStream_t st;
+    std::vector<void *> held;           // scratch on the device
+    int32_t *d_rows = nullptr;          // every row, tile after tile
+    int32_t *d_tile = nullptr, *d_out = nullptr;
+    size_t tile_cap = 0, out_cap = 0;
+    std::vector<int32_t> io, out;
+
+    hipError_t take(int32_t *&p, size_t ints)
+    {
+        p = (int32_t *)ctx->dev_alloc(ints * 4);
+        if (!p)
+            return hipErrorOutOfMemory;
+        held.push_back(p);
+        return hipSuccess;
+    }
+    // the listed tiles' ranges in d_tile, and room for `ints` results in d_out
+    hipError_t list(const std::vector<Tile> &tiles, const std::vector<int32_t> &which, size_t ints)
+    {
+        io.clear();
+        for (int32_t i : which) {
+            io.push_back(tiles[(size_t)i].begin);
+            io.push_back(tiles[(size_t)i].count);
+        }
+        hipError_t e = hipSuccess;
+        if (io.size() > tile_cap)
+            e = take(d_tile, tile_cap = io.size());
+        if (e == hipSuccess && ints > out_cap)
+            e = take(d_out, out_cap = ints);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(d_tile, io.data(), io.size() * 4, hipMemcpyHostToDevice, st);
+        return e;
+    }
+    hipError_t results(size_t ints)
+    {
+        out.resize(ints);
+        hipError_t e = hipMemcpyAsync(out.data(), d_out, ints * 4, hipMemcpyDeviceToHost, st);
+        return e == hipSuccess ? hipStreamSynchronize(st) : e;
+    }
+    hipError_t measure(std::vector<Tile> &tiles, const std::vector<int32_t> &which, int depth, int cap);
+    hipError_t split(std::vector<Tile> &tiles, const std::vector<int32_t> &which);
+};
+
+// closure sizes of the listed tiles
+hipError_t Builder::measure(std::vector<Tile> &tiles, const std::vector<int32_t> &which, int depth, int cap)
+{
+    const size_t ints = which.size() * (size_t)(depth + 1);
+    hipError_t e = list(tiles, which, ints);
+    if (e == hipSuccess)
+        e = launch_step_plan(ham->col, ham->ell_ld, ham->ell_w, depth, cap, (int)which.size(), d_tile, d_rows, d_out,
+                             nullptr, nullptr, nullptr, nullptr, 0, nullptr, false, st);
+    if (e == hipSuccess)
+        e = results(ints);
+    for (size_t k = 0; e == hipSuccess && k < which.size(); ++k) {
+        const int32_t *layer = &out[k * (size_t)(depth + 1)];
+        Tile &t = tiles[(size_t)which[k]];
+        t.size = layer[depth];
+        t.products = 0.0;
+        for (int d = 0; t.size > 0 && d < depth; ++d)
+            t.products += layer[d];
+    }
+    return e;
+}
+
+// every listed tile in two, in its place
+hipError_t Builder::split(std::vector<Tile> &tiles, const std::vector<int32_t> &which)
+{
+    hipError_t e = list(tiles, which, which.size());
+    if (e == hipSuccess)
+        e = launch_step_split(ham->col, ham->ell_ld, ham->ell_w, (int)which.size(), d_tile, d_rows, d_out, st);
+    if (e == hipSuccess)
+        e = results(which.size());
+    if (e != hipSuccess)
+        return e;
+    std::vector<Tile> next;
+    next.reserve(tiles.size() + which.size());
+    size_t k = 0;
+    for (size_t i = 0; i < tiles.size(); ++i) {
+        const Tile t = tiles[i];
+        if (k < which.size() && (size_t)which[k] == i) {
+            next.push_back({t.begin, out[k], 0, 0.0});
+            next.push_back({t.begin + out[k], t.count - out[k], 0, 0.0});
+            ++k;
+        } else {
+            next.push_back(t);
+        }
+    }
+    tiles.swap(next);
+    return hipSuccess;
+}
+
+#define PLAN_HIP(expr)                                                                       \
+    do {                                                                                     \
+        const hipError_t e_ = (expr);                                                        \
+        if (e_ != hipSuccess)                                                                \
+            return e_;                                                                       \
+    } while (0)
+
+hipError_t Builder::run()
+{
+    const int64_t n = ham->n, ld = ham->ell_ld;
+    const int w = ham->ell_w;
+    int32_t *d_flag = nullptr, facts = 0;
+    PLAN_HIP(take(d_flag, 64));
+    PLAN_HIP(hipMemsetAsync(d_flag, 0, 4, st));
+    PLAN_HIP(launch_step_facts(ham->dtype, ham->col, ham->val, n, ld, w, d_flag, st));
+    PLAN_HIP(hipMemcpyAsync(&facts, d_flag, 4, hipMemcpyDeviceToHost, st));
+    PLAN_HIP(hipStreamSynchronize(st));
+    const bool real = (facts & 1) == 0, self = (facts & 2) == 0;
+    const int cap = step_closure_max(ham->dtype, w, real);
+    if (cap < 1024)
+        return hipSuccess;              // not compiled
+
+    std::vector<Tile> first;
+    int32_t *d_first = nullptr, *d_spare = nullptr;
+    PLAN_HIP(take(d_first, (size_t)n));
+    PLAN_HIP(take(d_rows, (size_t)n));
+    PLAN_HIP(take(d_spare, (size_t)n));
+    if (ham->patched) {
+        for (int64_t q = 0; q < ham->npatch; ++q) {
+            const int32_t b = ham->h_patch_ptr[(size_t)q];
+            first.push_back({b, ham->h_patch_ptr[(size_t)q + 1] - b, 0, 0.0});
+        }
+        PLAN_HIP(launch_iota(d_first, n, st));
+    } else {
+        std::vector<int32_t> c((size_t)w * (size_t)ld), rows;
+        PLAN_HIP(hipMemcpyAsync(c.data(), ham->col, c.size() * 4, hipMemcpyDeviceToHost, st));
+        PLAN_HIP(hipStreamSynchronize(st));
+        grow_tiles(c, ld, w, n, (int)std::min<int64_t>(1024, std::max<int64_t>(64, (n + 255) / 256)), rows, first);
+        PLAN_HIP(hipMemcpyAsync(d_first, rows.data(), (size_t)n * 4, hipMemcpyHostToDevice, st));
+        PLAN_HIP(hipStreamSynchronize(st));
+    }
+
+    // The depth of which a step costs least: for each, tiles whose closures all
+    // fit, those over the cap cut in two until they do.  Nothing is planned that
+    // the term kernels outrun for one vector and (complex64) for blocks of 8.
+    std::vector<Tile> tiles;
+    int depth = 0;
+    double least = std::max(terms_us(ham, 20, 1), ham->dtype == TBPM_C64 ? terms_us(ham, 20, 8) / 8 : 0.0);
+    for (int d : {19, 10, 7, 5}) {
+        if (d == 19 && ham->patched)
+            continue;                   // a patch's rows within 19 hops do not fit
+        std::swap(d_rows, d_spare);     // d_spare: the best tiles so far
+        PLAN_HIP(hipMemcpyAsync(d_rows, d_first, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
+        std::vector<Tile> cut = first;
+        std::vector<int32_t> which;
+        double us = least;
+        while (true) {
+            which.clear();
+            for (size_t i = 0; i < cut.size(); ++i)
+                if (cut[i].size == 0)
+                    which.push_back((int32_t)i);
+            PLAN_HIP(measure(cut, which, d, cap));
+            double rows = 0.0, products = 0.0;
+            std::vector<int32_t> bad;
+            bool far = false;
+            for (int32_t i : which)
+                if (cut[(size_t)i].size == 0) {
+                    bad.push_back(i);
+                    far = far || cut[(size_t)i].count < 8;  // a handful of rows that reach too far
+                }
+            for (const Tile &t : cut) {
+                rows += t.size == 0 ? cap : t.size;
+                products += t.products;
+            }
+            const double tiles_now = (double)(cut.size() + bad.size());
+            us = step_time(d, tiles_now, tile_time(ham->dtype, w, rows / tiles_now, products / tiles_now));
+            if (far || us >= least || bad.empty()) {
+                if (far)
+                    us = least;
+                break;
+            }
+            PLAN_HIP(split(cut, bad));
+        }
+        if (us < least) {
+            least = us;
+            depth = d;
+            tiles.swap(cut);
+        } else {
+            std::swap(d_rows, d_spare);
+        }
+        if (depth == 19 && (double)tiles.size() <= STEP_SLOTS)
+            break;                      // every tile at once, one launch a step
+    }
+    if (depth == 0)
+        return hipSuccess;
+    const size_t nt = tiles.size();
+    std::vector<int32_t> cp(nt + 1, 0);
+    int64_t total = 0;
+    double products = 0.0;
+    int32_t most = 0;
+    for (size_t i = 0; i < nt; ++i) {
+        most = std::max(most, tiles[i].size);
+        products += tiles[i].products;
+        total += tiles[i].size;
+        if (total > INT32_MAX)
+            return hipSuccess;
+        cp[i + 1] = (int32_t)total;
+    }
+    tbpm_ham::StepPlan &p = ham->steps;
+    const size_t words = (size_t)((w + 3) / 4);
+    p.lde = (total + 255) / 256 * 256;
+    p.clo_ptr = (int32_t *)ctx->dev_alloc((nt + 1) * 4);
+    p.layer = (int32_t *)ctx->dev_alloc(nt * (size_t)(depth + 1) * 4);
+    p.rows = (int32_t *)ctx->dev_alloc((size_t)p.lde * 4);
+    p.lcol = (uint64_t *)ctx->dev_alloc(words * (size_t)p.lde * 8);
+    p.vsel = (uint32_t *)ctx->dev_alloc(words * (size_t)p.lde * 4);
+    if (!p.clo_ptr || !p.layer || !p.rows || !p.lcol || !p.vsel)
+        return hipErrorOutOfMemory;
+    std::vector<int32_t> all(nt);
+    for (size_t i = 0; i < nt; ++i)
+        all[i] = (int32_t)i;
+    PLAN_HIP(list(tiles, all, 1));
+    PLAN_HIP(hipMemcpyAsync(p.clo_ptr, cp.data(), (nt + 1) * 4, hipMemcpyHostToDevice, st));
+    PLAN_HIP(launch_step_plan(ham->col, ld, w, depth, cap, (int)nt, d_tile, d_rows, p.layer, p.clo_ptr, p.rows, p.lcol,
+                              p.vsel, p.lde, ham->vidx, self, st));
+    PLAN_HIP(hipStreamSynchronize(st));
+    p.depth = depth;
+    p.max_rows = most;
+    p.tile_us = tile_time(ham->dtype, w, (double)total / (double)nt, products / (double)nt);
+    p.real = real;
+    p.self = self;
+    p.ntiles = (int64_t)nt;
+    ham->bytes += (nt + 1) * 4 + nt * (size_t)(depth + 1) * 4 + (size_t)p.lde * (4 + 12 * words);
+    return hipSuccess;
+}
+#undef PLAN_HIP
 
 }  // namespace
 
@@ -128,181 +330,20 @@ void free_steps(tbpm_ham *ham)
     p = tbpm_ham::StepPlan();
 }
 
-// Builds ham->steps on stream st (left empty where no plan fits).  Only device
-// errors are returned.
+// Builds ham->steps on stream st, left empty where no plan fits or pays, or
+// where memory does not suffice for it (the term kernels need none).
 hipError_t build_steps(tbpm_ham *ham, hipStream_t st)
 {
-    tbpm_ctx *ctx = ham->ctx;
-    const int64_t n = ham->n;
     if (ham->format == TBPM_FMT_CSR || ham->patch_rows > 1024 || step_closure_max(ham->dtype, ham->ell_w, true) == 0)
         return hipSuccess;
-    Columns h;
-    h.ld = ham->ell_ld;
-    h.w = ham->ell_w;
-    auto fetch = [&]() -> hipError_t {
-        if (!h.c.empty())
-            return hipSuccess;
-        h.c.resize((size_t)h.w * (size_t)h.ld);
-        return hipMemcpy(h.c.data(), ham->col, h.c.size() * 4, hipMemcpyDeviceToHost);
-    };
-    // scratch on the device, freed on every way out
-    std::vector<void *> held;
-    auto take = [&](size_t bytes) -> void * {
-        void *q = ctx->dev_alloc(bytes);
-        if (q)
-            held.push_back(q);
-        return q;
-    };
-    auto done = [&](hipError_t e) -> hipError_t {
-        (void)hipStreamSynchronize(st);
-        for (void *q : held)
-            ctx->dev_free(q);
-        if (e != hipSuccess)
-            free_steps(ham);
-        return e;
-    };
-#define PLAN_HIP(expr)                                                                       \
-    do {                                                                                     \
-        const hipError_t e_ = (expr);                                                        \
-        if (e_ != hipSuccess)                                                                \
-            return done(e_);                                                                 \
-    } while (0)
-
-    int32_t facts = 0;
-    int32_t *d_flag = (int32_t *)take(256);
-    if (!d_flag)
-        return done(hipErrorOutOfMemory);
-    PLAN_HIP(hipMemsetAsync(d_flag, 0, 4, st));
-    PLAN_HIP(launch_step_facts(ham->dtype, ham->col, ham->val, n, h.ld, h.w, d_flag, st));
-    PLAN_HIP(hipMemcpyAsync(&facts, d_flag, 4, hipMemcpyDeviceToHost, st));
-    PLAN_HIP(hipStreamSynchronize(st));
-    const bool real = (facts & 1) == 0;
-    const int cap = step_closure_max(ham->dtype, h.w, real);
-    if (cap < 1024)
-        return done(hipSuccess);
-
-    Tiles first;
-    if (ham->patched) {
-        first.rows.resize((size_t)n);
-        for (int64_t i = 0; i < n; ++i)
-            first.rows[(size_t)i] = (int32_t)i;
-        first.ptr = ham->h_patch_ptr;
-    } else {
-        PLAN_HIP(fetch());
-        grow_tiles(h, n, (int)std::min<int64_t>(1024, std::max<int64_t>(64, (n + 255) / 256)), first);
+    hipError_t e;
+    {
+        Builder b(ham, st);
+        e = b.run();
     }
-    // the depth of which a time step at the default truncation (19 products) costs least
-    struct Choice {
-        Tiles tiles;
-        std::vector<int32_t> size;
-        int depth = 0;
-        double tile_us = 0.0, step_us = 1e300;
-    } best;
-    for (int depth : {19, 10, 7, 5}) {
-        // a patch's rows within 19 hops do not fit
-        if (depth == 19 && ham->patched)
-            continue;
-        Tiles good, todo = first;
-        std::vector<int32_t> size, layer, over;
-        double products = 0.0;              // rows formed, over all products of a launch
-        bool fits = true;
-        while (fits && todo.count() > 0) {
-            const int64_t nt = todo.count();
-            const size_t mark = held.size();
-            int32_t *d_ptr = (int32_t *)take((size_t)(nt + 1) * 4), *d_rows = (int32_t *)take(todo.rows.size() * 4),
-                    *d_layer = (int32_t *)take((size_t)nt * (depth + 1) * 4), *d_over = (int32_t *)take((size_t)nt * 4);
-            if (!d_ptr || !d_rows || !d_layer || !d_over)
-                return done(hipErrorOutOfMemory);
-            layer.resize((size_t)nt * (depth + 1));
-            over.resize((size_t)nt);
-            PLAN_HIP(hipMemcpyAsync(d_ptr, todo.ptr.data(), (size_t)(nt + 1) * 4, hipMemcpyHostToDevice, st));
-            PLAN_HIP(hipMemcpyAsync(d_rows, todo.rows.data(), todo.rows.size() * 4, hipMemcpyHostToDevice, st));
-            PLAN_HIP(launch_step_plan(ham->col, h.ld, h.w, depth, cap, (int)nt, d_ptr, d_rows, d_layer, d_over,
-                                      nullptr, nullptr, nullptr, nullptr, 0, nullptr, false, st));
-            PLAN_HIP(hipMemcpyAsync(layer.data(), d_layer, layer.size() * 4, hipMemcpyDeviceToHost, st));
-            PLAN_HIP(hipMemcpyAsync(over.data(), d_over, over.size() * 4, hipMemcpyDeviceToHost, st));
-            PLAN_HIP(hipStreamSynchronize(st));
-            while (held.size() > mark) {
-                ctx->dev_free(held.back());
-                held.pop_back();
-            }
-            Tiles next;
-            for (int64_t i = 0; i < nt; ++i) {
-                const int32_t b = todo.ptr[(size_t)i], e = todo.ptr[(size_t)i + 1];
-                if (!over[(size_t)i]) {
-                    good.rows.insert(good.rows.end(), todo.rows.begin() + b, todo.rows.begin() + e);
-                    good.close();
-                    size.push_back(layer[(size_t)i * (depth + 1) + depth]);
-                    for (int d = 0; d < depth; ++d)
-                        products += layer[(size_t)i * (depth + 1) + d];
-                    continue;
-                }
-                // a handful of rows that reach too far: the graph grows too fast for this depth
-                if (e - b < 8) {
-                    fits = false;
-                    break;
-                }
-                PLAN_HIP(fetch());
-                split_tile(h, todo.rows.data() + b, e - b, next);
-            }
-            todo = std::move(next);
-            if (good.count() + todo.count() > 4 * first.count() + 1024)
-                fits = false;
-        }
-        int64_t total = 0;
-        for (int32_t c : size)
-            total += c;
-        if (!fits || total > INT32_MAX)
-            continue;
-        const double nt = (double)good.count();
-        const double tile_us = step_tile_us(ham->dtype, h.w, (double)total / nt, products / nt);
-        const double step_us = (double)((19 + depth - 1) / depth) * std::max(1.0, nt / STEP_SLOTS) * tile_us;
-        if (step_us < best.step_us) {
-            best.tiles = std::move(good);
-            best.size = std::move(size);
-            best.depth = depth;
-            best.tile_us = tile_us;
-            best.step_us = step_us;
-        }
-        if (getenv("TBPM_PLAN_LOG"))
-            fprintf(stderr, "plan: n %lld first %lld tiles %.0f depth %d mean %.0f amp %.2f avg %.2f real %d tile %.1f us step %.1f us\n", (long long)n, (long long)first.count(), nt, depth, (double)total / nt, (double)total / n, products/depth/n, real, tile_us, step_us);
-        if (depth == 19 && nt <= STEP_SLOTS)
-            break;                          // every tile at once, one launch a step
-    }
-    if (best.depth > 0) {
-        const int depth = best.depth;
-        const int64_t nt = best.tiles.count();
-        std::vector<int32_t> cp((size_t)nt + 1, 0);
-        for (int64_t i = 0; i < nt; ++i)
-            cp[(size_t)i + 1] = cp[(size_t)i] + best.size[(size_t)i];
-        tbpm_ham::StepPlan &p = ham->steps;
-        p.lde = ((int64_t)cp.back() + 255) / 256 * 256;
-        p.clo_ptr = (int32_t *)ctx->dev_alloc((size_t)(nt + 1) * 4);
-        p.layer = (int32_t *)ctx->dev_alloc((size_t)nt * (depth + 1) * 4);
-        p.rows = (int32_t *)ctx->dev_alloc((size_t)p.lde * 4);
-        p.lcol = (uint64_t *)ctx->dev_alloc((size_t)((h.w + 3) / 4) * (size_t)p.lde * 8);
-        p.vsel = (uint32_t *)ctx->dev_alloc((size_t)((h.w + 3) / 4) * (size_t)p.lde * 4);
-        int32_t *d_ptr = (int32_t *)take((size_t)(nt + 1) * 4), *d_rows = (int32_t *)take((size_t)n * 4),
-                *d_over = (int32_t *)take((size_t)nt * 4);
-        if (!p.clo_ptr || !p.layer || !p.rows || !p.lcol || !p.vsel || !d_ptr || !d_rows || !d_over)
-            return done(hipErrorOutOfMemory);
-        PLAN_HIP(hipMemcpyAsync(p.clo_ptr, cp.data(), (size_t)(nt + 1) * 4, hipMemcpyHostToDevice, st));
-        PLAN_HIP(hipMemcpyAsync(d_ptr, best.tiles.ptr.data(), (size_t)(nt + 1) * 4, hipMemcpyHostToDevice, st));
-        PLAN_HIP(hipMemcpyAsync(d_rows, best.tiles.rows.data(), (size_t)n * 4, hipMemcpyHostToDevice, st));
-        PLAN_HIP(launch_step_plan(ham->col, h.ld, h.w, depth, cap, (int)nt, d_ptr, d_rows, p.layer, d_over, p.clo_ptr,
-                                  p.rows, p.lcol, p.vsel, p.lde, ham->vidx, (facts & 2) == 0, st));
-        PLAN_HIP(hipStreamSynchronize(st));
-        p.ntiles = nt;
-        p.depth = depth;
-        p.max_rows = *std::max_element(best.size.begin(), best.size.end());
-        p.tile_us = best.tile_us;
-        p.real = real;
-        p.self = (facts & 2) == 0;
-        ham->bytes += (size_t)(nt + 1) * 4 + (size_t)nt * (depth + 1) * 4 +
-                      (size_t)p.lde * (4 + 12 * (size_t)((h.w + 3) / 4));
-    }
-#undef PLAN_HIP
-    return done(hipSuccess);
+    if (ham->steps.ntiles == 0)
+        free_steps(ham);
+    return e == hipErrorOutOfMemory ? hipSuccess : e;
 }
 
 }  // namespace tbpm

@@ -31,7 +31,7 @@
 namespace tbpm {
 
 constexpr int SWG = 1024;                  // lanes per workgroup
-constexpr int SP_CAP = 6144;               // most rows of a closure the plan kernel takes
+constexpr int SP_CAP = STEP_CLOSURE;       // most rows of a closure the plan kernel takes
 constexpr int SP_HASH = 16384;             // slots of its row -> local index table (LDS)
 
 // ---- the plan ----------------------------------------------------------------------------
@@ -40,9 +40,9 @@ struct PlanArgs {
     const int32_t *col;                    // stored ELL columns [w][ld]
     int64_t ld;
     int32_t w, depth, cap, fill;
-    const int32_t *tile_ptr, *tile_rows;   // the tiles' own rows
-    int32_t *layer;                        // [tiles][depth + 1]: rows within d hops
-    int32_t *overflow;                     // [tiles]: closure larger than cap
+    const int32_t *tiles;                  // [tiles][2]: first row and count, in tile_rows
+    const int32_t *tile_rows;              // the tiles' own rows
+    int32_t *layer;                        // [tiles][depth + 1]: rows within d hops (0 at depth: more than cap)
     // fill: closures of tile i at entries clo_ptr[i] .. clo_ptr[i+1] - 1
     const int32_t *clo_ptr;
     int32_t *rows;
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(SWG) void step_plan_kernel(PlanArgs a)
     __shared__ int count;
     const int t = threadIdx.x;
     const int tile = blockIdx.x;
-    const int32_t *own = a.tile_rows + a.tile_ptr[tile];
-    const int n0 = min(a.tile_ptr[tile + 1] - a.tile_ptr[tile], SWG);
+    const int32_t *own = a.tile_rows + a.tiles[2 * tile];
+    const int n0 = min(a.tiles[2 * tile + 1], SWG);
     for (int i = t; i < SP_HASH; i += SWG)
         keys[i] = -1;
     if (t == 0)
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(SWG) void step_plan_kernel(PlanArgs a)
         const int found = count;
         if (found > a.cap) {                // uniform
             if (t == 0)
-                a.overflow[tile] = 1;
+                layer[a.depth] = 0;
             return;
         }
         // the layer in ascending row order: each row's rank among the layer's
@@ -140,8 +140,6 @@ __global__ __launch_bounds__(SWG) void step_plan_kernel(PlanArgs a)
         f0 = f1;
         f1 = found;
     }
-    if (t == 0)
-        a.overflow[tile] = 0;
     if (!a.fill)
         return;
     for (int i = t; i < f1; i += SWG)
@@ -172,6 +170,106 @@ __global__ __launch_bounds__(SWG) void step_plan_kernel(PlanArgs a)
             }
         }
     }
+}
+
+// Cuts a tile in two: its rows (a range of tile_rows) are put in breadth-first
+// order, piece after piece, and *cut is half of them, or the end of a piece
+// that lies nearer to half than a quarter.  Both parts are left ascending.
+__global__ __launch_bounds__(SWG) void step_split_kernel(const int32_t *col, int64_t ld, int32_t w,
+                                                         const int32_t *tiles, int32_t *tile_rows, int32_t *cuts)
+{
+    constexpr int HS = 4096;
+    __shared__ int32_t keys[HS];            // row -> its place below
+    __shared__ int16_t at[HS];
+    __shared__ int32_t rows[SWG];
+    __shared__ int16_t order[SWG];          // breadth-first
+    __shared__ int32_t seen[SWG];
+    __shared__ int count, seed, cut;
+    const int t = threadIdx.x;
+    int32_t *own = tile_rows + tiles[2 * blockIdx.x];
+    const int m = min(tiles[2 * blockIdx.x + 1], SWG);
+    for (int i = t; i < HS; i += SWG)
+        keys[i] = -1;
+    if (t < m)
+        rows[t] = own[t];
+    seen[t] = 0;
+    if (t == 0) {
+        count = 0;
+        cut = 0;
+    }
+    __syncthreads();
+    if (t < m) {
+        int h = (int)(((uint32_t)rows[t] * 2654435761u) >> 20);
+        while (atomicCAS(&keys[h], -1, rows[t]) != -1)      // the rows are distinct, and fewer than slots
+            h = (h + 1) & (HS - 1);
+        at[h] = (int16_t)t;
+    }
+    __syncthreads();
+    int f0 = 0, f1 = 0;                     // the newest layer in order
+    while (f1 < m) {
+        if (f0 == f1) {                     // a piece is complete: go on from the lowest row not seen
+            if (t == 0) {
+                if (4 * f1 >= m && 4 * f1 <= 3 * m && (cut == 0 || abs(2 * f1 - m) < abs(2 * cut - m)))
+                    cut = f1;
+                seed = SWG;
+            }
+            __syncthreads();
+            if (t < m && !seen[t])
+                atomicMin(&seed, t);
+            __syncthreads();
+            if (t == 0) {
+                order[f1] = (int16_t)seed;
+                seen[seed] = 1;
+                count = f1 + 1;
+            }
+            __syncthreads();
+            f1 = f1 + 1;
+        }
+        const int i = f0 + t;
+        if (i < f1) {
+            const int32_t r = rows[order[i]];
+            for (int s = 0; s < w; ++s) {
+                const int32_t c = col[(int64_t)s * ld + r];
+                int h = (int)(((uint32_t)c * 2654435761u) >> 20);
+                while (keys[h] != c && keys[h] != -1)
+                    h = (h + 1) & (HS - 1);
+                if (keys[h] == c && atomicExch(&seen[at[h]], 1) == 0)
+                    order[atomicAdd(&count, 1)] = at[h];
+            }
+        }
+        __syncthreads();
+        const int found = count;
+        // the layer in ascending order, so that the result does not depend on timing
+        int16_t mine = 0;
+        int rank = 0;
+        if (f1 + t < found) {
+            mine = order[f1 + t];
+            for (int j = f1; j < found; ++j)
+                rank += order[j] < mine ? 1 : 0;
+        }
+        __syncthreads();
+        if (f1 + t < found)
+            order[f1 + rank] = mine;
+        __syncthreads();
+        f0 = f1;
+        f1 = found;
+    }
+    const int half = cut > 0 ? cut : (m + 1) / 2;
+    if (t < m) {
+        const int b = t < half ? 0 : half, e = t < half ? half : m;
+        int rank = 0;
+        for (int j = b; j < e; ++j)
+            rank += order[j] < order[t] ? 1 : 0;
+        own[b + rank] = rows[order[t]];     // rows[] is ascending
+    }
+    if (t == 0)
+        cuts[blockIdx.x] = half;
+}
+
+__global__ __launch_bounds__(WG) void iota_kernel(int32_t *p, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x; i < n; i += (int64_t)gridDim.x * WG)
+        p[i] = (int32_t)i;
 }
 
 // what the stored ELL allows: *flag |= 1 when some value has an imaginary part
@@ -499,15 +597,30 @@ hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st)
 }
 
 hipError_t launch_step_plan(const int32_t *col, int64_t ld, int w, int depth, int cap, int tiles,
-                            const int32_t *tile_ptr, const int32_t *tile_rows, int32_t *layer, int32_t *overflow,
+                            const int32_t *tile, const int32_t *tile_rows, int32_t *layer,
                             const int32_t *clo_ptr, int32_t *rows, uint64_t *lcol, uint32_t *vsel, int64_t lde,
                             const uint32_t *vidx, bool self, hipStream_t st)
 {
     if (tiles <= 0 || depth < 1 || depth > STEP_DEPTH || cap < SWG || cap > SP_CAP || w < 1)
         return hipErrorInvalidValue;
-    PlanArgs a{col, ld, w, depth, cap, rows ? 1 : 0, tile_ptr, tile_rows, layer, overflow, clo_ptr, rows, lcol, vsel, lde,
-               vidx, self ? 1 : 0};
+    PlanArgs a{col, ld, w, depth, cap, rows ? 1 : 0, tile, tile_rows, layer, clo_ptr, rows, lcol, vsel, lde, vidx,
+               self ? 1 : 0};
     hipLaunchKernelGGL(step_plan_kernel, dim3(tiles), dim3(SWG), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_split(const int32_t *col, int64_t ld, int w, int tiles, const int32_t *tile, int32_t *tile_rows,
+                             int32_t *cuts, hipStream_t st)
+{
+    if (tiles <= 0 || w < 1)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(step_split_kernel, dim3(tiles), dim3(SWG), 0, st, col, ld, w, tile, tile_rows, cuts);
+    return hipGetLastError();
+}
+
+hipError_t launch_iota(int32_t *p, int64_t n, hipStream_t st)
+{
+    hipLaunchKernelGGL(iota_kernel, dim3(std::min(elem_grid(n), 4096)), dim3(WG), 0, st, p, n);
     return hipGetLastError();
 }
 
