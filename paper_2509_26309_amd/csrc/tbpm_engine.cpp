@@ -643,11 +643,7 @@ bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, in
     return tiles < terms;
 }
 
-// The series in launches of several products (tbpm_steps.hip): P -> (Q, S1),
-// then back and forth between (Q, S1) and (P, S2), the series in O throughout.
-static tbpm_status apply_series_steps(const tbpm_ham *ham, hipStream_t st, int B, const double *c, int M,
-                                      double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
-                                      double *partials, int *nblk, SeriesProfile *prof, std::string &err)
+StepArgs step_args(const tbpm_ham *ham, int B, double rescale)
 {
     const tbpm_ham::StepPlan &p = ham->steps;
     StepArgs a{};
@@ -655,12 +651,13 @@ static tbpm_status apply_series_steps(const tbpm_ham *ham, hipStream_t st, int B
     a.layer = p.layer;
     a.rows = p.rows;
     a.lcol = p.lcol;
+    a.vsel = p.vsel;
     a.lde = p.lde;
     a.depth = p.depth;
     a.max_rows = p.max_rows;
     a.ntiles = p.ntiles;
+    a.self = p.self;
     a.val = ham->val;
-    a.vsel = p.vsel;
     a.vtab = ham->vtab;
     a.vdiag = ham->vdiag;
     a.vdiag_real = ham->vdiag_real;
@@ -669,11 +666,21 @@ static tbpm_status apply_series_steps(const tbpm_ham *ham, hipStream_t st, int B
     a.w = ham->ell_w;
     a.B = B;
     a.stride = ham->n;
-    a.self = p.self;
-    a.out = bf.O;
-    a.partials = partials;
     a.scale1 = 1.0 / rescale;
     a.scale = 2.0 / rescale;
+    return a;
+}
+
+// The series in launches of several products (tbpm_steps.hip): P -> (Q, S1),
+// then back and forth between (Q, S1) and (P, S2), the series in O throughout.
+static tbpm_status apply_series_steps(const tbpm_ham *ham, hipStream_t st, int B, const double *c, int M,
+                                      double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
+                                      double *partials, int *nblk, SeriesProfile *prof, std::string &err)
+{
+    const tbpm_ham::StepPlan &p = ham->steps;
+    StepArgs a = step_args(ham, B, rescale);
+    a.out = bf.O;
+    a.partials = partials;
     // launches of nearly equal length
     const int launches = (M - 1 + p.depth - 1) / p.depth;
     void *x[2] = {bf.Q, bf.P}, *y[2] = {bf.S1, bf.S2};

@@ -194,6 +194,8 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
                          double *partials, int *nblk, SeriesProfile *prof, std::string &err,
                          bool skip_first = false, bool steps = false);
+// the arguments of a launch of several products on `ham`'s plan that do not change from one to the next
+StepArgs step_args(const tbpm_ham *ham, int B, double rescale);
 // whether a series of M terms on blocks of these (first vector, width) takes less
 // time by several products per launch on `ham` (steps above)
 bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, int>> &blocks);

@@ -211,6 +211,10 @@ struct StepArgs {
     int64_t ld;
     int32_t w, table_size, vdiag_real, B, count, self;
     int64_t stride;                        // between the block's vectors
+    // moments: no series (c, out, psi0 unused); product j from p_m+j-1 sums <p_m+j-1|p_m+j>,
+    // <p_m+j-1|p_m+j-1> at partials + (j - 1) * mom_stride
+    int32_t moments;
+    int64_t mom_stride;
     const void *x, *y;
     void *xout, *yout, *out;
     const void *psi0;

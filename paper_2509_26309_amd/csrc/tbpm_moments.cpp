@@ -39,6 +39,7 @@ struct MomentRun {
     int max_grid = 8;
     int chunk = 1;
     bool pairs = false;               // fused pairs of products (pair_kernel, moment mode)
+    bool steps = false;               // several products per launch (step_kernel); the block's vectors one after another
     void *va = nullptr, *vb = nullptr, *vc = nullptr, *vd = nullptr;
     std::vector<int64_t> site_rows;   // site-localised states (stored rows), else random phases
     // light cone of site-localised states on a patch-reordered H: p_j is zero
@@ -183,6 +184,13 @@ struct MomentRun {
                 pairs = pairs || blk.second == 1;
         if (pairs)
             max_grid = std::max<int64_t>(max_grid, ham->npatch);
+        // several products per launch, where the plan's tiles take less time
+        // (kernel timing counts pairs on patches and products otherwise: patches keep
+        // the pair kernels for it, plain ELL counts a launch's products)
+        steps = !light_cone && !(ctx->profiling && ham->patched) && ham->steps.ntiles > 0 &&
+                steps_us() < products_us();
+        if (steps)
+            max_grid = std::max<int64_t>(max_grid, ham->steps.ntiles);
         // partials of up to 64 launches, at most about 32 MiB of them
         const size_t per = (size_t)max_grid * bmax * 4 * sizeof(double);
         chunk = (int)std::max<size_t>(pairs ? 2 : 1, std::min<size_t>(64, ((size_t)32 << 20) / per));
@@ -190,10 +198,39 @@ struct MomentRun {
         return TBPM_OK;
     }
 
+    // modelled time (us) of a product on every block: by tiles (the sums of each
+    // product add about a fifth), and by the product kernels (launches of 2.9 us,
+    // half of 6.5 on patches, at least; else their bytes at 4.3 TB/s)
+    double steps_us() const
+    {
+        double us = 0.0;
+        for (auto &blk : blocks)
+            us += 1.2 * std::max(1.0, (double)ham->steps.ntiles * blk.second / STEP_SLOTS) * ham->steps.tile_us /
+                  ham->steps.depth;
+        return us;
+    }
+    double products_us() const
+    {
+        const double n = (double)ham->n, e = (double)elem;
+        const int nw = (ham->ell_w + 3) / 4;
+        const double hp = 8.0 * nw + (ham->vidx ? 4.0 * nw + (ham->vdiag ? e / 2 : 0.0) : ham->ell_w * e);
+        double us = 0.0;
+        for (auto &blk : blocks) {
+            const int B = blk.second;
+            if (pairs && B == 1)
+                us += std::max(6.5, n * (hp + 4.0 * e) / 4.3e6) / 2;
+            else if (choose_shape(ham, B, ctx->num_cu, p.lanes_per_row).staged)
+                us += std::max(3.3, n * (hp + 3.0 * e * B) / 4.3e6);
+            else
+                us += std::max(2.9, n * (ham->ell_w * (e + 4.0) + 3.0 * e * B) / 4.3e6);
+        }
+        return us;
+    }
+
     size_t footprint() const
     {
         const size_t n = (size_t)ham->n;
-        return (pairs ? 4 : 2) * n * (size_t)bmax * elem + (size_t)chunk * max_grid * bmax * 4 * sizeof(double) +
+        return (pairs || steps ? 4 : 2) * n * (size_t)bmax * elem + (size_t)chunk * max_grid * bmax * 4 * sizeof(double) +
                (size_t)bmax * kmax * 4 * sizeof(double) + (size_t)bmax * num * 2 * sizeof(double);
     }
 
@@ -216,9 +253,19 @@ struct MomentRun {
         partials = (double *)ctx->dev_alloc((size_t)chunk * max_grid * bmax * 4 * sizeof(double));
         raw = (double *)ctx->dev_alloc((size_t)bmax * kmax * 4 * sizeof(double));
         mu_dev = (double *)ctx->dev_alloc((size_t)bmax * num * 2 * sizeof(double));
-        if (pairs) {
-            vc = ctx->dev_alloc(n * elem);
-            vd = ctx->dev_alloc(n * elem);
+        if (pairs || steps) {
+            vc = ctx->dev_alloc(n * (steps ? bmax : 1) * elem);
+            vd = ctx->dev_alloc(n * (steps ? bmax : 1) * elem);
+        }
+        if (steps && (!vc || !vd)) {                // the product kernels take fewer vectors
+            ctx->dev_free(vc);
+            ctx->dev_free(vd);
+            vc = vd = nullptr;
+            steps = false;
+            if (pairs) {
+                vc = ctx->dev_alloc(n * elem);
+                vd = ctx->dev_alloc(n * elem);
+            }
         }
         if (light_cone) {
             d_order = (int32_t *)ctx->dev_alloc((size_t)ham->npatch * 4);
@@ -259,7 +306,19 @@ struct MomentRun {
             const KernelShape shape = choose_shape(ham, B, ctx->num_cu, p.lanes_per_row, !light_cone);
             const int64_t stride = (int64_t)shape.grid * B * 4;
             // psi0 itself is p_0; init writes the same state to both of its targets
-            if (!site_rows.empty()) {
+            if (steps) {
+                for (int b = 0; b < B; ++b) {
+                    void *q = static_cast<char *>(va) + (size_t)b * n * elem;
+                    SiteRows sr{};
+                    if (!site_rows.empty())
+                        sr.r[0] = site_rows[(size_t)r0 + b];
+                    MOM_HIP(site_rows.empty()
+                                ? launch_init_random(ham->dtype, q, q, ham->n, 1, p.seed,
+                                                     (int64_t)p.first_vector + r0 + b,
+                                                     ham->patched ? ham->old_of_new : nullptr, st)
+                                : launch_init_sites(ham->dtype, q, q, ham->n, 1, sr, st));
+                }
+            } else if (!site_rows.empty()) {
                 SiteRows sr{};
                 for (int b = 0; b < B; ++b)
                     sr.r[b] = site_rows[(size_t)r0 + b];
@@ -330,7 +389,50 @@ struct MomentRun {
                 return TBPM_OK;
             };
             tbpm_status rs = TBPM_OK;
-            if (pairs && B == 1) {
+            if (steps) {
+                // p_m, p_m-1 in one pair of vectors, p_m+K, p_m+K-1 to the other
+                StepArgs sa = step_args(ham, B, p.rescale);
+                const int64_t tstride = ham->steps.ntiles * (int64_t)B * 4;
+                sa.moments = 1;
+                sa.mom_stride = tstride;
+                sa.partials = partials;
+                const int most = std::min(ham->steps.depth, chunk);
+                void *in[2] = {va, nullptr}, *to[2] = {vc, vd}, *spare[2] = {va, vb};
+                int held = 0;                       // products whose sums wait in partials
+                for (int m = 0; m < kmax;) {
+                    // launches of nearly equal length
+                    const int left = (kmax - m + most - 1) / most;
+                    sa.count = prof && m == 0 ? 1 : (kmax - m + left - 1) / left;
+                    if (held + sa.count > chunk) {
+                        MOM_HIP(launch_moment_reduce(partials, (int)ham->steps.ntiles, B, tstride, held, m - held, raw,
+                                                     kmax, st));
+                        held = 0;
+                    }
+                    sa.partials = partials + (int64_t)held * tstride;
+                    sa.x = in[0];
+                    sa.y = in[1];
+                    const bool more = m + sa.count < kmax;
+                    sa.xout = more ? to[0] : nullptr;
+                    sa.yout = more ? to[1] : nullptr;
+                    const size_t ia = ev_used;
+                    if (prof)
+                        MOM_HIP(record(st));
+                    MOM_HIP(launch_steps(ham->dtype, ham->steps.real, sa, st));
+                    if (prof) {                     // product 0 alone (kind 0), then the others (kind 1)
+                        const size_t ib = ev_used;
+                        MOM_HIP(record(st));
+                        spans.push_back({ia, ib, m == 0 ? 0 : 1, sa.count});
+                    }
+                    m += sa.count;
+                    held += sa.count;
+                    in[0] = to[0];
+                    in[1] = to[1];
+                    std::swap(to[0], spare[0]);
+                    std::swap(to[1], spare[1]);
+                }
+                MOM_HIP(launch_moment_reduce(partials, (int)ham->steps.ntiles, B, tstride, held, kmax - held, raw, kmax,
+                                             st));
+            } else if (pairs && B == 1) {
                 // product 0 alone, then pairs (pair_kernel in moment mode), then a single one if left over
                 if ((rs = singles(0, 1, 0)) != TBPM_OK)
                     return rs;

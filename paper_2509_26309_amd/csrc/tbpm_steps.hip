@@ -303,21 +303,60 @@ constexpr int STW = 512;                   // lanes per workgroup: two workgroup
 constexpr int STW_OWN = 1024 / STW;        // rows of the tile per lane
 
 // Closure rows per lane: H's columns and values of a lane's rows, and their
-// p_m and p_m-1, take at most 92 (complex64: 72, its rows need more besides) of
+// p_m and p_m-1, take at most 92 (complex64: 84, its rows need more besides) of
 // the 128 registers that two workgroups leave, beyond which some row lengths
 // spill; two buffers of the closure's rows take at most half the LDS.
 template <typename T, int W, bool REAL>
 constexpr int step_rows()
 {
     const int regs = 2 * ((W + 3) / 4) + W * (int)sizeof(T) / (REAL ? 8 : 4) + (int)sizeof(T) / 2;
-    const int k = (sizeof(T) == 16 ? 92 : 72) / regs;
-    const int most = sizeof(T) == 16 ? 5 : 6;
+    const int k = (sizeof(T) == 16 ? 92 : 84) / regs;
+    const int most = sizeof(T) == 8 ? 6 : REAL ? 5 : 3;
     return k > most ? most : k < 2 ? 0 : k;        // 0: not compiled (a tile's 1024 rows take two)
+}
+
+// Sums of three values over a wave: lane l returns that of value l / 16 (0 for
+// l >= 48).  Halves, then rows of 16 lanes, trade places so that one addition
+// serves two values, and rotations finish each row: 25 instructions, where three
+// sums by shuffles take 54 and the LDS crossbar.
+__device__ __forceinline__ double swap_add(double x, double y, bool halves)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x), v = (uint64_t)__double_as_longlong(y);
+    uint32_t r[2][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t p = (uint32_t)(u >> (32 * q)), s = (uint32_t)(v >> (32 * q));
+        const auto w = halves ? __builtin_amdgcn_permlane32_swap(p, s, false, false)
+                              : __builtin_amdgcn_permlane16_swap(p, s, false, false);
+        r[0][q] = w[0];
+        r[1][q] = w[1];
+    }
+    return __longlong_as_double((long long)(((uint64_t)r[0][1] << 32) | r[0][0])) +
+           __longlong_as_double((long long)(((uint64_t)r[1][1] << 32) | r[1][0]));
+}
+template <int CTRL>
+__device__ __forceinline__ double row_rotate_add(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, false);
+    return x + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum3(double s0, double s1, double s2)
+{
+    // rows of 16: (0, 1, 2, 3) hold parts of s0, s1, s2 and nothing
+    double x = swap_add(s0, s2, true);              // halves: s0, s2
+    double y = swap_add(s1, 0.0, true);             // halves: s1, 0
+    x = swap_add(x, y, false);                      // rows: s0, s1, s2, 0
+    x = row_rotate_add<0x128>(x);                   // row_ror 8, 4, 2, 1
+    x = row_rotate_add<0x124>(x);
+    x = row_rotate_add<0x122>(x);
+    return row_rotate_add<0x121>(x);
 }
 
 // SELF: the plan has every row's entry in its own column (or a padding slot) in
 // its last slot, which reads the lane's register instead of LDS
-template <typename T, int W, bool REAL, bool SELF>
+template <typename T, int W, bool REAL, bool SELF, bool MOM>
 __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void step_kernel(StepArgs a)
 {
     using E = Elem<T>;
@@ -331,7 +370,8 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
     T *pa = reinterpret_cast<T *>(step_lds);        // p_m of the closure
     T *pb = pa + a.max_rows;                        // p_m+1
     V *vtab = reinterpret_cast<V *>(pb + a.max_rows);   // value table
-    __shared__ double red[STW / 64][3];
+    // sums of the waves: <psi0|out>, <out|out>; MOM: <p|p'>, <p|p> of every product
+    __shared__ double red[MOM ? STEP_DEPTH : 1][STW / 64][3];
 
     const int64_t per = (a.ntiles + NXCD - 1) / NXCD;
     const int64_t u = blockIdx.x / NXCD;
@@ -359,6 +399,9 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
     for (int k = 0; k < KR; ++k) {
         const int e = t + k * STW;
         row[k] = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q)
+            vw[k][q] = cw[k][2 * q] = cw[k][2 * q + 1] = 0;
         if (e < nk) {
             row[k] = a.rows[e0 + e];
 #pragma unroll
@@ -385,12 +428,12 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
     // together; then the values, row by row
     V v[KR][W];
     T own[KR], old[KR];                             // p_m and p_m-1 of the lane's rows
-    T so[STW_OWN];                                  // the series of the tile's rows so far
-    V dg[KR];                                       // the row's diagonal
+    V dg[SELF ? 1 : KR];                            // the row's diagonal (SELF: in its place, v[k][W - 1])
 #pragma unroll
     for (int k = 0; k < KR; ++k) {
         own[k] = old[k] = T{};
-        dg[k] = V{};
+        V &diag = SELF ? v[k][W - 1] : dg[SELF ? 0 : k];
+        diag = V{};
         if (t + k * STW < nk) {
             own[k] = x[row[k]];
             if (cont)
@@ -398,49 +441,59 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
             if (table && a.vdiag) {
                 const T h = diag_value(static_cast<const T *>(a.vdiag), a.vdiag_real, row[k]);
                 if constexpr (REAL)
-                    dg[k] = h.x;
+                    diag = h.x;
                 else
-                    dg[k] = h;
+                    diag = h;
             }
         }
-        if (k < STW_OWN) {
-            so[k < STW_OWN ? k : 0] = T{};
-            if (cont && t + k * STW < n0)
-                so[k < STW_OWN ? k : 0] = (static_cast<const T *>(a.out) + shift)[row[k]];
-        }
     }
+    if (table) {
 #pragma unroll
-    for (int k = 0; k < KR; ++k) {
-        __builtin_amdgcn_sched_barrier(0);
-        const int e = t + k * STW;
-        if (e < nk) {
+        for (int k = 0; k < KR; ++k) {
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int s = 0; s < W; ++s) {
                 const uint32_t i = (vw[k][s / 4] >> (8 * (s % 4))) & 255u;
-                if (table) {
-                    if (SELF && s < W - 1)          // never the diagonal
-                        v[k][s] = vtab[i];
-                    else
-                        v[k][s] = i == 255u ? dg[k] : vtab[min(i, 254u)];
-                } else {
-                    const T h = static_cast<const T *>(a.val)[(int64_t)i * a.ld + row[k]];
-                    if constexpr (REAL)
-                        v[k][s] = h.x;
-                    else
-                        v[k][s] = h;
-                }
+                const V h = vtab[min(i, (uint32_t)a.table_size - 1u)];
+                if (SELF && s == W - 1)             // the one slot that can be the diagonal
+                    v[k][s] = i == 255u ? v[k][s] : h;
+                else
+                    v[k][s] = !SELF && i == 255u ? dg[SELF ? 0 : k] : h;
             }
-            pa[e] = own[k];
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < KR; ++k) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < W; ++s) {
+                if (s % 2 == 0)
+                    __builtin_amdgcn_sched_barrier(0);
+                const uint32_t i = (vw[k][s / 4] >> (8 * (s % 4))) & 255u;
+                asm("" : "+v"(row[k]));             // (addresses formed anew rather than kept)
+                const int64_t at = (int64_t)i * a.ld + row[k];
+                if constexpr (REAL)
+                    v[k][s] = static_cast<const Re *>(a.val)[2 * at];
+                else
+                    v[k][s] = static_cast<const T *>(a.val)[at];
+            }
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    // the series of the tile's own rows so far
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+        if (t + k * STW < nk)
+            pa[t + k * STW] = own[k];
+#pragma unroll
+    for (int k = 0; k < STW_OWN; ++k)
+        asm("" : "+v"(row[k]));
+    // the series of the tile's own rows: this launch's terms
     d2 o[STW_OWN];
 #pragma unroll
     for (int k = 0; k < STW_OWN; ++k) {
         o[k] = d2{0.0, 0.0};
-        if (t + k * STW < n0)
-            o[k] = cont ? E::to_d(so[k]) : cmul(d2{a.c[0][0], a.c[0][1]}, E::to_d(own[k]));
+        if (!MOM && !cont)
+            o[k] = cmul(d2{a.c[0][0], a.c[0][1]}, E::to_d(own[k]));
     }
     __syncthreads();
 
@@ -448,6 +501,7 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
         const int next = j < K ? layer[K - j - 1] : 0;
         const double scale = (!cont && j == 1) ? a.scale1 : a.scale;
         const d2 c{a.c[j][0], a.c[j][1]};
+        double m0 = 0.0, m1 = 0.0, m2 = 0.0;
 #pragma unroll
         for (int k = 0; k < KR; ++k) {
             const int e = t + k * STW;
@@ -479,31 +533,71 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
                     old[k] = own[k];
                     own[k] = E::from_d(pn);
                     pb[e] = own[k];
-                    if (k < STW_OWN && e < n0)
-                        o[k < STW_OWN ? k : 0] += cmul(c, pn);
+                    if (k < STW_OWN && e < n0) {
+                        if constexpr (MOM) {        // p in old, p' in own, as stored
+                            const d2 xd = E::to_d(old[k]), yd = E::to_d(own[k]);
+                            m0 += xd.x * yd.x + xd.y * yd.y;
+                            m1 += xd.x * yd.y - xd.y * yd.x;
+                            m2 += xd.x * xd.x + xd.y * xd.y;
+                        } else {
+                            o[k < STW_OWN ? k : 0] += cmul(c, pn);
+                        }
+                    }
                 }
             }
         }
         lim = next;
+        if constexpr (MOM) {
+            const double m = wave_sum3(m0, m1, m2);
+            if (t % 16 == 0 && (t & 48) != 48)
+                red[j - 1][t / 64][(t & 63) / 16] = m;
+        }
         __syncthreads();                            // p_m+1 complete; every read of p_m done
         T *q = pa;
         pa = pb;
         pb = q;
     }
 
+    if constexpr (MOM) {
+        // (every wave's sums are in: the last product ended in a barrier)
+#pragma unroll
+        for (int k = 0; k < STW_OWN; ++k)
+            if (a.xout && t + k * STW < n0) {
+                static_cast<T *>(a.xout)[shift + row[k]] = own[k];
+                static_cast<T *>(a.yout)[shift + row[k]] = old[k];
+            }
+        if (t < 3 * K) {
+            double s = 0.0;
+            for (int w = 0; w < STW / 64; ++w)
+                s += red[t / 3][w][t % 3];
+            a.partials[(int64_t)(t / 3) * a.mom_stride + (tile * a.B + b) * 4 + t % 3] = s;
+        }
+        return;
+    }
+    T so[STW_OWN], p0[STW_OWN];                     // the series before this launch, psi0
+#pragma unroll
+    for (int k = 0; k < STW_OWN; ++k) {
+        so[k] = p0[k] = T{};
+        if (t + k * STW < n0) {
+            if (cont)
+                so[k] = static_cast<const T *>(a.out)[shift + row[k]];
+            if (a.psi0)
+                p0[k] = static_cast<const T *>(a.psi0)[shift + row[k]];
+        }
+    }
     double s0 = 0.0, s1 = 0.0, s2 = 0.0;            // <psi0|out>, <out|out> of the tile
 #pragma unroll
     for (int k = 0; k < STW_OWN; ++k) {
         if (t + k * STW < n0) {
             const int64_t at = shift + row[k];
-            const T os = E::from_d(o[k]);
+            const T os = E::from_d(E::to_d(so[k]) + o[k]);
             static_cast<T *>(a.out)[at] = os;
             if (a.xout) {                           // the next launch goes on from p_m+K, p_m+K-1
                 static_cast<T *>(a.xout)[at] = own[k];
                 static_cast<T *>(a.yout)[at] = old[k];
             }
             if (a.psi0) {
-                const d2 p = E::to_d(static_cast<const T *>(a.psi0)[at]);
+                const d2 p = E::to_d(p0[k]);
                 const d2 od = E::to_d(os);
                 s0 += p.x * od.x + p.y * od.y;
                 s1 += p.x * od.y - p.y * od.x;
@@ -519,15 +613,15 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
             s2 += __shfl_xor(s2, off, 64);
         }
         if (t % 64 == 0) {
-            red[t / 64][0] = s0;
-            red[t / 64][1] = s1;
-            red[t / 64][2] = s2;
+            red[0][t / 64][0] = s0;
+            red[0][t / 64][1] = s1;
+            red[0][t / 64][2] = s2;
         }
         __syncthreads();
         if (t < 3) {
             double s = 0.0;
             for (int w = 0; w < STW / 64; ++w)
-                s += red[w][t];
+                s += red[0][w][t];
             a.partials[(tile * a.B + b) * 4 + t] = s;
         }
     }
@@ -552,8 +646,8 @@ int step_closure_max(int dtype, int w, bool real)
 {
     const int k = dtype == TBPM_C128 ? (real ? rows_of<d2, true>(w) : rows_of<d2, false>(w))
                                      : (real ? rows_of<f2, true>(w) : rows_of<f2, false>(w));
-    // two workgroups a CU: half of the 160 KiB, the table's 4 KiB and the sums apart
-    const int fit = (81920 - 4096 - 512) / (2 * (dtype == TBPM_C128 ? 16 : 8));
+    // two workgroups a CU: half of the 160 KiB, the table's and the sums' 4 KiB apart
+    const int fit = (81920 - 4096 - 4096) / (2 * (dtype == TBPM_C128 ? 16 : 8));
     return std::min({k * STW, fit, SP_CAP});
 }
 
@@ -565,8 +659,11 @@ static hipError_t launch_w(const StepArgs &a, hipStream_t st)
     } else {
         const int64_t per = (a.ntiles + NXCD - 1) / NXCD;
         const size_t lds = (2 * (size_t)a.max_rows + (size_t)a.table_size) * sizeof(T);
-        hipLaunchKernelGGL((step_kernel<T, W, REAL, SELF>), dim3((unsigned)(per * NXCD * a.B)), dim3(STW), lds, st,
-                           a);
+        const dim3 grid((unsigned)(per * NXCD * a.B));
+        if (a.moments)
+            hipLaunchKernelGGL((step_kernel<T, W, REAL, SELF, true>), grid, dim3(STW), lds, st, a);
+        else
+            hipLaunchKernelGGL((step_kernel<T, W, REAL, SELF, false>), grid, dim3(STW), lds, st, a);
         return hipGetLastError();
     }
 }
@@ -587,7 +684,8 @@ static hipError_t launch_t(const StepArgs &a, hipStream_t st)
 hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st)
 {
     if (a.ntiles <= 0 || a.B < 1 || a.count < 1 || a.count > a.depth || a.depth > STEP_DEPTH || !a.rows || !a.lcol || !a.vsel ||
-        !a.layer || !a.x || !a.out || a.max_rows < 1 || a.max_rows > step_closure_max(dtype, a.w, real) ||
+        !a.layer || !a.x || (a.moments ? !a.partials || a.psi0 || a.mom_stride < a.ntiles * (int64_t)a.B * 4 : !a.out) ||
+        a.max_rows < 1 || a.max_rows > step_closure_max(dtype, a.w, real) ||
         (a.xout && !a.yout) || (a.psi0 && !a.partials) || a.table_size < 0 || a.table_size > 256 ||
         (a.vtab ? a.table_size < 1 : !a.val))
         return hipErrorInvalidValue;
