@@ -203,6 +203,7 @@ tbpm_status Job::setup(tbpm_ctx *c, const tbpm_ham *h, const tbpm_params *prm, h
     // by term, so it keeps the term kernels)
     cross_ok = pairs && any_single && !clenshaw && M >= 6 && M % 2 == 0;
     steps = !clenshaw && !ctx->profiling && steps_apply(ham, M, blocks);
+    term_grid = max_grid;
     if (steps)
         max_grid = std::max<int64_t>(max_grid, ham->steps.ntiles);
     cross = cross_ok && !steps;
@@ -227,6 +228,7 @@ bool Job::without_steps()
         return false;
     steps = false;
     cross = cross_ok;
+    max_grid = term_grid;
     return true;
 }
 

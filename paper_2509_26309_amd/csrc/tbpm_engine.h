@@ -41,7 +41,7 @@ struct Job {
     bool first_done = false;
     bool clenshaw = false;              // series by the backward recurrence (TBPM_SERIES_CLENSHAW)
     double *partials = nullptr;
-    int max_grid = 8;
+    int max_grid = 8, term_grid = 8;    // workgroups that write partial sums; without `steps`
     double *corr_dev = nullptr;      // [N_t+1][bmax] complex
     int32_t *div_flag = nullptr;     // device: set by the reductions when a norm leaves norm_tol
     int32_t *div_host = nullptr;     // pinned copy of div_flag, read after a chunk completes

@@ -154,8 +154,11 @@ void tbpm_server::start_request(Request *r)
         s = TBPM_ERR_HIP;
     if (s == TBPM_OK)
         s = job.setup(ctx, r->ham, &prm, r->stream);
-    if (s == TBPM_OK)
+    if (s == TBPM_OK) {
+        if (job.footprint() > r->footprint)          // never more than was admitted
+            job.without_steps();
         s = job.allocate();
+    }
     if (s != TBPM_OK) {
         finish_request(r, s, job.error.empty() ? "request start failed" : job.error);
         return;
@@ -291,6 +294,9 @@ tbpm_status tbpm_submit(tbpm_server *srv, const tbpm_ham *ham, const tbpm_params
         tbpm_status s = probe.setup(srv->ctx, ham, &prm, nullptr);
         if (s != TBPM_OK)
             return s;
+        // several products per launch may take more vectors than the term kernels
+        if (probe.footprint() > srv->budget)
+            probe.without_steps();
         r->footprint = probe.footprint();
         probe.ctx = nullptr;
     }
