@@ -8,9 +8,10 @@ random-phase state, 1024 time steps of 19 fused Chebyshev terms with the
 correlation sums, the copy of C(t) to the host and the DOS transform.
 
 Prints one JSON line: the throughput in Hamiltonian-nnz x Chebyshev-terms per
-second, the roofline of the dominant kernel (the middle Chebyshev term),
-timed live with HIP events on its launch stream, and the CPU oracle timed on
-a bounded sample of the same workload.
+second, the roofline of the kernel of one Chebyshev term (or pair of terms),
+timed with HIP events on its launch stream in a short pass of its own (the
+timed steps may form several products per launch, which has no launch per term),
+and the CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
@@ -116,6 +117,15 @@ def algorithmic_bytes_per_launch(info, n, B, dtype, clenshaw=False):
     return h + (5 - k) * sv * n * B, h, 1
 
 
+def deferred_series_bytes(info, n, B, dtype, terms_per_launch):
+    """Bytes per launch that the forward recurrence saves on average against
+    algorithmic_bytes_per_launch by bringing `out` up to date only where the
+    next launch could no longer: every other pair (a read and a write per four
+    terms), every third single term."""
+    sv = 16 if dtype == "c128" else 8
+    return sv * n * B * (1.0 if terms_per_launch == 2 else 4.0 / 3.0)
+
+
 def traffic_source_hash() -> str:
     return hashlib.sha256(b"".join(open(f, "rb").read() for f in TRAFFIC_SOURCES)).hexdigest()
 
@@ -140,10 +150,11 @@ def bytes_model_text(info, B, terms_per_launch, clenshaw, route):
     elif terms_per_launch == 2:
         v = ("5 vector passes for two products (reads of b_m+1, b_m+2, psi; writes of b_m, b_m-1)" if clenshaw
              else "6 vector passes for two terms (reads of x_m-1, y_m-2; writes of y_m, x_m+1; out read and "
-                  "written once)")
+                  "written by every other pair, so 5 on average are counted)")
     else:
         v = ("4 vector passes (gathered b_m+1, reads of b_m+2 and psi, write of b_m)" if clenshaw
-             else "5 vector passes (gathered x, y read and written, out read and written)")
+             else "11/3 vector passes on average (gathered x, y read and written, out read and written by every "
+                  "third term)")
     return f"{h} + {v}, each pass s_x n B bytes (B = {B})"
 
 
@@ -615,7 +626,6 @@ def main():
         log(f"bench: warmup {i} {time.perf_counter() - t:.2f} s")
 
     kept = []
-    tbpm.tbpm_ctx_set_profiling(ctx.handle, True)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for i in range(args.steps):
@@ -623,7 +633,16 @@ def main():
         log(f"bench: step {i} done at {time.perf_counter() - t0:.2f} s")
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
+
+    # the kernels of single terms (pairs), timed launch by launch in a short pass of their own
+    whole = nt, num_moments, wft_steps
+    nt, num_moments = min(nt, 24), min(num_moments, 256)
+    wft_steps = [k for k in wft_steps if k <= nt]
+    log("bench: kernel timing of the term kernels")
+    tbpm.tbpm_ctx_set_profiling(ctx.handle, True)
+    one_step(0, None)
     tbpm.tbpm_ctx_set_profiling(ctx.handle, False)
+    nt, num_moments, wft_steps = whole
 
     mid_ms, mid_n = tbpm.tbpm_ctx_kernel_time(ctx.handle, 1)
     first_ms, first_n = tbpm.tbpm_ctx_kernel_time(ctx.handle, 0)
@@ -649,6 +668,8 @@ def main():
             alg_bytes, terms_per_launch = h_bytes + 4 * sv * lat.n * B, 2
         else:
             alg_bytes, terms_per_launch = h_bytes + 3 * sv * lat.n * B, 1
+    elif not clenshaw:
+        alg_bytes -= deferred_series_bytes(info, lat.n, B, w["dtype"], terms_per_launch)
     mid_avg_s = mid_ms / max(mid_n, 1) / 1e3
     achieved = alg_bytes / mid_avg_s / 1e9 if mid_n else None
     if args.route == "sites" and info["format"] == 3:
@@ -757,6 +778,10 @@ def main():
                      "forward_recurrence_bytes_per_step": step_bytes if args.route == "propagate" else None,
                      "forward_recurrence_step_equiv_GBps": step_rate,
                      "forward_recurrence_step_equiv_frac": (step_rate / HBM_PEAK_GBS) if step_rate else None,
+                     "timing": "HIP events around each launch in a separate pass of at most 24 time steps; the "
+                               "timed steps form several products per launch where that is faster",
+                     "us_per_time_step": el / (args.steps * nt * blocks_per_bench_step) * 1e6
+                     if args.route == "propagate" else None,
                      "avg_launch_us": mid_avg_s * 1e6, "launches_timed": mid_n,
                      # with Clenshaw the "first" group is the first two products (the first
                      # pair and, when M - 5 is odd, the single product after it)
