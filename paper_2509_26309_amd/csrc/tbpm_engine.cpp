@@ -11,6 +11,9 @@
 #include <cmath>
 #include <cstring>
 
+#include <sys/mman.h>
+#include <unistd.h>
+
 namespace tbpm {
 
 #define JOB_HIP(expr)                                                                        \
@@ -346,11 +349,41 @@ tbpm_status Job::allocate()
     }
     cur_block = 0;
     block_open = false;
+    populate(snaps, snap_steps.size() * n * 16);
+    populate(qe_host, qe_energies.size() * n * 16);
+    populate(final_states, R * n * 16);
     return TBPM_OK;
+}
+
+void Job::populate(void *out, size_t bytes)
+{
+#ifdef MADV_POPULATE_WRITE
+    const uintptr_t page = (uintptr_t)sysconf(_SC_PAGESIZE);
+    const uintptr_t b = (uintptr_t)out & ~(page - 1);
+    const uintptr_t e = ((uintptr_t)out + bytes + page - 1) & ~(page - 1);
+    constexpr uintptr_t PIECE = (uintptr_t)1 << 20;
+    const int workers = out ? (int)std::min<size_t>(4, bytes / (4 * PIECE)) : 0;
+    for (int i = 0; i < workers; ++i)
+        try {
+            populating.emplace_back([=] {
+                for (uintptr_t q = b + i * PIECE; q < e; q += workers * PIECE)
+                    if (madvise((void *)q, std::min(PIECE, e - q), MADV_POPULATE_WRITE) != 0)
+                        return;
+            });
+        } catch (...) {                             // no thread: the copies take the faults
+            return;
+        }
+#else
+    (void)out;
+    (void)bytes;
+#endif
 }
 
 void Job::release()
 {
+    for (std::thread &t : populating)
+        t.join();
+    populating.clear();
     if (!ctx)
         return;
     drop_graphs();

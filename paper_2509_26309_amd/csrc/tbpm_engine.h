@@ -5,6 +5,7 @@
 #pragma once
 
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "tbpm_internal.h"
@@ -93,6 +94,13 @@ struct Job {
     std::vector<double> qe_energies;
     double *qe_host = nullptr;
     double *qe_dev = nullptr;
+
+    // The states above go to memory that the caller has often just mapped: its
+    // pages are faulted in, contents kept, by up to four threads while the GPU
+    // propagates, where the copies at the end would take the faults one by one.
+    // Joined by release(), so never outliving the call.  From 4 MiB per thread.
+    void populate(void *out, size_t bytes);
+    std::vector<std::thread> populating;
 
     std::string error;
 
