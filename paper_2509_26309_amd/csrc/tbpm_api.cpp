@@ -509,6 +509,9 @@ tbpm_status tbpm_build_csr(tbpm_ctx *ctx, const tbpm_csr *csr, int32_t dtype, in
                 return set_err(ctx, TBPM_ERR_OOM, "device allocation of H failed");
             }
             e = launch_to_csr(dtype, d_rp, d_col, d_val, n, nnz, ham->rp, ham->rp64, ham->col, ham->val, st);
+            // a caller who names the format keeps to its kernels and memory
+            if (e == hipSuccess && format == TBPM_FMT_AUTO)
+                e = tbpm::step_slots(ham, d_rp, d_col, d_val, st);
         } else {
             ham->ell_w = std::max(max_row, 1);
             ham->ell_ld = (n + 255) / 256 * 256;

@@ -648,12 +648,14 @@ static int term_kind(const double *c, int m, int M, int &held, bool last_sums, T
 // Modelled time of the M - 1 products of a step for a block of B vectors by the
 // term kernels, in microseconds: launches of 2.9 us (plain ELL; the graph's
 // rate) or 6.5 us (a patch's chain of latencies) at least, else their bytes at
-// the rates these kernels reach (5.0, staged 4.8, block pairs 4.1 TB/s).
+// the rates these kernels reach (5.0, CSR 4.1, staged 4.8, block pairs 4.1 TB/s).
 double terms_us(const tbpm_ham *ham, int M, int B)
 {
     const double n = (double)ham->n, e = ham->dtype == TBPM_C128 ? 16.0 : 8.0;
     const int nw = (ham->ell_w + 3) / 4;
     const double products = M - 1;
+    if (ham->format == TBPM_FMT_CSR)
+        return products * std::max(2.9, ((double)ham->nnz * (e + 4.0) + n * (4.0 + 11.0 / 3.0 * e * B)) / 4.1e6);
     if (!ham->patched)
         return products * std::max(2.9, n * (ham->ell_w * (e + 4.0) + 11.0 / 3.0 * e * B) / 5.0e6);
     const double h = 8.0 * nw + (ham->vidx ? 4.0 * nw + (ham->vdiag ? e / 2 : 0.0) : ham->ell_w * e);
@@ -692,13 +694,13 @@ StepArgs step_args(const tbpm_ham *ham, int B, double rescale)
     a.max_rows = p.max_rows;
     a.ntiles = p.ntiles;
     a.self = p.self;
-    a.val = ham->val;
+    a.val = p.ell_val ? p.ell_val : ham->val;
     a.vtab = ham->vtab;
     a.vdiag = ham->vdiag;
     a.vdiag_real = ham->vdiag_real;
     a.table_size = ham->vtab ? ham->table_size : 0;
-    a.ld = ham->ell_ld;
-    a.w = ham->ell_w;
+    a.ld = p.ld;
+    a.w = p.w;
     a.B = B;
     a.stride = ham->n;
     a.scale1 = 1.0 / rescale;

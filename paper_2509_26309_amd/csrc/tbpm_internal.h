@@ -301,6 +301,9 @@ hipError_t launch_qe_accumulate(int dtype, const void *psi, int64_t n, double *q
                                 hipStream_t st);
 // plan of several products per launch of a stored H (tbpm_plan.cpp)
 hipError_t build_steps(tbpm_ham *ham, hipStream_t st);
+// CSR: the padded copy for ham->steps, of the checked device CSR (none where a
+// row is too long or memory does not suffice)
+hipError_t step_slots(tbpm_ham *ham, const int64_t *rp, const int32_t *col, const double *val, hipStream_t st);
 // modelled time (us) of M - 1 products for a block of B vectors by the term kernels (tbpm_engine.cpp)
 double terms_us(const tbpm_ham *ham, int M, int B);
 void free_steps(tbpm_ham *ham);
@@ -407,6 +410,12 @@ struct tbpm_ham {
         int32_t *clo_ptr = nullptr, *layer = nullptr, *rows = nullptr;
         uint64_t *lcol = nullptr;
         uint32_t *vsel = nullptr;
+        // the slots that the plan counts: H's ELL, or (CSR) a padded copy, whose
+        // columns are freed when the plan is built
+        int32_t w = 0;
+        int64_t ld = 0;
+        int32_t *ell_col = nullptr;
+        void *ell_val = nullptr;
     } steps;
     double halo_fraction = 0.0;
     int32_t max_halo = 0;               // largest halo of a patch, in rows

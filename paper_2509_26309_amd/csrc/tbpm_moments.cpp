@@ -200,7 +200,7 @@ struct MomentRun {
 
     // modelled time (us) of a product on every block: by tiles (the sums of each
     // product add about a fifth), and by the product kernels (launches of 2.9 us,
-    // half of 6.5 on patches, at least; else their bytes at 4.3 TB/s)
+    // half of 6.5 on patches, at least; else their bytes at 4.3 TB/s, CSR 4.1)
     double steps_us() const
     {
         double us = 0.0;
@@ -221,6 +221,8 @@ struct MomentRun {
                 us += std::max(6.5, n * (hp + 4.0 * e) / 4.3e6) / 2;
             else if (choose_shape(ham, B, ctx->num_cu, p.lanes_per_row).staged)
                 us += std::max(3.3, n * (hp + 3.0 * e * B) / 4.3e6);
+            else if (ham->format == TBPM_FMT_CSR)
+                us += std::max(2.9, ((double)ham->nnz * (e + 4.0) + n * (4.0 + 3.0 * e * B)) / 4.1e6);
             else
                 us += std::max(2.9, n * (ham->ell_w * (e + 4.0) + 3.0 * e * B) / 4.3e6);
         }

@@ -23,40 +23,67 @@ struct Tile {
 };
 
 // breadth-first regions of at most `most` rows, one connected piece each, over
-// the stored ELL columns c [w][ld]; rows ascending within a tile
-void grow_tiles(const std::vector<int32_t> &c, int64_t ld, int w, int64_t n, int most, std::vector<int32_t> &rows,
-                std::vector<Tile> &tiles)
+// the stored ELL columns c [w][ld]; rows ascending within a tile.  Pieces of
+// fewer than `small` rows (what growing left over, clusters that vacancies cut
+// off) share tiles, in the order found, so that no workgroup is spent on a few rows.
+void grow_tiles(const std::vector<int32_t> &c, int64_t ld, int w, int64_t n, int most, int small,
+                std::vector<int32_t> &rows, std::vector<Tile> &tiles)
 {
-    std::vector<uint8_t> taken((size_t)n, 0);
-    std::vector<int32_t> queue;
-    int64_t low = 0;
-    int32_t seed = -1;                  // an untaken neighbour of the previous tile
-    while ((int64_t)rows.size() < n) {
-        if (seed < 0 || taken[(size_t)seed]) {
-            while (taken[(size_t)low])
+    constexpr int32_t NONE = -1;
+    std::vector<int32_t> piece((size_t)n, NONE), count;     // of a row; rows of a piece
+    std::vector<int32_t> queue((size_t)most);
+    int64_t low = 0, taken = 0;
+    int32_t seed = NONE;                // an untaken neighbour of the previous piece
+    while (taken < n) {
+        if (seed == NONE || piece[(size_t)seed] != NONE) {
+            while (piece[(size_t)low] != NONE)
                 ++low;
             seed = (int32_t)low;
         }
-        queue.assign(1, seed);
-        taken[(size_t)seed] = 1;
-        seed = -1;
-        for (size_t i = 0; i < queue.size(); ++i)
+        const int32_t id = (int32_t)count.size();
+        int end = 1;
+        queue[0] = seed;
+        piece[(size_t)seed] = id;
+        seed = NONE;
+        for (int i = 0; i < end; ++i)
             for (int s = 0; s < w; ++s) {
-                const int32_t u = c[(size_t)(s * ld + queue[i])];
-                if (taken[(size_t)u])
+                const int32_t u = c[(size_t)(s * ld + queue[(size_t)i])];
+                if (piece[(size_t)u] != NONE)
                     continue;
-                if ((int)queue.size() >= most) {
-                    if (seed < 0)
+                if (end == most) {
+                    if (seed == NONE)
                         seed = u;
                     continue;
                 }
-                taken[(size_t)u] = 1;
-                queue.push_back(u);
+                piece[(size_t)u] = id;
+                queue[(size_t)end++] = u;
             }
-        std::sort(queue.begin(), queue.end());
-        tiles.push_back({(int32_t)rows.size(), (int32_t)queue.size(), 0, 0.0});
-        rows.insert(rows.end(), queue.begin(), queue.end());
+        count.push_back(end);
+        taken += end;
     }
+    // a tile for each piece, small pieces together
+    std::vector<int32_t> tile_of(count.size());
+    int shared = -1;
+    for (size_t q = 0; q < count.size(); ++q) {
+        if (count[q] < small && shared >= 0 && tiles[(size_t)shared].count + count[q] <= most) {
+            tiles[(size_t)shared].count += count[q];
+            tile_of[q] = shared;
+            continue;
+        }
+        tile_of[q] = (int32_t)tiles.size();
+        if (count[q] < small)
+            shared = tile_of[q];
+        tiles.push_back({0, count[q], 0, 0.0});
+    }
+    std::vector<int32_t> at(tiles.size());
+    int32_t begin = 0;
+    for (size_t i = 0; i < tiles.size(); ++i) {
+        tiles[i].begin = at[i] = begin;
+        begin += tiles[i].count;
+    }
+    rows.resize((size_t)n);
+    for (int64_t r = 0; r < n; ++r)
+        rows[(size_t)at[(size_t)tile_of[(size_t)piece[(size_t)r]]]++] = (int32_t)r;
 }
 
 // Time of one tile and launch with two workgroups a CU, in microseconds: the
@@ -78,7 +105,11 @@ double step_time(int depth, double tiles, double tile_us)
 
 class Builder {
   public:
-    Builder(tbpm_ham *h, hipStream_t s) : ham(h), ctx(h->ctx), st(s) {}
+    Builder(tbpm_ham *h, hipStream_t s)
+        : ham(h), ctx(h->ctx), st(s), col(h->steps.ell_col ? h->steps.ell_col : h->col),
+          val(h->steps.ell_val ? h->steps.ell_val : h->val), ld(h->steps.ld), w(h->steps.w)
+    {
+    }
     ~Builder()
     {
         (void)hipStreamSynchronize(st);
@@ -91,6 +122,10 @@ class Builder {
     tbpm_ham *ham;
     tbpm_ctx *ctx;
     hipStream_t st;
+    const int32_t *col;                 // H's slots
+    const void *val;
+    int64_t ld;
+    int w;
     std::vector<void *> held;           // scratch on the device
     int32_t *d_rows = nullptr;          // every row, tile after tile
     int32_t *d_tile = nullptr, *d_out = nullptr;
@@ -138,7 +173,7 @@ hipError_t Builder::measure(std::vector<Tile> &tiles, const std::vector<int32_t>
     const size_t ints = which.size() * (size_t)(depth + 1);
     hipError_t e = list(tiles, which, ints);
     if (e == hipSuccess)
-        e = launch_step_plan(ham->col, ham->ell_ld, ham->ell_w, depth, cap, (int)which.size(), d_tile, d_rows, d_out,
+        e = launch_step_plan(col, ld, w, depth, cap, (int)which.size(), d_tile, d_rows, d_out,
                              nullptr, nullptr, nullptr, nullptr, 0, nullptr, false, st);
     if (e == hipSuccess)
         e = results(ints);
@@ -158,7 +193,7 @@ hipError_t Builder::split(std::vector<Tile> &tiles, const std::vector<int32_t> &
 {
     hipError_t e = list(tiles, which, which.size());
     if (e == hipSuccess)
-        e = launch_step_split(ham->col, ham->ell_ld, ham->ell_w, (int)which.size(), d_tile, d_rows, d_out, st);
+        e = launch_step_split(col, ld, w, (int)which.size(), d_tile, d_rows, d_out, st);
     if (e == hipSuccess)
         e = results(which.size());
     if (e != hipSuccess)
@@ -189,12 +224,11 @@ hipError_t Builder::split(std::vector<Tile> &tiles, const std::vector<int32_t> &
 
 hipError_t Builder::run()
 {
-    const int64_t n = ham->n, ld = ham->ell_ld;
-    const int w = ham->ell_w;
+    const int64_t n = ham->n;
     int32_t *d_flag = nullptr, facts = 0;
     PLAN_HIP(take(d_flag, 64));
     PLAN_HIP(hipMemsetAsync(d_flag, 0, 4, st));
-    PLAN_HIP(launch_step_facts(ham->dtype, ham->col, ham->val, n, ld, w, d_flag, st));
+    PLAN_HIP(launch_step_facts(ham->dtype, col, val, n, ld, w, d_flag, st));
     PLAN_HIP(hipMemcpyAsync(&facts, d_flag, 4, hipMemcpyDeviceToHost, st));
     PLAN_HIP(hipStreamSynchronize(st));
     const bool real = (facts & 1) == 0, self = (facts & 2) == 0;
@@ -215,9 +249,10 @@ hipError_t Builder::run()
         PLAN_HIP(launch_iota(d_first, n, st));
     } else {
         std::vector<int32_t> c((size_t)w * (size_t)ld), rows;
-        PLAN_HIP(hipMemcpyAsync(c.data(), ham->col, c.size() * 4, hipMemcpyDeviceToHost, st));
+        PLAN_HIP(hipMemcpyAsync(c.data(), col, c.size() * 4, hipMemcpyDeviceToHost, st));
         PLAN_HIP(hipStreamSynchronize(st));
-        grow_tiles(c, ld, w, n, (int)std::min<int64_t>(1024, std::max<int64_t>(64, (n + 255) / 256)), rows, first);
+        const int most = (int)std::min<int64_t>(1024, std::max<int64_t>(64, (n + 255) / 256));
+        grow_tiles(c, ld, w, n, most, ham->format == TBPM_FMT_CSR ? most / 8 : 0, rows, first);
         PLAN_HIP(hipMemcpyAsync(d_first, rows.data(), (size_t)n * 4, hipMemcpyHostToDevice, st));
         PLAN_HIP(hipStreamSynchronize(st));
     }
@@ -303,7 +338,7 @@ hipError_t Builder::run()
         all[i] = (int32_t)i;
     PLAN_HIP(list(tiles, all, 1));
     PLAN_HIP(hipMemcpyAsync(p.clo_ptr, cp.data(), (nt + 1) * 4, hipMemcpyHostToDevice, st));
-    PLAN_HIP(launch_step_plan(ham->col, ld, w, depth, cap, (int)nt, d_tile, d_rows, p.layer, p.clo_ptr, p.rows, p.lcol,
+    PLAN_HIP(launch_step_plan(col, ld, w, depth, cap, (int)nt, d_tile, d_rows, p.layer, p.clo_ptr, p.rows, p.lcol,
                               p.vsel, p.lde, ham->vidx, self, st));
     PLAN_HIP(hipStreamSynchronize(st));
     p.depth = depth;
@@ -327,22 +362,59 @@ void free_steps(tbpm_ham *ham)
     ham->ctx->dev_free(p.rows);
     ham->ctx->dev_free(p.lcol);
     ham->ctx->dev_free(p.vsel);
+    ham->ctx->dev_free(p.ell_col);
+    ham->ctx->dev_free(p.ell_val);
     p = tbpm_ham::StepPlan();
+}
+
+// Rows of uneven length stay in CSR, whose kernels read H's values and gather
+// vectors at 4.1 TB/s at best; the tiles' kernel holds H in registers, so the
+// padding to the next width it is compiled for costs no more than those.
+hipError_t step_slots(tbpm_ham *ham, const int64_t *rp, const int32_t *col, const double *val, hipStream_t st)
+{
+    tbpm_ham::StepPlan &p = ham->steps;
+    for (int w : {3, 4, 5, 8, 12})
+        if (p.w == 0 && ham->max_row <= w && step_closure_max(ham->dtype, w, true) > 0)
+            p.w = w;
+    if (p.w == 0 || ham->max_row == 0)
+        return hipSuccess;
+    p.ld = (ham->n + 255) / 256 * 256;
+    const size_t slots = (size_t)p.w * (size_t)p.ld;
+    p.ell_col = (int32_t *)ham->ctx->dev_alloc(slots * 4);
+    p.ell_val = ham->ctx->dev_alloc(slots * (ham->dtype == TBPM_C128 ? 16 : 8));
+    if (!p.ell_col || !p.ell_val) {
+        free_steps(ham);
+        return hipSuccess;
+    }
+    return launch_to_ell(ham->dtype, rp, col, val, ham->n, p.w, p.ld, p.ell_col, p.ell_val, st);
 }
 
 // Builds ham->steps on stream st, left empty where no plan fits or pays, or
 // where memory does not suffice for it (the term kernels need none).
 hipError_t build_steps(tbpm_ham *ham, hipStream_t st)
 {
-    if (ham->format == TBPM_FMT_CSR || ham->patch_rows > 1024 || step_closure_max(ham->dtype, ham->ell_w, true) == 0)
+    tbpm_ham::StepPlan &p = ham->steps;
+    if (ham->format == TBPM_FMT_CSR) {
+        if (!p.ell_val)
+            return hipSuccess;
+    } else {
+        p.w = ham->ell_w;
+        p.ld = ham->ell_ld;
+    }
+    if (ham->patch_rows > 1024 || step_closure_max(ham->dtype, p.w, true) == 0)
         return hipSuccess;
     hipError_t e;
     {
         Builder b(ham, st);
         e = b.run();
     }
-    if (ham->steps.ntiles == 0)
+    if (p.ntiles == 0) {
         free_steps(ham);
+    } else if (p.ell_col) {
+        ham->ctx->dev_free(p.ell_col);
+        p.ell_col = nullptr;
+        ham->bytes += (size_t)p.w * (size_t)p.ld * (ham->dtype == TBPM_C128 ? 16 : 8);
+    }
     return e == hipErrorOutOfMemory ? hipSuccess : e;
 }
 

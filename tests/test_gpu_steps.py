@@ -18,6 +18,7 @@ import time
 import numpy as np
 import pytest
 
+from tb_inputs.lattices import cell_by_name, supercell
 from tb_inputs import graphene, bilayer, honeycomb3, square, sample_sites, current_operator
 
 pytestmark = pytest.mark.gpu
@@ -123,6 +124,41 @@ def test_states_and_sites_equal_the_term_kernels(T, ctx, name, fmt, R, block, dt
     for key in d0:
         if isinstance(d0[key], np.ndarray):
             assert np.abs(d0[key] - d1[key]).max() <= _tol(dtype), key
+
+
+UNEVEN = {
+    # rows of uneven length (CSR, with a padded copy for the tiles): one tile, two,
+    # pieces that vacancies cut off (isolated orbitals among them), wide rows
+    "graphene_one_tile": (lambda: supercell(cell_by_name("graphene"), 13, 11, vacancy_p=0.2, seed=2), 8.2),
+    "graphene": (lambda: supercell(cell_by_name("graphene"), 61, 47, vacancy_p=0.2, seed=3), 8.2),
+    "graphene_clusters": (lambda: supercell(cell_by_name("graphene"), 60, 50, vacancy_p=0.5, seed=4), 8.2),
+    "graphene_complex": (lambda: _gauge(supercell(cell_by_name("graphene"), 60, 50, vacancy_p=0.2, seed=4), 10 ** 6), 8.2),
+    "honeycomb3": (lambda: honeycomb3(41, 37, vacancy_p=0.3, seed=5), 10.0),
+    "square": (lambda: supercell(cell_by_name("square_nnn"), 51, 47, vacancy_p=0.3, seed=6), 4.5),
+}
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("R,block", [(1, 1), (5, 4)])
+@pytest.mark.parametrize("name", list(UNEVEN))
+def test_uneven_rows(T, ctx, orc, name, R, block, dtype):
+    make, rho = UNEVEN[name]
+    lat = make()
+    nt, num = 14, 90
+    ham = ctx.build(lat, dtype=dtype)
+    try:
+        assert T.tbpm_ham_info(ham)["format"] == T.TBPM_FMT_CSR
+        p, _ = T.make_params(rho, nt, R, block=block, seed=3)
+        got = T.tbpm_propagate_dos(ctx.handle, ham, p)
+        p, _ = T.make_params(rho, 0, R, block=block, seed=3)
+        mu = T.tbpm_chebyshev_moments(ctx.handle, ham, p, num)
+    finally:
+        T.tbpm_ham_destroy(ham)
+    _, per, norms, _ = orc.corr_dos(lat, rescale=rho, num_steps=nt, num_vectors=R, seed=3)
+    assert np.abs(got["corr"] - per).max() <= _tol(dtype)
+    assert np.abs(got["norms"] - norms).max() <= _tol(dtype)
+    ref = np.stack([orc.moments(lat, orc.random_state(lat.n, 3, r), rescale=rho, num_moments=num) for r in range(R)])
+    assert np.abs(mu - ref).max() <= _tol(dtype)
 
 
 @pytest.mark.parametrize("dtype", [0, 1])
