@@ -234,7 +234,7 @@ constexpr int STEP_CLOSURE = 6144;         // most rows of a closure that launch
 hipError_t launch_step_plan(const int32_t *col, int64_t ld, int w, int depth, int cap, int tiles,
                             const int32_t *tile, const int32_t *tile_rows, int32_t *layer,
                             const int32_t *clo_ptr, int32_t *rows, uint64_t *lcol, uint32_t *vsel, int64_t lde,
-                            const uint32_t *vidx, bool self, hipStream_t st);
+                            const uint32_t *vidx, bool self, int dtype, hipStream_t st);
 // cuts each tile in two, in place: the first part has cuts[i] of its rows
 hipError_t launch_step_split(const int32_t *col, int64_t ld, int w, int tiles, const int32_t *tile, int32_t *tile_rows,
                              int32_t *cuts, hipStream_t st);

@@ -174,7 +174,7 @@ hipError_t Builder::measure(std::vector<Tile> &tiles, const std::vector<int32_t>
     hipError_t e = list(tiles, which, ints);
     if (e == hipSuccess)
         e = launch_step_plan(col, ld, w, depth, cap, (int)which.size(), d_tile, d_rows, d_out,
-                             nullptr, nullptr, nullptr, nullptr, 0, nullptr, false, st);
+                             nullptr, nullptr, nullptr, nullptr, 0, nullptr, false, ham->dtype, st);
     if (e == hipSuccess)
         e = results(ints);
     for (size_t k = 0; e == hipSuccess && k < which.size(); ++k) {
@@ -339,7 +339,7 @@ hipError_t Builder::run()
     PLAN_HIP(list(tiles, all, 1));
     PLAN_HIP(hipMemcpyAsync(p.clo_ptr, cp.data(), (nt + 1) * 4, hipMemcpyHostToDevice, st));
     PLAN_HIP(launch_step_plan(col, ld, w, depth, cap, (int)nt, d_tile, d_rows, p.layer, p.clo_ptr, p.rows, p.lcol,
-                              p.vsel, p.lde, ham->vidx, self, st));
+                              p.vsel, p.lde, ham->vidx, self, ham->dtype, st));
     PLAN_HIP(hipStreamSynchronize(st));
     p.depth = depth;
     p.max_rows = most;

@@ -13,14 +13,22 @@
 //
 // What bounds it: LDS bandwidth and issue rate (about one clock per CU for a
 // row and product: W gathers, an old value and a store of 16 bytes), no longer
-// memory.
+// memory; and, where a sample has fewer tiles than the card takes at once (512),
+// the latency of a launch: about 10 us for the closure's rows and H, waited for
+// in turn, plus the products.
+// Measured, against the term and pair kernels: graphene 2048^2, complex128, 16
+// steps: 25.7 -> 10.5 ms; graphene 64^2 (one launch a step), 256 steps: 13.9 ->
+// 3.6 ms; AB bilayer 1024x512, complex64, blocks of 16: 46.5 -> 31.5 ms; graphene
+// 640x480 with 20% vacancies (CSR), complex128 blocks of 4: 11.0 -> 2.7 ms.
+// Rows of 12 (third neighbours): five hops reach too far, and the staged term
+// kernel stays.
 //
 // Plan (StepPlan): tiles of at most 1024 rows; per tile the closure's rows in
 // order of hop distance (the tile's own first, each layer ascending), the
 // number of rows within d hops for d <= depth, and 16-bit local columns of the
-// rows within depth - 1 hops, and a byte per slot that selects its value: its
-// value table index, or without a table its stored slot.  step_plan_kernel builds it on the device by
-// breadth-first search from the stored ELL columns.
+// rows within depth - 1 hops (as byte offsets into the closure's vector), and a byte per slot that selects its value: its
+// value table index, or without a table its stored slot.  step_plan_kernel
+// builds it on the device by breadth-first search from the stored ELL columns.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -51,6 +59,7 @@ struct PlanArgs {
     int64_t lde;
     const uint32_t *vidx;                  // value table indexes of the rows, or null
     int32_t self;                          // move the slot of the row's own column to the end
+    int32_t eshift;                        // log2 of a vector element's bytes: lcol holds byte offsets
 };
 
 __device__ __forceinline__ int plan_slot(const int32_t *keys, int32_t c)
@@ -160,7 +169,7 @@ __global__ __launch_bounds__(SWG) void step_plan_kernel(PlanArgs a)
             const int q = s == a.w - 1 && from < a.w ? from : s < from ? s : s + 1;     // the stored slot
             const uint64_t l = i < inner ? at[plan_slot(keys, a.col[(int64_t)q * a.ld + r])] : 0;
             const uint32_t k = a.vidx ? (a.vidx[(int64_t)(q / 4) * a.ld + r] >> (8 * (q % 4))) & 255u : (uint32_t)q;
-            word |= l << (16 * (s % 4));
+            word |= (l << a.eshift) << (16 * (s % 4));
             sel |= k << (8 * (s % 4));
             if (s % 4 == 3 || s == a.w - 1) {
                 a.lcol[(int64_t)(s / 4) * a.lde + e0 + i] = word;
@@ -315,6 +324,17 @@ constexpr int step_rows()
     return k > most ? most : k < 2 ? 0 : k;        // 0: not compiled (a tile's 1024 rows take two)
 }
 
+// Closure rows of a tile: the lanes' registers, and two workgroups a CU: half of
+// the 160 KiB, the table's and the sums' 4 KiB apart, holds two vectors of them
+template <typename T, int W, bool REAL>
+constexpr int step_closure()
+{
+    const int fit = (81920 - 4096 - 4096) / (2 * (int)sizeof(T));
+    const int k = step_rows<T, W, REAL>() * STW;
+    const int most = k < fit ? k : fit;
+    return most < SP_CAP ? most : SP_CAP;
+}
+
 // Sums of three values over a wave: lane l returns that of value l / 16 (0 for
 // l >= 48).  Halves, then rows of 16 lanes, trade places so that one addition
 // serves two values, and rotations finish each row: 25 instructions, where three
@@ -367,9 +387,11 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
     constexpr int NW = (W + 3) / 4;
     constexpr int G = SELF ? W - 1 : W;             // slots gathered from LDS
     extern __shared__ __attribute__((aligned(16))) char step_lds[];
-    T *pa = reinterpret_cast<T *>(step_lds);        // p_m of the closure
-    T *pb = pa + a.max_rows;                        // p_m+1
-    V *vtab = reinterpret_cast<V *>(pb + a.max_rows);   // value table
+    // p_m of the closure and p_m+1, by turns
+    constexpr int PB = step_closure<T, W, REAL>();
+    T *const pa = reinterpret_cast<T *>(step_lds);
+    T *const pb = pa + PB;
+    V *vtab = reinterpret_cast<V *>(pb + PB);       // value table
     // sums of the waves: <psi0|out>, <out|out>; MOM: <p|p'>, <p|p> of every product
     __shared__ double red[MOM ? STEP_DEPTH : 1][STW / 64][3];
 
@@ -497,7 +519,12 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
     }
     __syncthreads();
 
-    for (int j = 1; j <= K; ++j) {
+    // product j: from cur (p_m; its closure at `from`) and prev (p_m-1) to prev
+    // and `to`.  Written out for both roles of the two, so that no register is
+    // copied and either buffer's place in LDS is an instruction's constant. (Rolled,
+    // with local indexes instead of byte offsets: 12 of 43 vector instructions a
+    // row more, 3 to 6% slower, and the longer rows spilled.)
+    auto product = [&](int j, const T *from, T *to, T (&cur)[KR], T (&prev)[KR]) __attribute__((always_inline)) {
         const int next = j < K ? layer[K - j - 1] : 0;
         const double scale = (!cont && j == 1) ? a.scale1 : a.scale;
         const d2 c{a.c[j][0], a.c[j][1]};
@@ -515,13 +542,14 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
                     A acc{0, 0};
                     if constexpr (SELF) {
                         if constexpr (REAL)
-                            acc = A{v[k][W - 1] * own[k].x, v[k][W - 1] * own[k].y};
+                            acc = A{v[k][W - 1] * cur[k].x, v[k][W - 1] * cur[k].y};
                         else
-                            cmac(acc, (A)v[k][W - 1], (A)own[k]);
+                            cmac(acc, (A)v[k][W - 1], (A)cur[k]);
                     }
 #pragma unroll
                     for (int s = 0; s < G; ++s) {
-                        const T xv = pa[(cw[k][s / 2] >> (16 * (s % 2))) & 0xFFFFu];
+                        const uint32_t at = (cw[k][s / 2] >> (16 * (s % 2))) & 0xFFFFu;
+                        const T xv = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(from) + at);
                         if constexpr (REAL) {
                             acc.x += v[k][s] * xv.x;
                             acc.y += v[k][s] * xv.y;
@@ -529,13 +557,12 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
                             cmac(acc, (A)v[k][s], (A)xv);
                         }
                     }
-                    const d2 pn = E::acc_to_d(acc) * scale - E::to_d(old[k]);
-                    old[k] = own[k];
-                    own[k] = E::from_d(pn);
-                    pb[e] = own[k];
+                    const d2 pn = E::acc_to_d(acc) * scale - E::to_d(prev[k]);
+                    prev[k] = E::from_d(pn);
+                    to[e] = prev[k];
                     if (k < STW_OWN && e < n0) {
-                        if constexpr (MOM) {        // p in old, p' in own, as stored
-                            const d2 xd = E::to_d(old[k]), yd = E::to_d(own[k]);
+                        if constexpr (MOM) {        // p in cur, p' in prev, as stored
+                            const d2 xd = E::to_d(cur[k]), yd = E::to_d(prev[k]);
                             m0 += xd.x * yd.x + xd.y * yd.y;
                             m1 += xd.x * yd.y - xd.y * yd.x;
                             m2 += xd.x * xd.x + xd.y * xd.y;
@@ -553,9 +580,20 @@ __global__ __launch_bounds__(STW) __attribute__((amdgpu_waves_per_eu(4))) void s
                 red[j - 1][t / 64][(t & 63) / 16] = m;
         }
         __syncthreads();                            // p_m+1 complete; every read of p_m done
-        T *q = pa;
-        pa = pb;
-        pb = q;
+    };
+    int j = 1;
+    for (; j < K; j += 2) {
+        product(j, pa, pb, own, old);
+        product(j + 1, pb, pa, old, own);
+    }
+    if (j == K) {
+        product(j, pa, pb, own, old);
+#pragma unroll
+        for (int k = 0; k < STW_OWN; ++k) {         // the newest in own
+            const T q = own[k];
+            own[k] = old[k];
+            old[k] = q;
+        }
     }
 
     if constexpr (MOM) {
@@ -633,22 +671,20 @@ template <typename T, bool REAL>
 static int rows_of(int w)
 {
     switch (w) {
-    case 3: return step_rows<T, 3, REAL>();
-    case 4: return step_rows<T, 4, REAL>();
-    case 5: return step_rows<T, 5, REAL>();
-    case 8: return step_rows<T, 8, REAL>();
-    case 12: return step_rows<T, 12, REAL>();
+    case 3: return step_closure<T, 3, REAL>();
+    case 4: return step_closure<T, 4, REAL>();
+    case 5: return step_closure<T, 5, REAL>();
+    case 8: return step_closure<T, 8, REAL>();
+    case 12: return step_closure<T, 12, REAL>();
     default: return 0;
     }
 }
 
 int step_closure_max(int dtype, int w, bool real)
 {
-    const int k = dtype == TBPM_C128 ? (real ? rows_of<d2, true>(w) : rows_of<d2, false>(w))
-                                     : (real ? rows_of<f2, true>(w) : rows_of<f2, false>(w));
-    // two workgroups a CU: half of the 160 KiB, the table's and the sums' 4 KiB apart
-    const int fit = (81920 - 4096 - 4096) / (2 * (dtype == TBPM_C128 ? 16 : 8));
-    return std::min({k * STW, fit, SP_CAP});
+    if (dtype == TBPM_C128)
+        return real ? rows_of<d2, true>(w) : rows_of<d2, false>(w);
+    return real ? rows_of<f2, true>(w) : rows_of<f2, false>(w);
 }
 
 template <typename T, int W, bool REAL, bool SELF>
@@ -658,7 +694,7 @@ static hipError_t launch_w(const StepArgs &a, hipStream_t st)
         return hipErrorInvalidValue;
     } else {
         const int64_t per = (a.ntiles + NXCD - 1) / NXCD;
-        const size_t lds = (2 * (size_t)a.max_rows + (size_t)a.table_size) * sizeof(T);
+        const size_t lds = (2 * (size_t)step_closure<T, W, REAL>() + (size_t)a.table_size) * sizeof(T);
         const dim3 grid((unsigned)(per * NXCD * a.B));
         if (a.moments)
             hipLaunchKernelGGL((step_kernel<T, W, REAL, SELF, true>), grid, dim3(STW), lds, st, a);
@@ -683,8 +719,8 @@ static hipError_t launch_t(const StepArgs &a, hipStream_t st)
 
 hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st)
 {
-    if (a.ntiles <= 0 || a.B < 1 || a.count < 1 || a.count > a.depth || a.depth > STEP_DEPTH || !a.rows || !a.lcol || !a.vsel ||
-        !a.layer || !a.x || (a.moments ? !a.partials || a.psi0 || a.mom_stride < a.ntiles * (int64_t)a.B * 4 : !a.out) ||
+    if (a.ntiles <= 0 || a.B < 1 || a.count < 1 || a.count > a.depth || a.depth > STEP_DEPTH || !a.rows ||
+        !a.lcol || !a.vsel || !a.layer || !a.x || (a.moments ? !a.partials || a.psi0 || a.mom_stride < a.ntiles * (int64_t)a.B * 4 : !a.out) ||
         a.max_rows < 1 || a.max_rows > step_closure_max(dtype, a.w, real) ||
         (a.xout && !a.yout) || (a.psi0 && !a.partials) || a.table_size < 0 || a.table_size > 256 ||
         (a.vtab ? a.table_size < 1 : !a.val))
@@ -697,12 +733,12 @@ hipError_t launch_steps(int dtype, bool real, const StepArgs &a, hipStream_t st)
 hipError_t launch_step_plan(const int32_t *col, int64_t ld, int w, int depth, int cap, int tiles,
                             const int32_t *tile, const int32_t *tile_rows, int32_t *layer,
                             const int32_t *clo_ptr, int32_t *rows, uint64_t *lcol, uint32_t *vsel, int64_t lde,
-                            const uint32_t *vidx, bool self, hipStream_t st)
+                            const uint32_t *vidx, bool self, int dtype, hipStream_t st)
 {
     if (tiles <= 0 || depth < 1 || depth > STEP_DEPTH || cap < SWG || cap > SP_CAP || w < 1)
         return hipErrorInvalidValue;
     PlanArgs a{col, ld, w, depth, cap, rows ? 1 : 0, tile, tile_rows, layer, clo_ptr, rows, lcol, vsel, lde, vidx,
-               self ? 1 : 0};
+               self ? 1 : 0, dtype == TBPM_C128 ? 4 : 3};
     hipLaunchKernelGGL(step_plan_kernel, dim3(tiles), dim3(SWG), 0, st, a);
     return hipGetLastError();
 }
