@@ -85,7 +85,10 @@ enum { TBPM_C128 = 0, TBPM_C64 = 1 };
  * original orbital order for every format.  TBPM_FMT_AUTO picks PATCH for
  * matrices of at least 65536 rows whose rows fit ELL (<= 15% padding) with a
  * row length of 3, 4, 5, 8 or 12 and small enough patch halos; else ELL when
- * padding is <= 15%; else CSR.  PATCH falls back the same way. */
+ * padding is <= 15%; else CSR.  PATCH falls back the same way.  The formats
+ * other than a CSR asked for by name also get a plan of tiles, where one pays,
+ * so that one launch forms several products with H (rows of at most 12 entries);
+ * a CSR that AUTO picked then holds a padded copy of its values besides. */
 enum { TBPM_FMT_CSR = 0, TBPM_FMT_ELL = 1, TBPM_FMT_AUTO = 2, TBPM_FMT_PATCH = 3 };
 /* tbpm_build_csr flags: check Hermiticity; use 2048-row instead of 1024-row
  * patches for TBPM_FMT_PATCH when rows hold at most 5 entries; store every
@@ -147,7 +150,9 @@ const char *tbpm_status_string(tbpm_status s);
  * synchronous propagation calls brackets its first Chebyshev term, its run
  * of middle terms and its last term with HIP events on the context's stream
  * and adds the elapsed times to per-kind totals (kind 0: first term,
- * 1: middle terms, 2: last term with the correlation sums).  Enabling resets
+ * 1: middle terms, 2: last term with the correlation sums).  The calls then
+ * run one or two terms to a launch, also where they would otherwise run
+ * several products (results differ by rounding alone).  Enabling resets
  * the totals.  *launches receives the number of kernel launches timed. */
 tbpm_status tbpm_ctx_set_profiling(tbpm_ctx *ctx, int32_t enable);
 /* HIP graphs for the time steps of tbpm_propagate_dos / _states / _sites:
@@ -215,7 +220,8 @@ tbpm_status tbpm_value_table_plan(const tbpm_csr *csr, int32_t dtype, int32_t *e
  * two to a pass over H: *fused = 1 for one vector on TBPM_FMT_PATCH, and for
  * complex64 blocks of 8 or 16 vectors on TBPM_FMT_PATCH with at most 8
  * entries in a row whose patches have halos of at most 1280 rows; else 0
- * (one term per pass).  Series of fewer
+ * (one term per pass).  Where a call runs several products to a launch
+ * (see TBPM_FMT_*) it takes neither.  Series of fewer
  * than 4 terms, and Clenshaw's recurrence on blocks, take single terms
  * whatever this says.  TBPM_ERR_ARG for a null ham or fused, or block < 1. */
 tbpm_status tbpm_ham_fused_pairs(const tbpm_ham *ham, int32_t block, int32_t *fused);
@@ -337,7 +343,7 @@ tbpm_status tbpm_dos(const double *corr, int32_t num_time_steps, double rescale,
  *   corr      host complex [R][N_t+1] (required), norms host [R][N_t+1]
  *             (optional), corr_mean host complex [N_t+1] (optional): as in
  *             tbpm_propagate_dos; LDOS sites are rejected (TBPM_ERR_ARG).
- * TBPM_ERR_TOO_LARGE when the buffers (about 4, with fused term pairs 6,
+ * TBPM_ERR_TOO_LARGE when the buffers (4, with fused term pairs up to 7,
  * vectors of n x block complex entries, plus (N_t+1) x block x 24 bytes)
  * exceed the scratch area.  Calls share the device's scratch area and keep
  * its last contents: calls that overlap on one device (two threads, or two

@@ -223,6 +223,8 @@ int Job::vectors() const
     return cross ? 7 : pairs ? 6 : 4;               // psi0 + three (five, six) rotating vectors
 }
 
+double Job::step_us(int B) const { return steps ? steps_us(ham, M, B) : terms_us(ham, M, B); }
+
 size_t Job::sums() const { return (size_t)max_grid * (size_t)bmax * 4 * (steps ? GRAPH_STEPS : 1); }
 
 bool Job::without_steps()
@@ -666,15 +668,19 @@ double terms_us(const tbpm_ham *ham, int M, int B)
     return products * std::max(6.5, n * (h + 11.0 / 3.0 * e * B) / 4.8e6);
 }
 
-bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, int>> &blocks)
+double steps_us(const tbpm_ham *ham, int M, int B)
 {
     const tbpm_ham::StepPlan &p = ham->steps;
-    if (p.ntiles == 0 || M < 2)
+    return (double)((M - 1 + p.depth - 1) / p.depth) * std::max(1.0, (double)p.ntiles * B / STEP_SLOTS) * p.tile_us;
+}
+
+bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, int>> &blocks)
+{
+    if (ham->steps.ntiles == 0 || M < 2)
         return false;
     double tiles = 0.0, terms = 0.0;
     for (auto &blk : blocks) {
-        tiles += (double)((M - 1 + p.depth - 1) / p.depth) *
-                 std::max(1.0, (double)p.ntiles * blk.second / STEP_SLOTS) * p.tile_us;
+        tiles += steps_us(ham, M, blk.second);
         terms += terms_us(ham, M, blk.second);
     }
     return tiles < terms;
@@ -750,7 +756,8 @@ static tbpm_status apply_series_steps(const tbpm_ham *ham, hipStream_t st, int B
 // O = sum_{m<M} c_m T_m(H/rho) P (see tbpm_engine.h).
 tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape &shape, bool pairs, bool clenshaw,
                          const double *c, int M, double rescale, const SeriesBufs &bf, bool dots, const void *psi0,
-                         double *partials, int *nblk, SeriesProfile *prof, std::string &err, bool skip_first, bool steps)
+                         double *partials, int *nblk, SeriesProfile *prof, std::string &err, bool skip_first,
+                         bool steps)
 {
 #define SER_HIP(expr)                                                                        \
     do {                                                                                     \
@@ -1390,7 +1397,8 @@ tbpm_status Job::advance(int max_steps)
             // captured from the current roles, or capture one while there is room
             const bool roles = !first_done && (graph_B != shape.B || (int)graphs.size() < MAX_GRAPHS ||
                                                find_graph() >= 0);
-            if (graph_mode && roles && pending == 0 && p.num_time_steps - k >= GRAPH_STEPS && max_steps - done >= GRAPH_STEPS) {
+            if (graph_mode && roles && pending == 0 && p.num_time_steps - k >= GRAPH_STEPS &&
+                max_steps - done >= GRAPH_STEPS) {
                 tbpm_status s = graph_steps();
                 if (s != TBPM_OK)
                     return s;

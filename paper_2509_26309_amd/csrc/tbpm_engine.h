@@ -141,6 +141,7 @@ struct Job {
     tbpm_status setup(tbpm_ctx *c, const tbpm_ham *h, const tbpm_params *prm, hipStream_t stream);
     // turns `steps` off where its vectors do not fit; false if it was off
     bool without_steps();
+    double step_us(int B) const;     // modelled device time of a time step of B vectors
     int vectors() const;             // of n x bmax elements, psi0 among them
     size_t sums() const;             // doubles of the partial sums: one step's, or (steps) a group of steps'
     // device bytes allocate() will take
@@ -206,6 +207,7 @@ tbpm_status apply_series(const tbpm_ham *ham, hipStream_t st, const KernelShape 
 StepArgs step_args(const tbpm_ham *ham, int B, double rescale);
 // whether a series of M terms on blocks of these (first vector, width) takes less
 // time by several products per launch on `ham` (steps above)
+double steps_us(const tbpm_ham *ham, int M, int B);    // modelled time of a step by tiles (terms_us: by terms)
 bool steps_apply(const tbpm_ham *ham, int M, const std::vector<std::pair<int, int>> &blocks);
 // A time step of one vector on patch-reordered H whose successor follows it
 // (forward recurrence, M even >= 6): a pair of terms 1 and 2 from P (p_1 to

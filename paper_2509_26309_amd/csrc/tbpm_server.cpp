@@ -10,6 +10,7 @@
 // while the others keep running.  Each request's kernels, launch shapes and
 // reduction order are those of a lone tbpm_propagate_dos call, so its result
 // does not depend on what else is running.
+#include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <condition_variable>
@@ -74,17 +75,16 @@ struct tbpm_server {
     void feed(Request *r);
 };
 
-// work per chunk: about 64 MB of algorithmic traffic (or at least one step),
-// so that every running request gets device time each round
-static int chunk_steps_for(const tbpm_ham *ham, const Job &job)
+// Steps per chunk: about 300 us of modelled device time (or at least one step),
+// so that every running request gets device time each round, and the two chunks
+// that a request has queued outlast a round of the scheduler (its 50 us sleep
+// takes about 110, and each request fed some 10 to 30).  With chunks of about
+// 15 us (64 MB of traffic) the device waited for the scheduler: six requests of
+// 9,000 to 102,000 orbitals took 39 ms.  Whole graphs where steps are replayed.
+static int chunk_steps_for(const Job &job)
 {
-    const double per_step = (double)(job.M - 1) * ((double)ham->bytes + 5.0 * (double)ham->n * job.elem * job.bmax);
-    int s = (int)(64e6 / (per_step > 1 ? per_step : 1));
-    if (s < 1)
-        s = 1;
-    if (s > 256)
-        s = 256;
-    return s;
+    const int s = (int)std::min(256.0, std::max(1.0, 300.0 / job.step_us(job.bmax)));
+    return job.graph_mode ? (s + Job::GRAPH_STEPS - 1) / Job::GRAPH_STEPS * Job::GRAPH_STEPS : s;
 }
 
 bool tbpm_server::admit_locked(std::vector<Request *> &admitted)
@@ -163,7 +163,7 @@ void tbpm_server::start_request(Request *r)
         finish_request(r, s, job.error.empty() ? "request start failed" : job.error);
         return;
     }
-    r->chunk_steps = chunk_steps_for(r->ham, job);
+    r->chunk_steps = chunk_steps_for(job);
 }
 
 // enqueue one chunk when fewer than two are outstanding; complete the request
