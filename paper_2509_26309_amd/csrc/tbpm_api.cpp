@@ -32,11 +32,16 @@ void *tbpm_ctx::dev_alloc(size_t bytes)
 {
     if (bytes == 0)
         bytes = 256;
-    if (has_alloc)
-        return alloc.alloc(bytes, alloc.user);
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess)
-        return nullptr;
+    if (has_alloc)
+        p = alloc.alloc(bytes, alloc.user);
+    else if (hipMalloc(&p, bytes) != hipSuccess)
+        p = nullptr;
+    // The caller sees the null pointer and may go on with less; the runtime keeps
+    // the refused allocation's error until it is read, and the next launch's
+    // check would report it as that launch's.
+    if (!p)
+        (void)hipGetLastError();
     return p;
 }
 

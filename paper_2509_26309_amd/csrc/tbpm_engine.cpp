@@ -336,6 +336,7 @@ tbpm_status Job::allocate()
     if (hipHostMalloc((void **)&corr_all, nt1 * R * 2 * sizeof(double), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&norms_all, nt1 * R * sizeof(double), hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&div_host, 256, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();                    // read here, not by a later call's launch check
         release();
         return fail(TBPM_ERR_OOM, "pinned host allocation failed");
     }
