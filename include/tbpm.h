@@ -225,6 +225,14 @@ tbpm_status tbpm_value_table_plan(const tbpm_csr *csr, int32_t dtype, int32_t *e
  * than 4 terms, and Clenshaw's recurrence on blocks, take single terms
  * whatever this says.  TBPM_ERR_ARG for a null ham or fused, or block < 1. */
 tbpm_status tbpm_ham_fused_pairs(const tbpm_ham *ham, int32_t block, int32_t *fused);
+/* Whether one launch forms several products with H: *products = the most that
+ * a launch forms where a propagation runs blocks of `block` vectors of `ham`
+ * that way (default truncation, forward recurrence, kernel timing off, device
+ * memory for its vectors), 0 where it takes one or two terms a launch.
+ * *tiles and *tile_rows: the tiles of the plan and the rows of its largest (0
+ * without a plan).  Any output may be NULL; TBPM_ERR_ARG for a null ham or a
+ * block outside 1..64. */
+tbpm_status tbpm_ham_tiles(const tbpm_ham *ham, int32_t block, int32_t *products, int64_t *tiles, int32_t *tile_rows);
 tbpm_status tbpm_ham_destroy(tbpm_ham *ham);
 
 /* Autotuner: times one middle Chebyshev term of `ham` on scratch vectors for

@@ -576,6 +576,21 @@ tbpm_status tbpm_ham_fused_pairs(const tbpm_ham *ham, int32_t block, int32_t *fu
     return TBPM_OK;
 }
 
+tbpm_status tbpm_ham_tiles(const tbpm_ham *ham, int32_t block, int32_t *products, int64_t *tiles, int32_t *tile_rows)
+{
+    if (!ham || block < 1 || block > 64)
+        return TBPM_ERR_ARG;
+    double c[2 * 64];
+    const int M = chebyshev_coefficients(3.141592653589793238462643383279, 1e-14, 64, c);
+    if (products)
+        *products = steps_apply(ham, M, {{0, block}}) ? std::min(ham->steps.depth, M - 1) : 0;
+    if (tiles)
+        *tiles = ham->steps.ntiles;
+    if (tile_rows)
+        *tile_rows = ham->steps.tile_rows;
+    return TBPM_OK;
+}
+
 tbpm_status tbpm_ham_destroy(tbpm_ham *ham)
 {
     if (!ham)

@@ -403,7 +403,7 @@ struct tbpm_ham {
     // tiles of several products per launch (empty: ntiles 0), device arrays
     struct StepPlan {
         int64_t ntiles = 0;
-        int32_t depth = 0, max_rows = 0;
+        int32_t depth = 0, max_rows = 0, tile_rows = 0;    // hops; rows of the largest closure, of the largest tile
         double tile_us = 0.0;           // modelled time of a tile and launch (two workgroups a CU)
         bool real = false, self = false;   // all values real; every row has a slot in its own column
         int64_t lde = 0;                // closure entries of all tiles

@@ -314,9 +314,10 @@ hipError_t Builder::run()
     std::vector<int32_t> cp(nt + 1, 0);
     int64_t total = 0;
     double products = 0.0;
-    int32_t most = 0;
+    int32_t most = 0, own = 0;
     for (size_t i = 0; i < nt; ++i) {
         most = std::max(most, tiles[i].size);
+        own = std::max(own, tiles[i].count);
         products += tiles[i].products;
         total += tiles[i].size;
         if (total > INT32_MAX)
@@ -343,6 +344,7 @@ hipError_t Builder::run()
     PLAN_HIP(hipStreamSynchronize(st));
     p.depth = depth;
     p.max_rows = most;
+    p.tile_rows = own;
     p.tile_us = tile_time(ham->dtype, w, (double)total / (double)nt, products / (double)nt);
     p.real = real;
     p.self = self;

@@ -74,6 +74,7 @@ _SIGS = {
     "tbpm_patch_plan": ([ctypes.POINTER(tbpm_csr), ctypes.c_int32, P, P, P, P], ctypes.c_int32),
     "tbpm_ham_value_table": ([P, P, P], ctypes.c_int32),
     "tbpm_ham_fused_pairs": ([P, ctypes.c_int32, P], ctypes.c_int32),
+    "tbpm_ham_tiles": ([P, ctypes.c_int32, P, P, P], ctypes.c_int32),
     "tbpm_value_table_plan": ([ctypes.POINTER(tbpm_csr), ctypes.c_int32, P, P], ctypes.c_int32),
     "tbpm_coefficients": ([ctypes.c_double, ctypes.c_double, ctypes.c_int32, P, P], ctypes.c_int32),
     "tbpm_propagate_dos": ([P, P, ctypes.POINTER(tbpm_params), P, P, P, P], ctypes.c_int32),
@@ -272,6 +273,14 @@ def tbpm_ham_fused_pairs(ham, block: int) -> bool:
     f = ctypes.c_int32()
     _check(load().tbpm_ham_fused_pairs(ham, int(block), ctypes.byref(f)), what="tbpm_ham_fused_pairs")
     return bool(f.value)
+
+
+def tbpm_ham_tiles(ham, block: int = 1) -> dict:
+    """Several products with H per launch for blocks of `block` vectors (products 0: one or two terms a launch)."""
+    k, n, r = ctypes.c_int32(), ctypes.c_int64(), ctypes.c_int32()
+    _check(load().tbpm_ham_tiles(ham, block, ctypes.byref(k), ctypes.byref(n), ctypes.byref(r)),
+           what="tbpm_ham_tiles")
+    return {"products": k.value, "tiles": n.value, "tile_rows": r.value}
 
 
 def tbpm_value_table_plan(n: int, row_ptr: np.ndarray, col: np.ndarray, val: np.ndarray,
