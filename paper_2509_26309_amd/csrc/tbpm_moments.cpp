@@ -191,22 +191,30 @@ struct MomentRun {
                 steps_us() < products_us();
         if (steps)
             max_grid = std::max<int64_t>(max_grid, ham->steps.ntiles);
-        // partials of up to 64 launches, at most about 32 MiB of them
+        // Partials of up to 64 products, at most about 32 MiB of them, but never
+        // fewer than one launch forms: launches of fewer products pay the prologue
+        // (H and the closures' vectors) more often.  That is 32 bytes a tile, vector
+        // and product, where the tile's vectors take 32 KiB each and more.
         const size_t per = (size_t)max_grid * bmax * 4 * sizeof(double);
-        chunk = (int)std::max<size_t>(pairs ? 2 : 1, std::min<size_t>(64, ((size_t)32 << 20) / per));
+        const size_t least = steps ? (size_t)ham->steps.depth : pairs ? 2 : 1;
+        chunk = (int)std::max<size_t>(least, std::min<size_t>(64, ((size_t)32 << 20) / per));
         chunk = std::min(chunk, kmax);
         return TBPM_OK;
     }
 
-    // modelled time (us) of a product on every block: by tiles (the sums of each
-    // product add about a fifth), and by the product kernels (launches of 2.9 us,
-    // half of 6.5 on patches, at least; else their bytes at 4.3 TB/s, CSR 4.1)
+    // modelled time (us) of the kmax products on every block: by tiles (the sums
+    // of each product add about a fifth; half of a whole launch's time is its
+    // prologue, which a launch of fewer products pays as well), and by the
+    // product kernels (launches of 2.9 us, half of 6.5 on patches, at least; else
+    // their bytes at 4.3 TB/s, CSR 4.1)
     double steps_us() const
     {
+        const int depth = ham->steps.depth;
+        const double launches = 0.5 * ((kmax + depth - 1) / depth + (double)kmax / depth);
         double us = 0.0;
         for (auto &blk : blocks)
-            us += 1.2 * std::max(1.0, (double)ham->steps.ntiles * blk.second / STEP_SLOTS) * ham->steps.tile_us /
-                  ham->steps.depth;
+            us += 1.2 * launches * std::max(1.0, (double)ham->steps.ntiles * blk.second / STEP_SLOTS) *
+                  ham->steps.tile_us;
         return us;
     }
     double products_us() const
@@ -217,14 +225,17 @@ struct MomentRun {
         double us = 0.0;
         for (auto &blk : blocks) {
             const int B = blk.second;
-            if (pairs && B == 1)
-                us += std::max(6.5, n * (hp + 4.0 * e) / 4.3e6) / 2;
-            else if (choose_shape(ham, B, ctx->num_cu, p.lanes_per_row).staged)
-                us += std::max(3.3, n * (hp + 3.0 * e * B) / 4.3e6);
+            double one;                             // a single product
+            if (choose_shape(ham, B, ctx->num_cu, p.lanes_per_row).staged)
+                one = std::max(3.3, n * (hp + 3.0 * e * B) / 4.3e6);
             else if (ham->format == TBPM_FMT_CSR)
-                us += std::max(2.9, ((double)ham->nnz * (e + 4.0) + n * (4.0 + 3.0 * e * B)) / 4.1e6);
+                one = std::max(2.9, ((double)ham->nnz * (e + 4.0) + n * (4.0 + 3.0 * e * B)) / 4.1e6);
             else
-                us += std::max(2.9, n * (ham->ell_w * (e + 4.0) + 3.0 * e * B) / 4.3e6);
+                one = std::max(2.9, n * (ham->ell_w * (e + 4.0) + 3.0 * e * B) / 4.3e6);
+            if (pairs && B == 1)                    // product 0 alone, then pairs
+                us += one + (kmax - 1) * std::max(6.5, n * (hp + 4.0 * e) / 4.3e6) / 2;
+            else
+                us += one * kmax;
         }
         return us;
     }
