@@ -449,11 +449,14 @@ tbpm_status tbpm_dyn_polarization(const double *corr, int32_t num_time_steps, do
 /* A request server on `ctx`'s device: admits submitted propagations while
  * their footprints fit in hbm_budget bytes and fewer than max_slots run,
  * keeps admitted vectors resident, and advances all running requests
- * together (continuous batching).  Results do not depend on what else runs. */
+ * together (continuous batching).  Results do not depend on what else runs,
+ * nor on kernel timing (unless device memory runs out that the budget counted
+ * on: the term kernels' results differ by rounding). */
 tbpm_status tbpm_server_create(tbpm_ctx *ctx, size_t hbm_budget, int32_t max_slots, tbpm_server **out);
 /* Queues a tbpm_propagate_dos request; never blocks on the GPU.  The server
  * copies *params (and its ldos_sites).  TBPM_ERR_TOO_LARGE if the request can
- * never fit the budget. */
+ * never fit the budget (the request's status, if it no longer can with the
+ * series' mode at its start). */
 tbpm_status tbpm_submit(tbpm_server *srv, const tbpm_ham *ham, const tbpm_params *params, uint64_t *ticket);
 /* TBPM_PENDING while queued or running; once done returns the request's
  * status and, when it is TBPM_OK, copies into the optional host outputs

@@ -625,6 +625,7 @@ tbpm_status tbpm_footprint(const tbpm_ham *ham, const tbpm_params *params, size_
     if (!ham || !params || !bytes)
         return TBPM_ERR_ARG;
     Job job;
+    job.profile = ham->ctx->profiling;
     tbpm_status s = job.setup(ham->ctx, ham, params, nullptr);
     if (s != TBPM_OK)
         return s;
@@ -668,8 +669,8 @@ static tbpm_status run_sync(tbpm_ctx *ctx, const tbpm_ham *ham, const tbpm_param
         job.qe_energies.assign(outs->energies, outs->energies + outs->num_energies);
         job.qe_host = outs->qe;
     }
-    tbpm_status s = job.setup(ctx, ham, params, ctx->stream);
     job.profile = ctx->profiling;
+    tbpm_status s = job.setup(ctx, ham, params, ctx->stream);
     if (s == TBPM_OK)
         s = job.allocate();
     if (s == TBPM_OK && job.p.norm_tol > 0.0) {

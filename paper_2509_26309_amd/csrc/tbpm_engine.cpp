@@ -205,7 +205,7 @@ tbpm_status Job::setup(tbpm_ctx *c, const tbpm_ham *h, const tbpm_params *prm, h
     // several products per launch, where H has a plan for it (kernel timing is
     // by term, so it keeps the term kernels)
     cross_ok = pairs && any_single && !clenshaw && M >= 6 && M % 2 == 0;
-    steps = !clenshaw && !ctx->profiling && steps_apply(ham, M, blocks);
+    steps = !clenshaw && !profile && steps_apply(ham, M, blocks);
     term_grid = max_grid;
     if (steps)
         max_grid = std::max<int64_t>(max_grid, ham->steps.ntiles);
@@ -309,7 +309,7 @@ tbpm_status Job::allocate()
     }
     if (!ok) {
         release();
-        if (!arena && without_steps())              // the term kernels may take fewer vectors
+        if (!arena && without_steps() && footprint() <= limit)      // the term kernels may take fewer vectors
             return allocate();
         return fail(arena ? TBPM_ERR_TOO_LARGE : TBPM_ERR_OOM,
                     arena ? "the propagation buffers exceed the scratch area"

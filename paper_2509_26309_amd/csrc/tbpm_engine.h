@@ -126,8 +126,10 @@ struct Job {
     int find_graph() const;          // index of the graph for the current roles, or -1
     void drop_graphs();
 
-    // kernel timing: when set, each step records 4 events from ctx->events
+    // kernel timing: when set (before setup), each step records 4 events from
+    // ctx->events; timing is by term, so the term kernels run
     bool profile = false;
+    size_t limit = SIZE_MAX;         // bytes that allocate() may take instead where the tiles' vectors do not fit
     size_t ev_used = 0;
     std::vector<size_t> step_ev;     // first of 4 pool events per eagerly launched step
     std::vector<size_t> graph_ev;    // first of 2 pool events around each graph launch

@@ -91,6 +91,7 @@ extern "C" tbpm_status tbpm_propagate_dos_noalloc(tbpm_ctx *ctx, const tbpm_ham 
     job.arena_bytes = NOALLOC_SCRATCH_BYTES;
     job.direct_corr = corr;
     job.direct_norms = norms;
+    job.profile = ctx->profiling;
     tbpm_status s = job.setup(ctx, ham, params, ctx->stream);
     if (s == TBPM_OK && job.arena_need() > NOALLOC_SCRATCH_BYTES)
         (void)job.without_steps();                  // the term kernels may take fewer vectors

@@ -8,8 +8,13 @@
 // different requests run concurrently on the device; a request that finishes
 // frees its slot and memory at once, and the next queued request is admitted
 // while the others keep running.  Each request's kernels, launch shapes and
-// reduction order are those of a lone tbpm_propagate_dos call, so its result
-// does not depend on what else is running.
+// reduction order are those of a lone tbpm_propagate_dos call with kernel timing
+// off, so its result does not depend on what else is running; where the tiles'
+// vectors would not fit the server's budget, or the device's memory (held by
+// others than this server), they are those of the term kernels, which differ by
+// rounding.  The reservation of a running request always covers what it holds:
+// what changed between submission and start (the series' mode) is settled
+// before its buffers are allocated.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -35,7 +40,7 @@ struct Request {
     tbpm_params params{};
     std::vector<int64_t> sites;
     std::unique_ptr<Job> job;
-    size_t footprint = 0;
+    size_t footprint = 0;      // reserved of the budget while admitted
     hipStream_t stream = nullptr;
     hipEvent_t chunk_ev[2] = {nullptr, nullptr};
     int chunks_out = 0;        // chunks recorded and not yet seen complete (0..2)
@@ -71,6 +76,8 @@ struct tbpm_server {
     void run();
     bool admit_locked(std::vector<Request *> &admitted);
     void start_request(Request *r);
+    bool reserve(Request *r, Job &job, tbpm_status *s);
+    static void drop(Request *r);
     void finish_request(Request *r, tbpm_status s, const std::string &err);
     void feed(Request *r);
 };
@@ -113,7 +120,8 @@ bool tbpm_server::admit_locked(std::vector<Request *> &admitted)
     return any;
 }
 
-void tbpm_server::finish_request(Request *r, tbpm_status s, const std::string &err)
+// what a started request holds on the device
+void tbpm_server::drop(Request *r)
 {
     if (r->job)
         r->job->release();
@@ -127,6 +135,40 @@ void tbpm_server::finish_request(Request *r, tbpm_status s, const std::string &e
         (void)hipStreamDestroy(r->stream);
         r->stream = nullptr;
     }
+}
+
+// Makes the admitted request's reservation that of its job as set up now.  Where
+// the running requests hold the difference, it goes back to the head of the queue
+// (false); *s: TBPM_ERR_TOO_LARGE where it can never fit.
+bool tbpm_server::reserve(Request *r, Job &job, tbpm_status *s)
+{
+    std::lock_guard<std::mutex> lk(mu);
+    if (job.footprint() > budget)
+        job.without_steps();
+    const size_t need = job.footprint();
+    if (need > budget) {
+        *s = job.fail_with(TBPM_ERR_TOO_LARGE,
+                           "the request does not fit the server's budget with the series' mode at its start");
+        return true;
+    }
+    const bool fits = used - r->footprint + need <= budget;
+    used -= r->footprint;
+    r->footprint = need;
+    if (fits) {
+        used += need;
+        job.limit = need;
+        return true;
+    }
+    r->admitted = false;
+    r->t_admit = -1;
+    active.erase(std::find(active.begin(), active.end(), r));
+    queue.push_front(r);
+    return false;
+}
+
+void tbpm_server::finish_request(Request *r, tbpm_status s, const std::string &err)
+{
+    drop(r);
     std::lock_guard<std::mutex> lk(mu);
     used -= r->footprint;
     r->status = s;
@@ -154,11 +196,12 @@ void tbpm_server::start_request(Request *r)
         s = TBPM_ERR_HIP;
     if (s == TBPM_OK)
         s = job.setup(ctx, r->ham, &prm, r->stream);
-    if (s == TBPM_OK) {
-        if (job.footprint() > r->footprint)          // never more than was admitted
-            job.without_steps();
-        s = job.allocate();
+    if (s == TBPM_OK && !reserve(r, job, &s)) {
+        drop(r);
+        return;
     }
+    if (s == TBPM_OK)
+        s = job.allocate();
     if (s != TBPM_OK) {
         finish_request(r, s, job.error.empty() ? "request start failed" : job.error);
         return;
