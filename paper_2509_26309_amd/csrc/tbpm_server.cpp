@@ -87,11 +87,16 @@ struct tbpm_server {
 // that a request has queued outlast a round of the scheduler (its 50 us sleep
 // takes about 110, and each request fed some 10 to 30).  With chunks of about
 // 15 us (64 MB of traffic) the device waited for the scheduler: six requests of
-// 9,000 to 102,000 orbitals took 39 ms.  Whole graphs where steps are replayed.
+// 9,000 to 102,000 orbitals took 39 ms.  Whole graphs where steps are replayed
+// and one takes at most twice that time (with at most that time six requests took
+// 26.6 ms instead of 25.7): of slower steps the launches cost little, and a whole
+// graph of them, queued twice, would hold up cancellation and other requests.
 static int chunk_steps_for(const Job &job)
 {
     const int s = (int)std::min(256.0, std::max(1.0, 300.0 / job.step_us(job.bmax)));
-    return job.graph_mode ? (s + Job::GRAPH_STEPS - 1) / Job::GRAPH_STEPS * Job::GRAPH_STEPS : s;
+    if (!job.graph_mode || 2 * s < Job::GRAPH_STEPS)
+        return s;
+    return (s + Job::GRAPH_STEPS - 1) / Job::GRAPH_STEPS * Job::GRAPH_STEPS;
 }
 
 bool tbpm_server::admit_locked(std::vector<Request *> &admitted)

@@ -94,3 +94,23 @@ def test_never_more_than_the_budget(T, ctx):
         _queued_behind_another(T, ctx, budget, 3, lambda: T.tbpm_ctx_set_series(ctx.handle, T.TBPM_SERIES_CLENSHAW))
     assert seen[1] > seen[0]
     assert e.value.status == T.TBPM_ERR_TOO_LARGE and "poll" in str(e.value)       # accepted, refused at its start
+
+
+@pytest.mark.parametrize("cells,R,replays", [(12, 1, True), (512, 8, False)])
+def test_chunks_are_whole_graphs_only_where_one_fits(T, ctx, cells, R, replays):
+    """A chunk is about 300 us of device time, or one step: steps of a few microseconds
+    are replayed in whole graphs, slow ones (eight vectors of 524,288 orbitals: more than
+    150 us) are launched one by one, also where graphs are asked for at any size."""
+    lat = graphene(cells, disorder_w=1.0, seed=3)
+    ham = ctx.build(lat)
+    p, _ = T.make_params(9.0, 24, R, block=R, seed=2)
+    T.tbpm_ctx_set_graphs(ctx.handle, 2)
+    before = T.tbpm_ctx_graph_replays(ctx.handle)
+    srv = T.tbpm_server_create(ctx.handle, 8 << 30, 1)
+    try:
+        st, corr, _, _ = _wait(T, srv, T.tbpm_submit(srv, ham, p), R, 24)
+    finally:
+        T.tbpm_server_destroy(srv)
+    assert st == T.TBPM_OK
+    assert (T.tbpm_ctx_graph_replays(ctx.handle) > before) == replays
+    assert np.array_equal(corr, T.tbpm_propagate_dos(ctx.handle, ham, p)["corr"])
