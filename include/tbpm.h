@@ -235,15 +235,16 @@ tbpm_status tbpm_ham_fused_pairs(const tbpm_ham *ham, int32_t block, int32_t *fu
 tbpm_status tbpm_ham_tiles(const tbpm_ham *ham, int32_t block, int32_t *products, int64_t *tiles, int32_t *tile_rows);
 tbpm_status tbpm_ham_destroy(tbpm_ham *ham);
 
-/* Autotuner: times one middle Chebyshev term of `ham` on scratch vectors for
- * every candidate shape -- lanes per row 1, 2, 4, 8, 16 (CSR, one vector) and
- * block widths 1, 2, 4, ... up to max_block (a power of two <= 64) -- and
- * picks the fastest per vector.  The chosen lanes per row is stored in `ham`
+/* Autotuner: times a few time steps of `ham`, as a propagation takes them with
+ * the context's series, for every candidate shape -- lanes per row 1, 2, 4, 8,
+ * 16 (CSR, one vector, terms one by one) and block widths 1, 2, 4, ... up to
+ * max_block (a power of two <= 64; those that fit the device) -- and picks the
+ * fastest per vector (of block widths within 3% the narrower).  The chosen lanes per row is stored in `ham`
  * and used whenever params->lanes_per_row is 0; the chosen block width is
  * stored likewise and used whenever params->block is 0 (capped by the
  * number of vectors).  Outputs (each may be NULL): best_lanes, best_block,
  * and us_per_vector_term, the measured microseconds per vector and term.
- * Allocates scratch vectors for max_block vectors for the duration. */
+ * Allocates what a propagation of max_block vectors does for the duration. */
 tbpm_status tbpm_autotune(tbpm_ctx *ctx, tbpm_ham *ham, int32_t max_block, int32_t *best_lanes, int32_t *best_block,
                           double *us_per_vector_term);
 

@@ -783,113 +783,85 @@ tbpm_status tbpm_quasi_eigenstates(tbpm_ctx *ctx, const tbpm_ham *ham, const tbp
 
 // ---- autotuner ------------------------------------------------------------------------
 
+// Time of a term (product with H) and vector, microseconds, in the time steps that
+// a call takes with this block width and these lanes per row: a propagation's own
+// steps on its own buffers, after a few untimed ones (the same number of steps in a
+// graph where the call would replay them).  terms: without tiles.
+static tbpm_status time_steps(tbpm_ctx *ctx, const tbpm_ham *ham, int block, int lanes, bool terms, hipEvent_t e0,
+                              hipEvent_t e1, double *us)
+{
+    const bool small = ham->n * (int64_t)block <= (int64_t)1 << 21;
+    const int warm = small ? Job::GRAPH_STEPS : 1, timed = 2 * warm;
+    tbpm_params p{};
+    p.rescale = ham->gersh > 0.0 ? ham->gersh : 1.0;
+    p.num_time_steps = warm + timed + 1;            // the block stays open: its rows are not copied
+    p.num_vectors = block;
+    p.block = block;
+    p.lanes_per_row = lanes;
+    Job job;
+    tbpm_status s = job.setup(ctx, ham, &p, ctx->stream);
+    if (terms)
+        job.without_steps();
+    if (s == TBPM_OK)
+        s = job.allocate();
+    if (s == TBPM_OK && (s = job.advance(warm)) == TBPM_PENDING)
+        s = hipEventRecord(e0, ctx->stream) == hipSuccess ? TBPM_OK : TBPM_ERR_HIP;
+    if (s == TBPM_OK && (s = job.advance(timed)) == TBPM_PENDING)
+        s = hipEventRecord(e1, ctx->stream) == hipSuccess ? TBPM_OK : TBPM_ERR_HIP;
+    if (hipStreamSynchronize(ctx->stream) != hipSuccess && s == TBPM_OK)
+        s = TBPM_ERR_HIP;
+    float ms = 0.0f;
+    if (s == TBPM_OK && hipEventElapsedTime(&ms, e0, e1) != hipSuccess)
+        s = TBPM_ERR_HIP;
+    if (s != TBPM_OK)
+        return set_err(ctx, s, "autotune: " + (job.error.empty() ? std::string("timing failed") : job.error));
+    *us = ms * 1e3 / ((double)timed * (job.M - 1) * block);
+    return TBPM_OK;
+}
+
 extern "C" tbpm_status tbpm_autotune(tbpm_ctx *ctx, tbpm_ham *ham, int32_t max_block, int32_t *best_lanes,
                                      int32_t *best_block, double *us_per_vector_term)
 {
     if (!ctx || !ham || ham->ctx != ctx || max_block < 1 || max_block > 64)
         return set_err(ctx, TBPM_ERR_ARG, "autotune: bad arguments");
     CTX_HIP(ctx, hipSetDevice(ctx->device));
-    int bmax = 1;
-    while (bmax * 2 <= max_block)
-        bmax *= 2;
-    const size_t elem = ham->dtype == TBPM_C128 ? 16 : 8;
-    const size_t vbytes = (size_t)ham->n * bmax * elem;
-    void *x = ctx->dev_alloc(vbytes), *y = ctx->dev_alloc(vbytes), *o = ctx->dev_alloc(vbytes);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
     auto release = [&]() {
-        ctx->dev_free(x);
-        ctx->dev_free(y);
-        ctx->dev_free(o);
-        if (e0) (void)hipEventDestroy(e0);
-        if (e1) (void)hipEventDestroy(e1);
+        for (hipEvent_t e : ev)
+            if (e)
+                (void)hipEventDestroy(e);
     };
-    if (!x || !y || !o) {
-        release();
-        return set_err(ctx, TBPM_ERR_OOM, "autotune: scratch allocation failed");
-    }
-    hipStream_t st = ctx->stream;
-    if (hipMemsetAsync(x, 0, vbytes, st) != hipSuccess || hipMemsetAsync(y, 0, vbytes, st) != hipSuccess ||
-        hipMemsetAsync(o, 0, vbytes, st) != hipSuccess || hipEventCreate(&e0) != hipSuccess ||
-        hipEventCreate(&e1) != hipSuccess) {
+    if (hipEventCreate(&ev[0]) != hipSuccess || hipEventCreate(&ev[1]) != hipSuccess) {
         release();
         return set_err(ctx, TBPM_ERR_HIP, "autotune: setup failed");
     }
-    TermArgs a{};
-    a.n = ham->n;
-    if (ham->format == TBPM_FMT_CSR) {
-        a.rp = ham->rp;
-        a.rp64 = ham->rp64;
-    } else {
-        a.ld = ham->ell_ld;
-        a.w = ham->ell_w;
-    }
-    a.col = ham->col;
-    a.val = ham->val;
-    a.vidx = ham->vidx;
-    a.vtab = ham->vtab;
-    a.vdiag = ham->vdiag;
-    a.vdiag_real = ham->vdiag_real;
-    a.x = x;
-    a.y = y;
-    a.out = o;
-    a.scale = 0.0;      // scratch vectors stay zero
-    const int fmt = ham->format == TBPM_FMT_CSR ? F_CSR : F_ELL;
-    // time one shape: mean of 3 launches after one warm-up, microseconds
-    auto time_shape = [&](KernelShape s, double *us) -> tbpm_status {
-        CTX_HIP(ctx, launch_term(K_MID, ham->dtype, fmt, a, s, st));
-        CTX_HIP(ctx, hipEventRecord(e0, st));
-        for (int r = 0; r < 3; ++r)
-            CTX_HIP(ctx, launch_term(K_MID, ham->dtype, fmt, a, s, st));
-        CTX_HIP(ctx, hipEventRecord(e1, st));
-        CTX_HIP(ctx, hipEventSynchronize(e1));
-        float ms = 0.0f;
-        CTX_HIP(ctx, hipEventElapsedTime(&ms, e0, e1));
-        *us = ms * 1e3 / 3.0;
-        return TBPM_OK;
-    };
-    int lanes = ham->lpr;
-    double best1 = 1e300;
-    if (ham->format == TBPM_FMT_CSR) {
-        for (int l = 1; l <= 16; l *= 2) {
-            KernelShape s{1, l, 0};
-            s.grid = term_grid(ham->n, s, ctx->num_cu);
-            double us;
-            tbpm_status r = time_shape(s, &us);
-            if (r != TBPM_OK) {
-                release();
-                return r;
-            }
-            if (us < best1) {
-                best1 = us;
+    int lanes = ham->lpr, block = 1;
+    double best = 0.0, us = 0.0;
+    tbpm_status s = TBPM_OK;
+    if (ham->format == TBPM_FMT_CSR) {              // lanes matter where single vectors take the term kernels
+        double least = 1e300;
+        for (int l = 1; s == TBPM_OK && l <= 16; l *= 2)
+            if ((s = time_steps(ctx, ham, 1, l, true, ev[0], ev[1], &us)) == TBPM_OK && us < least) {
+                least = us;
                 lanes = l;
             }
-        }
-    } else {
-        KernelShape s{1, 1, 0};
-        s.grid = term_grid(ham->n, s, ctx->num_cu);
-        tbpm_status r = time_shape(s, &best1);
-        if (r != TBPM_OK) {
-            release();
-            return r;
-        }
     }
-    int block = 1;
-    double best = best1;   // per vector
-    for (int b = 2; b <= bmax; b *= 2) {
-        KernelShape s{b, block_lanes(b, ham->dtype), 0};
-        s.grid = term_grid(ham->n, s, ctx->num_cu);
-        double us;
-        tbpm_status r = time_shape(s, &us);
-        if (r != TBPM_OK) {
-            release();
-            return r;
-        }
-        if (us / b < best) {
-            best = us / b;
+    if (s == TBPM_OK)
+        s = time_steps(ctx, ham, 1, lanes, false, ev[0], ev[1], &best);
+    for (int b = 2; s == TBPM_OK && b <= max_block; b *= 2) {
+        const tbpm_status w = time_steps(ctx, ham, b, lanes, false, ev[0], ev[1], &us);
+        if (w == TBPM_ERR_OOM)                      // wider blocks do not fit, nor would a call's
+            break;
+        s = w;
+        // two timings of one shape differ by 1 to 2%, and a wider block holds more memory
+        if (s == TBPM_OK && us < 0.97 * best) {
+            best = us;
             block = b;
         }
     }
     release();
+    if (s != TBPM_OK)
+        return s;
     ham->lpr = lanes;
     ham->tuned_block = block;
     if (best_lanes) *best_lanes = lanes;
