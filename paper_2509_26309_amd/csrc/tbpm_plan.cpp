@@ -8,6 +8,7 @@
 // per row happens on the device; the host sees a few numbers per tile.
 #include <algorithm>
 #include <cmath>
+#include <new>
 #include <vector>
 
 #include "tbpm_internal.h"
@@ -392,7 +393,8 @@ hipError_t step_slots(tbpm_ham *ham, const int64_t *rp, const int32_t *col, cons
 }
 
 // Builds ham->steps on stream st, left empty where no plan fits or pays, or
-// where memory does not suffice for it (the term kernels need none).
+// where memory of the device or the host does not suffice for it (the term
+// kernels need none).
 hipError_t build_steps(tbpm_ham *ham, hipStream_t st)
 {
     tbpm_ham::StepPlan &p = ham->steps;
@@ -406,9 +408,11 @@ hipError_t build_steps(tbpm_ham *ham, hipStream_t st)
     if (ham->patch_rows > 1024 || step_closure_max(ham->dtype, p.w, true) == 0)
         return hipSuccess;
     hipError_t e;
-    {
+    try {
         Builder b(ham, st);
         e = b.run();
+    } catch (const std::bad_alloc &) {              // host memory: no plan either
+        e = hipErrorOutOfMemory;
     }
     if (p.ntiles == 0) {
         free_steps(ham);
