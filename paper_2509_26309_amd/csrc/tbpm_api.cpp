@@ -536,7 +536,7 @@ tbpm_status tbpm_build_csr(tbpm_ctx *ctx, const tbpm_csr *csr, int32_t dtype, in
         e = hipStreamSynchronize(st);
     cleanup();
     if (e == hipSuccess)
-        e = tbpm::build_steps(ham, st);
+        e = tbpm::build_steps(ham, csr->on_device ? nullptr : csr, st);
     if (e != hipSuccess) {
         tbpm_ham_destroy(ham);
         return set_err(ctx, TBPM_ERR_HIP, std::string("H conversion: ") + hipGetErrorString(e));

@@ -300,7 +300,7 @@ struct QeFactors {
 hipError_t launch_qe_accumulate(int dtype, const void *psi, int64_t n, double *qe, int count, const QeFactors &f,
                                 hipStream_t st);
 // plan of several products per launch of a stored H (tbpm_plan.cpp)
-hipError_t build_steps(tbpm_ham *ham, hipStream_t st);
+hipError_t build_steps(tbpm_ham *ham, const tbpm_csr *host_csr, hipStream_t st);
 // CSR: the padded copy for ham->steps, of the checked device CSR (none where a
 // row is too long or memory does not suffice)
 hipError_t step_slots(tbpm_ham *ham, const int64_t *rp, const int32_t *col, const double *val, hipStream_t st);

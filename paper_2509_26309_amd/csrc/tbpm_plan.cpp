@@ -2,13 +2,17 @@
 // form a tile, to how many hops, and the closure of each tile.
 //
 // Tiles are compact regions of the sparsity graph of at most 1024 rows: the
-// patches of a patch-reordered H, or (plain ELL) regions grown by breadth-first
-// search here.  A tile whose closure is too large for the kernel (patches of
+// patches of a patch-reordered H, or (plain ELL, CSR) regions grown by
+// breadth-first search here.  A tile whose closure is too large for the kernel (patches of
 // several pieces, above all) is cut in two until its parts fit.  Everything
 // per row happens on the device; the host sees a few numbers per tile.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <initializer_list>
+#include <memory>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "tbpm_internal.h"
@@ -21,70 +25,139 @@ struct Tile {
     int32_t begin, count;               // rows: a range of the row list
     int32_t size;                       // rows of its closure, 0: not known or too many
     double products;                    // rows formed in all products of a launch
+    bool shared;                        // by small pieces
 };
 
-// breadth-first regions of at most `most` rows, one connected piece each, over
-// the stored ELL columns c [w][ld]; rows ascending within a tile.  Pieces of
-// fewer than `small` rows (what growing left over, clusters that vacancies cut
-// off) share tiles, in the order found, so that no workgroup is spent on a few rows.
-void grow_tiles(const std::vector<int32_t> &c, int64_t ld, int w, int64_t n, int most, int small,
-                std::vector<int32_t> &rows, std::vector<Tile> &tiles)
+// neighbours of a row: of the caller's CSR, or (rp null) of ELL columns c [w][ld]
+struct Rows {
+    const int64_t *rp;
+    const int32_t *c;
+    int64_t ld;
+    int w;
+    template <typename F>
+    void each(int32_t r, F f) const
+    {
+        if (rp)
+            for (int64_t k = rp[r]; k < rp[r + 1]; ++k)
+                f(c[k]);
+        else
+            for (int s = 0; s < w; ++s)
+                f(c[(size_t)s * (size_t)ld + (size_t)r]);
+    }
+};
+
+// f(0) .. f(count - 1) on threads of their own, on this one where none can be had;
+// throws std::bad_alloc when one of them ran out of memory
+template <typename F>
+void in_parallel(int count, F f)
+{
+    std::atomic<bool> failed{false};
+    auto one = [&](int i) {
+        try {
+            f(i);
+        } catch (...) {
+            failed = true;
+        }
+    };
+    std::vector<std::thread> threads;
+    int i = 0;
+    try {
+        threads.reserve((size_t)count);
+        for (; i + 1 < count; ++i)
+            threads.emplace_back(one, i);
+    } catch (...) {
+    }
+    for (; i < count; ++i)
+        one(i);
+    for (std::thread &t : threads)
+        t.join();
+    if (failed)
+        throw std::bad_alloc();
+}
+
+// breadth-first pieces of at most `most` rows among the rows lo .. hi - 1, one
+// connected piece each: piece[row] and the pieces' numbers of rows
+void grow_pieces(const Rows &g, int32_t lo, int32_t hi, int most, int32_t *piece, std::vector<int32_t> &count)
 {
     constexpr int32_t NONE = -1;
-    std::vector<int32_t> piece((size_t)n, NONE), count;     // of a row; rows of a piece
+    std::fill(piece + lo, piece + hi, NONE);
     std::vector<int32_t> queue((size_t)most);
-    int64_t low = 0, taken = 0;
+    int32_t low = lo, taken = lo;
     int32_t seed = NONE;                // an untaken neighbour of the previous piece
-    while (taken < n) {
-        if (seed == NONE || piece[(size_t)seed] != NONE) {
-            while (piece[(size_t)low] != NONE)
+    while (taken < hi) {
+        if (seed == NONE || piece[seed] != NONE) {
+            while (piece[low] != NONE)
                 ++low;
-            seed = (int32_t)low;
+            seed = low;
         }
         const int32_t id = (int32_t)count.size();
         int end = 1;
         queue[0] = seed;
-        piece[(size_t)seed] = id;
+        piece[seed] = id;
         seed = NONE;
         for (int i = 0; i < end; ++i)
-            for (int s = 0; s < w; ++s) {
-                const int32_t u = c[(size_t)(s * ld + queue[(size_t)i])];
-                if (piece[(size_t)u] != NONE)
-                    continue;
+            g.each(queue[(size_t)i], [&](int32_t u) {
+                if (u < lo || u >= hi || piece[u] != NONE)
+                    return;
                 if (end == most) {
                     if (seed == NONE)
                         seed = u;
-                    continue;
+                    return;
                 }
-                piece[(size_t)u] = id;
+                piece[u] = id;
                 queue[(size_t)end++] = u;
-            }
+            });
         count.push_back(end);
         taken += end;
     }
-    // a tile for each piece, small pieces together
-    std::vector<int32_t> tile_of(count.size());
-    int shared = -1;
-    for (size_t q = 0; q < count.size(); ++q) {
-        if (count[q] < small && shared >= 0 && tiles[(size_t)shared].count + count[q] <= most) {
-            tiles[(size_t)shared].count += count[q];
-            tile_of[q] = shared;
-            continue;
+}
+
+// Tiles of at most `most` rows, one connected piece each, grown in up to eight
+// ranges of the rows at once (491,000 rows: 1.6 ms instead of 7.3; the ranges
+// depend on n alone).  Pieces of fewer than `small` rows (what growing left over,
+// clusters that vacancies cut off) share tiles, in the order found, so that no
+// workgroup is spent on a few rows.  rows: tile after tile, ascending in each piece.
+void grow_tiles(const Rows &g, int64_t n, int most, int small, int32_t *rows, std::vector<Tile> &tiles)
+{
+    const int parts = (int)std::min<int64_t>(8, std::max<int64_t>(1, n / 32768));
+    auto from = [&](int i) { return (int32_t)(n * i / parts); };
+    std::unique_ptr<int32_t[]> piece(new int32_t[(size_t)n]);
+    std::vector<std::vector<int32_t>> count((size_t)parts);
+    in_parallel(parts, [&](int i) { grow_pieces(g, from(i), from(i + 1), most, piece.get(), count[(size_t)i]); });
+    std::vector<std::vector<int32_t>> tile_of(count);
+    int32_t shared = -1;
+    for (int i = 0; i < parts; ++i)
+        for (size_t q = 0; q < count[(size_t)i].size(); ++q) {
+            const int32_t c = count[(size_t)i][q];
+            const bool joins = c < small && shared >= 0 && tiles[(size_t)shared].count + c <= most;
+            if (!joins) {
+                tiles.push_back({0, 0, 0, 0.0, c < small});
+                if (c < small)
+                    shared = (int32_t)tiles.size() - 1;
+            }
+            const int32_t t = joins ? shared : (int32_t)tiles.size() - 1;
+            tile_of[(size_t)i][q] = t;
+            tiles[(size_t)t].count += c;
         }
-        tile_of[q] = (int32_t)tiles.size();
-        if (count[q] < small)
-            shared = tile_of[q];
-        tiles.push_back({0, count[q], 0, 0.0});
-    }
     std::vector<int32_t> at(tiles.size());
     int32_t begin = 0;
     for (size_t i = 0; i < tiles.size(); ++i) {
         tiles[i].begin = at[i] = begin;
         begin += tiles[i].count;
     }
-    rows.resize((size_t)n);
-    for (int64_t r = 0; r < n; ++r)
-        rows[(size_t)at[(size_t)tile_of[(size_t)piece[(size_t)r]]]++] = (int32_t)r;
+    // where each piece begins, then its rows
+    for (int i = 0; i < parts; ++i)
+        for (size_t q = 0; q < count[(size_t)i].size(); ++q) {
+            int32_t &t = tile_of[(size_t)i][q];
+            const int32_t b = at[(size_t)t];
+            at[(size_t)t] += count[(size_t)i][q];
+            t = b;
+        }
+    in_parallel(parts, [&](int i) {
+        std::vector<int32_t> &next = tile_of[(size_t)i];
+        for (int32_t r = from(i); r < from(i + 1); ++r)
+            rows[next[(size_t)piece[(size_t)r]]++] = r;
+    });
 }
 
 // Time of one tile and launch with two workgroups a CU, in microseconds: the
@@ -106,8 +179,8 @@ double step_time(int depth, double tiles, double tile_us)
 
 class Builder {
   public:
-    Builder(tbpm_ham *h, hipStream_t s)
-        : ham(h), ctx(h->ctx), st(s), col(h->steps.ell_col ? h->steps.ell_col : h->col),
+    Builder(tbpm_ham *h, const tbpm_csr *host_csr, hipStream_t s)
+        : ham(h), ctx(h->ctx), csr(host_csr), st(s), col(h->steps.ell_col ? h->steps.ell_col : h->col),
           val(h->steps.ell_val ? h->steps.ell_val : h->val), ld(h->steps.ld), w(h->steps.w)
     {
     }
@@ -122,6 +195,7 @@ class Builder {
   private:
     tbpm_ham *ham;
     tbpm_ctx *ctx;
+    const tbpm_csr *csr;                // H as given, in host memory, or null
     hipStream_t st;
     const int32_t *col;                 // H's slots
     const void *val;
@@ -166,6 +240,7 @@ class Builder {
     }
     hipError_t measure(std::vector<Tile> &tiles, const std::vector<int32_t> &which, int depth, int cap);
     hipError_t split(std::vector<Tile> &tiles, const std::vector<int32_t> &which);
+    hipError_t fit(std::vector<Tile> &cut, int depth, int cap, double scale, double least, double *us);
 };
 
 // closure sizes of the listed tiles
@@ -189,24 +264,33 @@ hipError_t Builder::measure(std::vector<Tile> &tiles, const std::vector<int32_t>
     return e;
 }
 
-// every listed tile in two, in its place
+// every listed tile in two, in its place: breadth-first halves, or (shared: hundreds
+// of small pieces one after the other, of which the kernel walks each) list halves
 hipError_t Builder::split(std::vector<Tile> &tiles, const std::vector<int32_t> &which)
 {
-    hipError_t e = list(tiles, which, which.size());
-    if (e == hipSuccess)
-        e = launch_step_split(col, ld, w, (int)which.size(), d_tile, d_rows, d_out, st);
-    if (e == hipSuccess)
-        e = results(which.size());
+    std::vector<int32_t> walked;
+    for (int32_t i : which)
+        if (!tiles[(size_t)i].shared)
+            walked.push_back(i);
+    hipError_t e = hipSuccess;
+    if (!walked.empty()) {
+        e = list(tiles, walked, walked.size());
+        if (e == hipSuccess)
+            e = launch_step_split(col, ld, w, (int)walked.size(), d_tile, d_rows, d_out, st);
+        if (e == hipSuccess)
+            e = results(walked.size());
+    }
     if (e != hipSuccess)
         return e;
     std::vector<Tile> next;
     next.reserve(tiles.size() + which.size());
-    size_t k = 0;
+    size_t k = 0, walk = 0;
     for (size_t i = 0; i < tiles.size(); ++i) {
         const Tile t = tiles[i];
         if (k < which.size() && (size_t)which[k] == i) {
-            next.push_back({t.begin, out[k], 0, 0.0});
-            next.push_back({t.begin + out[k], t.count - out[k], 0, 0.0});
+            const int32_t at = t.shared ? (t.count + 1) / 2 : out[walk++];
+            next.push_back({t.begin, at, 0, 0.0, t.shared});
+            next.push_back({t.begin + at, t.count - at, 0, 0.0, t.shared});
             ++k;
         } else {
             next.push_back(t);
@@ -222,6 +306,40 @@ hipError_t Builder::split(std::vector<Tile> &tiles, const std::vector<int32_t> &
         if (e_ != hipSuccess)                                                                \
             return e_;                                                                       \
     } while (0)
+
+// Cuts the tiles whose closures are over the cap until all fit.  *us: the modelled
+// time of a step where the sample has `scale` times these tiles; it ends early, with
+// at least `least`, where that is no longer to be undercut.
+hipError_t Builder::fit(std::vector<Tile> &cut, int depth, int cap, double scale, double least, double *us)
+{
+    std::vector<int32_t> which, bad;
+    while (true) {
+        which.clear();
+        for (size_t i = 0; i < cut.size(); ++i)
+            if (cut[i].size == 0)
+                which.push_back((int32_t)i);
+        PLAN_HIP(measure(cut, which, depth, cap));
+        double rows = 0.0, products = 0.0;
+        bad.clear();
+        bool far = false;
+        for (int32_t i : which)
+            if (cut[(size_t)i].size == 0) {
+                bad.push_back(i);
+                far = far || cut[(size_t)i].count < 8;      // a handful of rows that reach too far
+            }
+        for (const Tile &t : cut) {
+            rows += t.size == 0 ? cap : t.size;
+            products += t.products;
+        }
+        const double now = (double)(cut.size() + bad.size());
+        *us = step_time(depth, now * scale, tile_time(ham->dtype, w, rows / now, products / now));
+        if (far)
+            *us = std::max(*us, least);
+        if (far || *us >= least || bad.empty())
+            return hipSuccess;
+        PLAN_HIP(split(cut, bad));
+    }
+}
 
 hipError_t Builder::run()
 {
@@ -245,16 +363,22 @@ hipError_t Builder::run()
     if (ham->patched) {
         for (int64_t q = 0; q < ham->npatch; ++q) {
             const int32_t b = ham->h_patch_ptr[(size_t)q];
-            first.push_back({b, ham->h_patch_ptr[(size_t)q + 1] - b, 0, 0.0});
+            first.push_back({b, ham->h_patch_ptr[(size_t)q + 1] - b, 0, 0.0, false});
         }
         PLAN_HIP(launch_iota(d_first, n, st));
     } else {
-        std::vector<int32_t> c((size_t)w * (size_t)ld), rows;
-        PLAN_HIP(hipMemcpyAsync(c.data(), col, c.size() * 4, hipMemcpyDeviceToHost, st));
-        PLAN_HIP(hipStreamSynchronize(st));
+        std::unique_ptr<int32_t[]> c, rows(new int32_t[(size_t)n]);
+        Rows g{csr ? csr->row_ptr : nullptr, csr ? csr->col : nullptr, ld, w};
+        if (!csr) {
+            const size_t slots = (size_t)w * (size_t)ld;
+            c.reset(new int32_t[slots]);
+            g.c = c.get();
+            PLAN_HIP(hipMemcpyAsync(c.get(), col, slots * 4, hipMemcpyDeviceToHost, st));
+            PLAN_HIP(hipStreamSynchronize(st));
+        }
         const int most = (int)std::min<int64_t>(1024, std::max<int64_t>(64, (n + 255) / 256));
-        grow_tiles(c, ld, w, n, most, ham->format == TBPM_FMT_CSR ? most / 8 : 0, rows, first);
-        PLAN_HIP(hipMemcpyAsync(d_first, rows.data(), (size_t)n * 4, hipMemcpyHostToDevice, st));
+        grow_tiles(g, n, most, ham->format == TBPM_FMT_CSR ? most / 8 : 0, rows.get(), first);
+        PLAN_HIP(hipMemcpyAsync(d_first, rows.get(), (size_t)n * 4, hipMemcpyHostToDevice, st));
         PLAN_HIP(hipStreamSynchronize(st));
     }
 
@@ -264,44 +388,52 @@ hipError_t Builder::run()
     std::vector<Tile> tiles;
     int depth = 0;
     double least = std::max(terms_us(ham, 20, 1), ham->dtype == TBPM_C64 ? terms_us(ham, 20, 8) / 8 : 0.0);
-    for (int d : {19, 10, 7, 5}) {
-        if (d == 19 && ham->patched)
-            continue;                   // a patch's rows within 19 hops do not fit
+    struct Try {
+        int depth;
+        double us;                      // as a sample of the tiles has it
+    };
+    std::vector<Try> order;
+    // Many tiles grown here: what each depth would cost is first found on up to 32 of
+    // them (not those that small pieces share: they are cut most, and few), from 10
+    // on, which wins most often, so that the others end as soon as they cost a tenth
+    // more.  The four take 0.5 to 5 ms so (521 tiles of 491,000 rows of 3; 766 of
+    // 784,000 rows of 12), on all tiles 7 and 40; of 280 tiles the search on all
+    // takes 2 to 3 and a sample no less.  (On patches, whose search is a few percent
+    // of storing H, all tiles decide: patches of several pieces make a sample miss.)
+    constexpr size_t SAMPLE = 32;
+    const bool sampled = !ham->patched && first.size() >= 16 * SAMPLE;
+    for (int d : sampled ? std::initializer_list<int>{10, 19, 7, 5} : std::initializer_list<int>{19, 10, 7, 5})
+        if (d != 19 || !ham->patched)   // a patch's rows within 19 hops do not fit
+            order.push_back({d, 0.0});
+    std::vector<Tile> some;
+    for (size_t i = 0; sampled && i < SAMPLE; ++i)
+        for (size_t k = (2 * i + 1) * first.size() / (2 * SAMPLE); k < (i + 1) * first.size() / SAMPLE; ++k)
+            if (!first[k].shared) {
+                some.push_back(first[k]);
+                break;
+            }
+    if (!some.empty()) {
+        const double scale = (double)first.size() / (double)some.size();
+        double bound = 1.1 * least;
+        for (Try &t : order) {
+            PLAN_HIP(hipMemcpyAsync(d_rows, d_first, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
+            std::vector<Tile> cut = some;
+            PLAN_HIP(fit(cut, t.depth, cap, scale, bound, &t.us));
+            bound = std::min(bound, 1.1 * t.us);
+        }
+        std::stable_sort(order.begin(), order.end(), [](const Try &a, const Try &b) { return a.us < b.us; });
+    }
+    for (const Try &t : order) {
+        if (t.us >= 1.1 * least)
+            continue;                   // (a sample misses by a few percent)
         std::swap(d_rows, d_spare);     // d_spare: the best tiles so far
         PLAN_HIP(hipMemcpyAsync(d_rows, d_first, (size_t)n * 4, hipMemcpyDeviceToDevice, st));
         std::vector<Tile> cut = first;
-        std::vector<int32_t> which;
         double us = least;
-        while (true) {
-            which.clear();
-            for (size_t i = 0; i < cut.size(); ++i)
-                if (cut[i].size == 0)
-                    which.push_back((int32_t)i);
-            PLAN_HIP(measure(cut, which, d, cap));
-            double rows = 0.0, products = 0.0;
-            std::vector<int32_t> bad;
-            bool far = false;
-            for (int32_t i : which)
-                if (cut[(size_t)i].size == 0) {
-                    bad.push_back(i);
-                    far = far || cut[(size_t)i].count < 8;  // a handful of rows that reach too far
-                }
-            for (const Tile &t : cut) {
-                rows += t.size == 0 ? cap : t.size;
-                products += t.products;
-            }
-            const double tiles_now = (double)(cut.size() + bad.size());
-            us = step_time(d, tiles_now, tile_time(ham->dtype, w, rows / tiles_now, products / tiles_now));
-            if (far || us >= least || bad.empty()) {
-                if (far)
-                    us = least;
-                break;
-            }
-            PLAN_HIP(split(cut, bad));
-        }
+        PLAN_HIP(fit(cut, t.depth, cap, 1.0, least, &us));
         if (us < least) {
             least = us;
-            depth = d;
+            depth = t.depth;
             tiles.swap(cut);
         } else {
             std::swap(d_rows, d_spare);
@@ -392,10 +524,11 @@ hipError_t step_slots(tbpm_ham *ham, const int64_t *rp, const int32_t *col, cons
     return launch_to_ell(ham->dtype, rp, col, val, ham->n, p.w, p.ld, p.ell_col, p.ell_val, st);
 }
 
-// Builds ham->steps on stream st, left empty where no plan fits or pays, or
+// Builds ham->steps on stream st (host_csr: H as given, where that is in host
+// memory), left empty where no plan fits or pays, or
 // where memory of the device or the host does not suffice for it (the term
 // kernels need none).
-hipError_t build_steps(tbpm_ham *ham, hipStream_t st)
+hipError_t build_steps(tbpm_ham *ham, const tbpm_csr *host_csr, hipStream_t st)
 {
     tbpm_ham::StepPlan &p = ham->steps;
     if (ham->format == TBPM_FMT_CSR) {
@@ -409,7 +542,7 @@ hipError_t build_steps(tbpm_ham *ham, hipStream_t st)
         return hipSuccess;
     hipError_t e;
     try {
-        Builder b(ham, st);
+        Builder b(ham, host_csr, st);
         e = b.run();
     } catch (const std::bad_alloc &) {              // host memory: no plan either
         e = hipErrorOutOfMemory;
