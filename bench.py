@@ -126,6 +126,27 @@ def deferred_series_bytes(info, n, B, dtype, terms_per_launch):
     return sv * n * B * (1.0 if terms_per_launch == 2 else 4.0 / 3.0)
 
 
+def tile_bytes_per_step(info, n, B, dtype, terms, products, real):
+    """Bytes that a time step by tiles (up to `products` products with H per launch)
+    cannot do without, and its launches: each launch reads the plan and values of its
+    rows (row number, columns and value selectors; with a value table the row's
+    diagonal, else w values) and its vectors once, for every vector of the block by
+    itself.  Vector passes: x read and psi0 read and out written where one launch does
+    the step; else x read, out and two vectors passed on written by the first, x, y and
+    out read and all three written by those between, x, y, out and psi0 read and out
+    written by the last.  What the tiles' closures read besides is not counted."""
+    sv = 16 if dtype == "c128" else 8
+    words = (info["ell_w"] + 3) // 4
+    row = 4 + 12 * words
+    if info.get("table_used"):
+        row += {0: 0, 1: sv, 2: sv // 2}[int(info.get("table_diag", 0))]
+    else:
+        row += info["ell_w"] * (sv // 2 if real else sv)
+    launches = -(-terms // products)
+    passes = 3 if launches == 1 else 4 + 6 * (launches - 2) + 5
+    return n * B * (launches * row + passes * sv), launches
+
+
 def traffic_source_hash() -> str:
     return hashlib.sha256(b"".join(open(f, "rb").read() for f in TRAFFIC_SOURCES)).hexdigest()
 
@@ -634,13 +655,15 @@ def main():
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
 
-    # the kernels of single terms (pairs), timed launch by launch in a short pass of their own
+    # the kernels of single terms (pairs), timed launch by launch in a short pass of
+    # their own, after one untimed (these kernels' first launches load them)
     whole = nt, num_moments, wft_steps
     nt, num_moments = min(nt, 24), min(num_moments, 256)
     wft_steps = [k for k in wft_steps if k <= nt]
     log("bench: kernel timing of the term kernels")
-    tbpm.tbpm_ctx_set_profiling(ctx.handle, True)
-    one_step(0, None)
+    for _ in range(2):
+        tbpm.tbpm_ctx_set_profiling(ctx.handle, True)       # (resets the totals)
+        one_step(0, None)
     tbpm.tbpm_ctx_set_profiling(ctx.handle, False)
     nt, num_moments, wft_steps = whole
 
@@ -695,6 +718,19 @@ def main():
     blocks_per_bench_step = max(1, R // B)
     step_rate = (step_bytes * nt * blocks_per_bench_step * args.steps / el / 1e9
                  if args.route == "propagate" else None)
+    # the timed steps, where they formed several products per launch on tiles
+    products = 0 if clenshaw else tbpm.tbpm_ham_tiles(ham, B)["products"]
+    tiled = None
+    if args.route == "propagate" and products:
+        tile_bytes, launches = tile_bytes_per_step(info, lat.n, B, w["dtype"], terms, products,
+                                                   not np.any(np.imag(lat.val)))
+        us = el / (args.steps * nt * blocks_per_bench_step) * 1e6
+        tiled = {"kernel": "several Chebyshev products per launch on tiles, closures recomputed on chip",
+                 "products_per_launch": products, "launches_per_time_step": launches,
+                 "bound": "HBM with the tiles' closures read besides, LDS and issue (counters: profiles/)",
+                 "algorithmic_bytes_per_time_step": tile_bytes, "us_per_time_step": us,
+                 "achieved": tile_bytes / us / 1e3, "unit": "GB/s", "frac": tile_bytes / us / 1e3 / HBM_PEAK_GBS,
+                 "timing": "host clock of the timed steps, everything of the call included"}
     norms_dev = max(float(np.abs(o["norms"] - 1).max()) for o in kept) if args.route == "propagate" else None
     if args.route == "wft":
         norms_dev = max(float(np.abs(o["snapshot_norms"] - 1).max()) for o in kept)
@@ -751,7 +787,9 @@ def main():
                                            "propagation_equivalent_value":
                                                lat.nnz * terms * nt * R * args.steps / el}
                                           if args.route in ("moments", "sites") else {})},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"of_timed_steps": not products or args.route == "sites",
+                     "timed_steps": tiled,
+                     "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": (achieved / HBM_PEAK_GBS) if achieved else None,
                      "traffic": traffic,
                      "kernel": ("moment pair (two fused SpMV + recurrence + <p|p>, <p|p'> partial sums per "
@@ -778,8 +816,9 @@ def main():
                      "forward_recurrence_bytes_per_step": step_bytes if args.route == "propagate" else None,
                      "forward_recurrence_step_equiv_GBps": step_rate,
                      "forward_recurrence_step_equiv_frac": (step_rate / HBM_PEAK_GBS) if step_rate else None,
-                     "timing": "HIP events around each launch in a separate pass of at most 24 time steps; the "
-                               "timed steps form several products per launch where that is faster",
+                     "timing": "HIP events around each launch in a separate pass of at most 24 time steps, by the "
+                               "kernels of one term or a pair; of_timed_steps says whether the timed steps launch "
+                               "them (timed_steps: the tiles' figures where not)",
                      "us_per_time_step": el / (args.steps * nt * blocks_per_bench_step) * 1e6
                      if args.route == "propagate" else None,
                      "avg_launch_us": mid_avg_s * 1e6, "launches_timed": mid_n,

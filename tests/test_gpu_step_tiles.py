@@ -140,3 +140,27 @@ def test_query_arguments(T, ctx):
                 T.tbpm_ham_tiles(ham, block)
     finally:
         T.tbpm_ham_destroy(ham)
+
+
+@pytest.mark.parametrize("kind", ["ell", "csr"])
+def test_h_given_in_device_memory(T, ctx, kind):
+    """The plan of an H given in device memory is that of the same H given in host memory."""
+    import torch
+    if kind == "ell":
+        lat, fmt = graphene(61, 47, disorder_w=1.0, seed=4), T.TBPM_FMT_ELL
+    else:
+        lat, fmt = supercell(cell_by_name("graphene"), 61, 47, vacancy_p=0.2, seed=3), T.TBPM_FMT_AUTO
+    dev = [torch.as_tensor(x, device="cuda") for x in (np.asarray(lat.row_ptr, dtype=np.int64),
+                                                       np.asarray(lat.col, dtype=np.int32),
+                                                       np.asarray(lat.val, dtype=np.complex128))]
+    torch.cuda.synchronize()
+    got = []
+    for ham in (ctx.build(lat, fmt=fmt),
+                T.tbpm_build_csr_device(ctx.handle, lat.n, lat.nnz, *(x.data_ptr() for x in dev), 0, fmt)):
+        try:
+            p, _ = T.make_params(9.0, 5, 2, block=2, seed=3)
+            got.append((T.tbpm_ham_tiles(ham, 2), T.tbpm_propagate_dos(ctx.handle, ham, p)["corr"]))
+        finally:
+            T.tbpm_ham_destroy(ham)
+    assert got[0][0] == got[1][0] and got[0][0]["products"] > 0
+    assert np.array_equal(got[0][1], got[1][1])
