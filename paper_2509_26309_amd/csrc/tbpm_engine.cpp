@@ -426,28 +426,23 @@ tbpm_status Job::open_block()
     if (given_states)
         JOB_HIP(hipMemcpyAsync(states_dev, given_states + (size_t)r0 * n * 2, (size_t)B * n * 16,
                                hipMemcpyHostToDevice, st));
-    // groups of BV interleaved vectors: the whole block, or (steps) single vectors
-    const int BV = group();
-    for (int b = 0; b < B; b += BV) {
-        if (!site_states.empty()) {
-            SiteRows sr{};
-            for (int q = 0; q < BV; ++q)
-                sr.r[q] = site_states[(size_t)r0 + b + q];
-            JOB_HIP(launch_init_sites(ham->dtype, vec(psi0, b), vec(P, b), n, BV, sr, st));
-        } else if (given_states) {
-            JOB_HIP(launch_pack_states(ham->dtype, states_dev + (size_t)b * n * 2, vec(psi0, b), vec(P, b), n, BV, perm,
-                                       st));
-        } else {
-            JOB_HIP(launch_init_random(ham->dtype, vec(psi0, b), vec(P, b), n, BV, p.seed,
-                                       (int64_t)p.first_vector + r0 + b, perm, st));
-        }
-        // C(t_0) = <psi0|psi0>
-        JOB_HIP(launch_dot_partials(ham->dtype, vec(psi0, b), vec(P, b), n, BV, partials, dot_grid, st));
-        JOB_HIP(launch_reduce(partials, dot_grid, BV, corr_dev + 2 * b, norms_dev + b, st, p.norm_tol, div_flag));
-        if (!sites.empty())
-            JOB_HIP(launch_ldos_gather(ham->dtype, vec(psi0, b), vec(P, b), n, BV, sites_dev, (int)sites.size(),
-                                       site_dev, p.num_time_steps + 1, 0, st));
+    const int apart = steps ? 1 : 0;
+    if (!site_states.empty()) {
+        SiteRows sr{};
+        for (int b = 0; b < B; ++b)
+            sr.r[b] = site_states[(size_t)r0 + b];
+        JOB_HIP(launch_init_sites(ham->dtype, psi0, P, n, B, sr, st, apart));
+    } else if (given_states) {
+        JOB_HIP(launch_pack_states(ham->dtype, states_dev, psi0, P, n, B, perm, st, apart));
+    } else {
+        JOB_HIP(launch_init_random(ham->dtype, psi0, P, n, B, p.seed, (int64_t)p.first_vector + r0, perm, st, apart));
     }
+    // C(t_0) = <psi0|psi0>
+    JOB_HIP(launch_dot_partials(ham->dtype, psi0, P, n, B, partials, dot_grid, st, apart));
+    JOB_HIP(launch_reduce(partials, dot_grid, B, corr_dev, norms_dev, st, p.norm_tol, div_flag));
+    if (!sites.empty())
+        JOB_HIP(launch_ldos_gather(ham->dtype, psi0, P, n, B, sites_dev, (int)sites.size(), site_dev,
+                                   p.num_time_steps + 1, 0, st, apart));
     if (graph_mode)
         JOB_HIP(launch_set_counter(kstep, 1, st));
     k = 0;
@@ -1304,9 +1299,8 @@ tbpm_status Job::step()
         JOB_HIP(launch_reduce(partials, nblk, B, corr_dev + (size_t)k * B * 2, norms_dev + (size_t)k * B, st,
                               p.norm_tol, div_flag));
     if (!sites.empty())
-        for (int b = 0; b < B; b += group())
-            JOB_HIP(launch_ldos_gather(ham->dtype, vec(psi0, b), vec(psi_next, b), n, group(), sites_dev,
-                                       (int)sites.size(), site_dev, p.num_time_steps + 1, k, st));
+        JOB_HIP(launch_ldos_gather(ham->dtype, psi0, psi_next, n, B, sites_dev, (int)sites.size(), site_dev,
+                                   p.num_time_steps + 1, k, st, steps ? 1 : 0));
     if (xs) {
         // psi(t_k) in Pn; the next step's p_1 and partial series in Qn, On
         P = Pn;

@@ -94,16 +94,18 @@ inline int block_lanes(int B, int dtype) { return dtype == TBPM_C64 ? B / 2 : B;
 
 // launchers (tbpm_kernels.hip); all return hipSuccess or the launch error
 hipError_t launch_term(int kind, int dtype, int fmt, const TermArgs &a, const KernelShape &s, hipStream_t st);
-// perm (nullable): original row index of each stored row
+// perm (nullable): original row index of each stored row; apart: the block's vectors
+// one after another, [B][n], instead of interleaved, [n][B] (here and below)
 hipError_t launch_init_random(int dtype, void *psi0, void *p, int64_t n, int B, uint64_t seed, int64_t r0,
-                              const int32_t *perm, hipStream_t st);
+                              const int32_t *perm, hipStream_t st, int apart = 0);
 hipError_t launch_pack_states(int dtype, const double *src, void *psi0, void *p, int64_t n, int B,
-                              const int32_t *perm, hipStream_t st);
+                              const int32_t *perm, hipStream_t st, int apart = 0);
 // site-localised states: vector b of the block is 1 at stored row rows[b], 0 elsewhere
 struct SiteRows {
     int64_t r[64];
 };
-hipError_t launch_init_sites(int dtype, void *psi0, void *p, int64_t n, int B, const SiteRows &rows, hipStream_t st);
+hipError_t launch_init_sites(int dtype, void *psi0, void *p, int64_t n, int B, const SiteRows &rows, hipStream_t st,
+                             int apart = 0);
 hipError_t launch_unpack_state(int dtype, const void *src, double *dst, int64_t n, int B, int b,
                                const int32_t *perm, hipStream_t st);
 
@@ -259,7 +261,7 @@ hipError_t launch_to_ell_perm(int dtype, const int64_t *rp, const int32_t *col, 
                               int32_t w, int64_t ld, const int32_t *old_of_new, const int32_t *new_of_old,
                               int32_t *col_out, void *val_out, hipStream_t st);
 hipError_t launch_dot_partials(int dtype, const void *psi0, const void *v, int64_t n, int B, double *partials,
-                               int grid, hipStream_t st);
+                               int grid, hipStream_t st, int apart = 0);
 // tol > 0 and flag: *flag (device) is set to 1 when some |norm - 1| > tol
 hipError_t launch_reduce(const double *partials, int nblocks, int B, double *corr, double *norms,
                          hipStream_t st, double tol = 0.0, int32_t *flag = nullptr);
@@ -281,7 +283,7 @@ hipError_t launch_moment_reduce(const double *partials, int nblocks, int B, int6
 hipError_t launch_moment_finish(const double *raw, int kmax, int B, int num, double *mu, hipStream_t st);
 hipError_t launch_ldos_gather(int dtype, const void *psi0, const void *v, int64_t n, int B,
                               const int64_t *sites, int nsites, double *site_corr, int stride, int k,
-                              hipStream_t st);
+                              hipStream_t st, int apart = 0);
 // operators stored as CSR in H's row order (tbpm_build_operator), one vector:
 //   op_apply: y = A x
 //   op_dot:   partials[blk][0..1] = sum over the rows of workgroup blk of conj(u_i) (A v)_i

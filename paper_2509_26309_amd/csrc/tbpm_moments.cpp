@@ -320,17 +320,13 @@ struct MomentRun {
             const int64_t stride = (int64_t)shape.grid * B * 4;
             // psi0 itself is p_0; init writes the same state to both of its targets
             if (steps) {
-                for (int b = 0; b < B; ++b) {
-                    void *q = static_cast<char *>(va) + (size_t)b * n * elem;
-                    SiteRows sr{};
-                    if (!site_rows.empty())
-                        sr.r[0] = site_rows[(size_t)r0 + b];
-                    MOM_HIP(site_rows.empty()
-                                ? launch_init_random(ham->dtype, q, q, ham->n, 1, p.seed,
-                                                     (int64_t)p.first_vector + r0 + b,
-                                                     ham->patched ? ham->old_of_new : nullptr, st)
-                                : launch_init_sites(ham->dtype, q, q, ham->n, 1, sr, st));
-                }
+                SiteRows sr{};
+                for (int b = 0; b < B && !site_rows.empty(); ++b)
+                    sr.r[b] = site_rows[(size_t)r0 + b];
+                MOM_HIP(site_rows.empty()
+                            ? launch_init_random(ham->dtype, va, va, ham->n, B, p.seed, (int64_t)p.first_vector + r0,
+                                                 ham->patched ? ham->old_of_new : nullptr, st, 1)
+                            : launch_init_sites(ham->dtype, va, va, ham->n, B, sr, st, 1));
             } else if (!site_rows.empty()) {
                 SiteRows sr{};
                 for (int b = 0; b < B; ++b)

@@ -11,6 +11,15 @@
 
 namespace tbpm {
 
+// Where a block of B vectors of n rows holds element (i, b): interleaved, [n][B], or
+// one vector after another, [B][n] (`apart`), each in one launch for the whole block.
+__device__ __forceinline__ int64_t at_row(int64_t e, int64_t n, int B, int apart) { return apart ? e % n : e / B; }
+__device__ __forceinline__ int at_vec(int64_t e, int64_t n, int B, int apart) { return (int)(apart ? e / n : e % B); }
+__device__ __forceinline__ int64_t at_elem(int64_t i, int b, int64_t n, int B, int apart)
+{
+    return apart ? (int64_t)b * n + i : i * B + b;
+}
+
 // ---- random-phase initial states -----------------------------------------------------
 // SplitMix64 (Steele, Lea & Flood, OOPSLA 2014): state += golden gamma, output
 // is a 64-bit mixing of the state.  Vector r's key is output r+1 of the
@@ -29,15 +38,16 @@ constexpr uint64_t SM64_GAMMA = 0x9E3779B97F4A7C15ull;
 // receives the same state as the original one, reordered
 template <typename T>
 __global__ __launch_bounds__(WG) void init_random_kernel(T *psi0, T *p, int64_t n, int B, uint64_t seed, int64_t r0,
-                                                         const int32_t *perm)
+                                                         const int32_t *perm, int apart)
 {
     using E = Elem<T>;
     const int64_t total = n * B;
     const double amp = 1.0 / sqrt((double)n);
     const double two_pi = 6.283185307179586476925286766559;
     for (int64_t e = (int64_t)blockIdx.x * WG + threadIdx.x; e < total; e += (int64_t)gridDim.x * WG) {
-        const int64_t i = perm ? (int64_t)perm[e / B] : e / B;
-        const int64_t r = r0 + e % B;
+        const int64_t row = at_row(e, n, B, apart);
+        const int64_t i = perm ? (int64_t)perm[row] : row;
+        const int64_t r = r0 + at_vec(e, n, B, apart);
         const uint64_t key = sm64_mix(seed + (uint64_t)(r + 1) * SM64_GAMMA);
         const uint64_t bits = sm64_mix(key + (uint64_t)(i + 1) * SM64_GAMMA);
         const double u = (double)(bits >> 11) * 0x1.0p-53;
@@ -51,26 +61,27 @@ __global__ __launch_bounds__(WG) void init_random_kernel(T *psi0, T *p, int64_t 
 
 
 hipError_t launch_init_random(int dtype, void *psi0, void *p, int64_t n, int B, uint64_t seed, int64_t r0,
-                              const int32_t *perm, hipStream_t st)
+                              const int32_t *perm, hipStream_t st, int apart)
 {
     const int g = elem_grid(n * B);
     if (dtype == TBPM_C128)
         hipLaunchKernelGGL(init_random_kernel<d2>, dim3(g), dim3(WG), 0, st, (d2 *)psi0, (d2 *)p, n, B, seed, r0,
-                           perm);
+                           perm, apart);
     else
         hipLaunchKernelGGL(init_random_kernel<f2>, dim3(g), dim3(WG), 0, st, (f2 *)psi0, (f2 *)p, n, B, seed, r0,
-                           perm);
+                           perm, apart);
     return hipGetLastError();
 }
 
 // vector b = e_{rows[b]} (stored row order); psi0 and p may be the same buffer
 template <typename T>
-__global__ __launch_bounds__(WG) void init_sites_kernel(T *psi0, T *p, int64_t n, int B, SiteRows rows)
+__global__ __launch_bounds__(WG) void init_sites_kernel(T *psi0, T *p, int64_t n, int B, SiteRows rows,
+                                                        int apart)
 {
     const int64_t total = n * B;
     for (int64_t e = (int64_t)blockIdx.x * WG + threadIdx.x; e < total; e += (int64_t)gridDim.x * WG) {
-        const int64_t i = e / B;
-        const int b = (int)(e % B);
+        const int64_t i = at_row(e, n, B, apart);
+        const int b = at_vec(e, n, B, apart);
         T v{};
         if (i == rows.r[b])
             v.x = 1;
@@ -79,28 +90,31 @@ __global__ __launch_bounds__(WG) void init_sites_kernel(T *psi0, T *p, int64_t n
     }
 }
 
-hipError_t launch_init_sites(int dtype, void *psi0, void *p, int64_t n, int B, const SiteRows &rows, hipStream_t st)
+hipError_t launch_init_sites(int dtype, void *psi0, void *p, int64_t n, int B, const SiteRows &rows, hipStream_t st,
+                             int apart)
 {
     if (B < 1 || B > 64 || n <= 0)
         return hipErrorInvalidValue;
     const int g = elem_grid(n * B);
     if (dtype == TBPM_C128)
-        hipLaunchKernelGGL(init_sites_kernel<d2>, dim3(g), dim3(WG), 0, st, (d2 *)psi0, (d2 *)p, n, B, rows);
+        hipLaunchKernelGGL(init_sites_kernel<d2>, dim3(g), dim3(WG), 0, st, (d2 *)psi0, (d2 *)p, n, B, rows, apart);
     else
-        hipLaunchKernelGGL(init_sites_kernel<f2>, dim3(g), dim3(WG), 0, st, (f2 *)psi0, (f2 *)p, n, B, rows);
+        hipLaunchKernelGGL(init_sites_kernel<f2>, dim3(g), dim3(WG), 0, st, (f2 *)psi0, (f2 *)p, n, B, rows, apart);
     return hipGetLastError();
 }
 
-// src: complex128 [B][n] (vector-major, original order) -> psi0, p: [n][B] in
-// storage precision and stored row order
+// src: complex128 [B][n] (vector-major, original order) -> psi0, p: [n][B] (apart:
+// [B][n]) in storage precision and stored row order
 template <typename T>
-__global__ __launch_bounds__(WG) void pack_kernel(const d2 *src, T *psi0, T *p, int64_t n, int B, const int32_t *perm)
+__global__ __launch_bounds__(WG) void pack_kernel(const d2 *src, T *psi0, T *p, int64_t n, int B, const int32_t *perm,
+                                                  int apart)
 {
     using E = Elem<T>;
     const int64_t total = n * B;
     for (int64_t e = (int64_t)blockIdx.x * WG + threadIdx.x; e < total; e += (int64_t)gridDim.x * WG) {
-        const int64_t i = perm ? (int64_t)perm[e / B] : e / B;
-        const int64_t b = e % B;
+        const int64_t row = at_row(e, n, B, apart);
+        const int64_t i = perm ? (int64_t)perm[row] : row;
+        const int64_t b = at_vec(e, n, B, apart);
         const T v = E::from_d(src[b * n + i]);
         psi0[e] = v;
         p[e] = v;
@@ -108,15 +122,15 @@ __global__ __launch_bounds__(WG) void pack_kernel(const d2 *src, T *psi0, T *p, 
 }
 
 hipError_t launch_pack_states(int dtype, const double *src, void *psi0, void *p, int64_t n, int B, const int32_t *perm,
-                              hipStream_t st)
+                              hipStream_t st, int apart)
 {
     const int g = elem_grid(n * B);
     if (dtype == TBPM_C128)
         hipLaunchKernelGGL(pack_kernel<d2>, dim3(g), dim3(WG), 0, st, (const d2 *)src, (d2 *)psi0, (d2 *)p, n, B,
-                           perm);
+                           perm, apart);
     else
         hipLaunchKernelGGL(pack_kernel<f2>, dim3(g), dim3(WG), 0, st, (const d2 *)src, (f2 *)psi0, (f2 *)p, n, B,
-                           perm);
+                           perm, apart);
     return hipGetLastError();
 }
 
@@ -143,18 +157,20 @@ hipError_t launch_unpack_state(int dtype, const void *src, double *dst, int64_t 
 
 // ---- correlation sums -------------------------------------------------------------------
 
-// partials[blk][b] = (sum conj(psi0) v, sum |v|^2) over the rows of workgroup blk
+// partials[blk][b] = (sum conj(psi0) v, sum |v|^2) over the rows of workgroup blk;
+// workgroups blockIdx.y of gridDim.y share the vectors
 template <typename T>
 __global__ __launch_bounds__(WG) void dot_partials_kernel(const T *psi0, const T *v, int64_t n, int B,
-                                                          double *partials)
+                                                          double *partials, int apart)
 {
     using E = Elem<T>;
     __shared__ double red[WG][3];
-    for (int b = 0; b < B; ++b) {
+    for (int b = blockIdx.y; b < B; b += gridDim.y) {
         double s0 = 0.0, s1 = 0.0, s2 = 0.0;
         for (int64_t i = (int64_t)blockIdx.x * WG + threadIdx.x; i < n; i += (int64_t)gridDim.x * WG) {
-            const d2 p = E::to_d(psi0[i * B + b]);
-            const d2 o = E::to_d(v[i * B + b]);
+            const int64_t e = at_elem(i, b, n, B, apart);
+            const d2 p = E::to_d(psi0[e]);
+            const d2 o = E::to_d(v[e]);
             s0 += p.x * o.x + p.y * o.y;
             s1 += p.x * o.y - p.y * o.x;
             s2 += o.x * o.x + o.y * o.y;
@@ -183,14 +199,15 @@ __global__ __launch_bounds__(WG) void dot_partials_kernel(const T *psi0, const T
 }
 
 hipError_t launch_dot_partials(int dtype, const void *psi0, const void *v, int64_t n, int B, double *partials,
-                               int grid, hipStream_t st)
+                               int grid, hipStream_t st, int apart)
 {
+    const dim3 g((unsigned)grid, (unsigned)(apart ? B : 1));    // (interleaved vectors share their lines)
     if (dtype == TBPM_C128)
-        hipLaunchKernelGGL(dot_partials_kernel<d2>, dim3(grid), dim3(WG), 0, st, (const d2 *)psi0, (const d2 *)v,
-                           n, B, partials);
+        hipLaunchKernelGGL(dot_partials_kernel<d2>, g, dim3(WG), 0, st, (const d2 *)psi0, (const d2 *)v, n, B,
+                           partials, apart);
     else
-        hipLaunchKernelGGL(dot_partials_kernel<f2>, dim3(grid), dim3(WG), 0, st, (const f2 *)psi0, (const f2 *)v,
-                           n, B, partials);
+        hipLaunchKernelGGL(dot_partials_kernel<f2>, g, dim3(WG), 0, st, (const f2 *)psi0, (const f2 *)v, n, B,
+                           partials, apart);
     return hipGetLastError();
 }
 
@@ -552,7 +569,7 @@ hipError_t launch_qe_accumulate(int dtype, const void *psi, int64_t n, double *q
 template <typename T>
 __global__ __launch_bounds__(WG) void ldos_gather_kernel(const T *psi0, const T *v, int64_t n, int B,
                                                          const int64_t *sites, int nsites, d2 *site_corr,
-                                                         int stride, int k)
+                                                         int stride, int k, int apart)
 {
     using E = Elem<T>;
     const int s = blockIdx.x * WG + threadIdx.x;
@@ -563,25 +580,26 @@ __global__ __launch_bounds__(WG) void ldos_gather_kernel(const T *psi0, const T 
         return;
     d2 acc{0.0, 0.0};
     for (int b = 0; b < B; ++b) {
-        const d2 p = E::to_d(psi0[i * B + b]);
-        const d2 o = E::to_d(v[i * B + b]);
+        const int64_t e = at_elem(i, b, n, B, apart);
+        const d2 p = E::to_d(psi0[e]);
+        const d2 o = E::to_d(v[e]);
         acc += d2{p.x * o.x + p.y * o.y, p.x * o.y - p.y * o.x};
     }
     site_corr[(int64_t)s * stride + k] += acc;
 }
 
 hipError_t launch_ldos_gather(int dtype, const void *psi0, const void *v, int64_t n, int B, const int64_t *sites,
-                              int nsites, double *site_corr, int stride, int k, hipStream_t st)
+                              int nsites, double *site_corr, int stride, int k, hipStream_t st, int apart)
 {
     const int g = (nsites + WG - 1) / WG;
     if (g == 0)
         return hipSuccess;
     if (dtype == TBPM_C128)
         hipLaunchKernelGGL(ldos_gather_kernel<d2>, dim3(g), dim3(WG), 0, st, (const d2 *)psi0, (const d2 *)v, n, B,
-                           sites, nsites, (d2 *)site_corr, stride, k);
+                           sites, nsites, (d2 *)site_corr, stride, k, apart);
     else
         hipLaunchKernelGGL(ldos_gather_kernel<f2>, dim3(g), dim3(WG), 0, st, (const f2 *)psi0, (const f2 *)v, n, B,
-                           sites, nsites, (d2 *)site_corr, stride, k);
+                           sites, nsites, (d2 *)site_corr, stride, k, apart);
     return hipGetLastError();
 }
 

@@ -1,4 +1,6 @@
-"""Storing uneven rows with a plan of tiles pays for itself in one short run: H stored by
+"""Calls whose fixed part must not outgrow what tiles save, as times of the same process.
+
+Storing uneven rows with a plan of tiles pays for itself in one short run: H stored by
 the library's choice and 16 time steps of four vectors take no longer than with the CSR
 named, which has no plan (about 9 ms against 12;
 22 while the tiles were grown by one thread and every depth was tried on all of them)."""
@@ -29,3 +31,27 @@ def test_one_short_run_on_a_fresh_h():
         runs = [(once(T.TBPM_FMT_AUTO), once(T.TBPM_FMT_CSR)) for _ in range(6)]
     assert all(auto[1] and not named[1] for auto, named in runs)
     assert min(auto[0] for auto, _ in runs) <= min(named[0] for _, named in runs)
+
+
+def test_wide_blocks_of_a_small_sample():
+    """Local correlations of a block of 64 vectors on 512 rows by tiles: starting a block and
+    gathering the sites is a launch each for the whole block, so the tiles take no longer than
+    the term kernels (launched with kernel timing on)."""
+    from paper_2509_26309_amd import tbpm as T
+    from tb_inputs import graphene, sample_sites
+    lat = graphene(16, disorder_w=1.0, seed=1)
+    with T.Context(0) as ctx:
+        ham = ctx.build(lat)
+        p, keep = T.make_params(9.0, 32, 64, block=64, seed=1, sites=sample_sites(lat.n, 50, 3))
+        took = {}
+        for timing in (False, True):
+            T.tbpm_ctx_set_profiling(ctx.handle, timing)
+            runs = []
+            for _ in range(8):
+                t = time.perf_counter()
+                T.tbpm_propagate_dos(ctx.handle, ham, p)
+                runs.append(time.perf_counter() - t)
+            took[timing] = min(runs)
+        assert T.tbpm_ham_tiles(ham, 64)["products"] > 0
+        T.tbpm_ham_destroy(ham)
+    assert took[False] <= took[True], took
