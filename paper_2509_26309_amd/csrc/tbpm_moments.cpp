@@ -203,18 +203,26 @@ struct MomentRun {
     }
 
     // modelled time (us) of the kmax products on every block: by tiles (the sums
-    // of each product add about a fifth; half of a whole launch's time is its
-    // prologue, which a launch of fewer products pays as well), and by the
-    // product kernels (launches of 2.9 us, half of 6.5 on patches, at least; else
-    // their bytes at 4.3 TB/s, CSR 4.1)
+    // of each product add about a fifth, and more where the kernel spills registers
+    // for them; half of a whole launch's time is its prologue, which a launch of
+    // fewer products pays as well), and by the product kernels (launches of 2.9 us
+    // at least, else their bytes at 4.3 TB/s, CSR 4.1; pairs on patches 6.5 us and
+    // their bytes at 4.6 TB/s).  One vector, complex128, us a product by tiles
+    // and by pairs: clean graphene (spilling) 180,000 rows 3.3 and 4.5, 8.4M 82
+    // and 68; clean bilayer (spilling) 160,000 rows 4.9 and 4.5, 4.2M 68 and 41;
+    // disordered bilayer (spilling) 1M 13 and 16, 4.2M 52 and 47; disordered
+    // graphene 8.4M 34 and 78.
     double steps_us() const
     {
         const int depth = ham->steps.depth;
+        const tbpm_ham::StepPlan &s = ham->steps;
+        double sums = 1.2;
+        if (ham->dtype == TBPM_C128 && s.real)
+            sums *= s.w == 3 ? 1.75 : s.w == 4 && !s.self ? 2.3 : s.w == 5 && s.self ? 1.65 : 1.0;
         const double launches = 0.5 * ((kmax + depth - 1) / depth + (double)kmax / depth);
         double us = 0.0;
         for (auto &blk : blocks)
-            us += 1.2 * launches * std::max(1.0, (double)ham->steps.ntiles * blk.second / STEP_SLOTS) *
-                  ham->steps.tile_us;
+            us += sums * launches * std::max(1.0, (double)s.ntiles * blk.second / STEP_SLOTS) * s.tile_us;
         return us;
     }
     double products_us() const
@@ -233,7 +241,7 @@ struct MomentRun {
             else
                 one = std::max(2.9, n * (ham->ell_w * (e + 4.0) + 3.0 * e * B) / 4.3e6);
             if (pairs && B == 1)                    // product 0 alone, then pairs
-                us += one + (kmax - 1) * std::max(6.5, n * (hp + 4.0 * e) / 4.3e6) / 2;
+                us += one + (kmax - 1) * (6.5 + n * (hp + 4.0 * e) / 4.6e6) / 2;
             else
                 us += one * kmax;
         }

@@ -1,4 +1,5 @@
-"""Calls whose fixed part must not outgrow what tiles save, as times of the same process.
+"""Calls that tiles must not make slower than the kernels before them, as times of the
+same process.
 
 Storing uneven rows with a plan of tiles pays for itself in one short run: H stored by
 the library's choice and 16 time steps of four vectors take no longer than with the CSR
@@ -55,3 +56,27 @@ def test_wide_blocks_of_a_small_sample():
         assert T.tbpm_ham_tiles(ham, 64)["products"] > 0
         T.tbpm_ham_destroy(ham)
     assert took[False] <= took[True], took
+
+
+@pytest.mark.parametrize("cells", [512, 1024])
+def test_moments_by_the_faster_kernels(cells):
+    """Moments of the clean bilayer in complex128 (the tiles' kernel spills registers for its
+    sums there): no slower than by pairs of products, which kernel timing asks for."""
+    from paper_2509_26309_amd import tbpm as T
+    from tb_inputs import bilayer
+    lat = bilayer(cells)
+    with T.Context(0) as ctx:
+        ham = ctx.build(lat)
+        p, _ = T.make_params(9.0, 0, 1, seed=1)
+        took = {}
+        for timing in (False, True):
+            T.tbpm_ctx_set_profiling(ctx.handle, timing)
+            runs = []
+            for _ in range(8):
+                t = time.perf_counter()
+                T.tbpm_chebyshev_moments(ctx.handle, ham, p, 300)
+                runs.append(time.perf_counter() - t)
+            took[timing] = min(runs)
+        assert T.tbpm_ham_tiles(ham, 1)["tiles"] > 0
+        T.tbpm_ham_destroy(ham)
+    assert took[False] <= 1.1 * took[True], took
