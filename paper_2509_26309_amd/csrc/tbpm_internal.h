@@ -48,7 +48,6 @@ struct TermArgs {
     double scale;
     double ca_re, ca_im;
     double cb_re, cb_im;
-    double cc_re, cc_im;
     double *partials;        // [grid][B][4] (LAST, MOM0, MOM)
     // optional: process only the rows of the patches plist[0..pcount) of a
     // patch-reordered H (patch q: rows patch_ptr[q] .. patch_ptr[q+1]-1, at most
@@ -57,10 +56,16 @@ struct TermArgs {
     int64_t pcount;
     const int32_t *patch_ptr;
     int32_t patch_tiles;
+    int32_t vdiag_real;      // vdiag (below) holds real parts only (double or float)
     // Clenshaw mode (FIRST, MID, LAST kinds)
     int32_t cl;
     int32_t no_y;
-    const void *psi;
+    union {
+        const void *psi;     // Clenshaw
+        struct {
+            double cc_re, cc_im;    // forward: c_c
+        };
+    };
     // patch-reordered H: number of patches (with patch_ptr), patch-local
     // columns [w][ld] and the halo lists, for the kernel that stages each
     // patch's x in LDS (KernelShape::staged)
@@ -73,8 +78,10 @@ struct TermArgs {
     const uint32_t *vidx;
     const void *vtab;
     const void *vdiag;
-    int32_t vdiag_real;      // vdiag holds real parts only (double or float)
 };
+// (240 bytes: past them a launch reads a line of arguments more, 0.15 us of the 4 that
+// small samples' launches take)
+static_assert(sizeof(TermArgs) == 240, "");
 
 struct KernelShape {
     int B;       // vectors per block
