@@ -152,8 +152,12 @@ const char *tbpm_status_string(tbpm_status s);
  * and adds the elapsed times to per-kind totals (kind 0: first term,
  * 1: middle terms, 2: last term with the correlation sums).  The calls then
  * run one or two terms to a launch, also where they would otherwise run
- * several products (results differ by rounding alone).  Enabling resets
- * the totals.  *launches receives the number of kernel launches timed. */
+ * several products (results differ by rounding alone).  Chebyshev moments are
+ * timed as product 0, the others (on TBPM_FMT_PATCH pairs of products) and a
+ * single product left over; on the other formats several products may share a
+ * launch and are counted one by one.  Served requests are not timed.  Enabling
+ * resets the totals.  *launches receives the number of kernel launches timed
+ * (moments: pairs or products). */
 tbpm_status tbpm_ctx_set_profiling(tbpm_ctx *ctx, int32_t enable);
 /* HIP graphs for the time steps of tbpm_propagate_dos / _states / _sites:
  * mode 0 never; 1 (default) when the problem is small enough for launch

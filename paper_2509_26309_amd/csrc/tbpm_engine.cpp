@@ -39,12 +39,15 @@ int choose_block(const tbpm_ham *ham, const tbpm_params *p, bool pairs_ok)
         return std::min(64, pow2_floor(p->block));
     if (ham->tuned_block > 0)
         return std::min(ham->tuned_block, pow2_floor(std::max(1, p->num_vectors)));
-    // patch-reordered H: one vector at a time takes the fused pairs, which
-    // move fewer bytes per vector and term than any block of complex128
-    // vectors (3 vector passes per term against 5, H being small); complex64
-    // blocks of 8 and 16 have the staged kernel, and blocks of 8 the fused
-    // pairs where H allows them (a block of 16 splits every 128-byte row
-    // between two workgroups: 10% slower per vector on the AB bilayer)
+    // patch-reordered H, by what the term kernels make of a width: one vector at
+    // a time takes the fused pairs, which move fewer bytes per vector and term
+    // than any block of complex128 vectors (2.5 vector passes per term against
+    // 11/3, H being small); complex64 blocks of 8 and 16 have the staged kernel,
+    // and blocks of 8 the fused pairs where H allows them (a block of 16 splits
+    // every 128-byte row between two workgroups: 10% slower per vector on the AB
+    // bilayer).  Tiles run each vector by itself: there a width only says how many
+    // tiles a launch holds (four complex128 vectors of 131,000 rows: 2.85 ms one at
+    // a time, 1.66 ms as a block, which params->block or the autotuner can ask for)
     if (ham->patched) {
         if (ham->dtype == TBPM_C128)
             return 1;

@@ -165,9 +165,9 @@ struct Job {
     tbpm_status finish(double *corr, double *norms, double *ldos, double *corr_mean = nullptr);
 
   private:
-    // vectors of the current block that are interleaved, and the start of the
-    // group that vector b (a multiple of it) begins: blocks run by `steps` hold
-    // their vectors one after another
+    // vectors of the current block that are interleaved (blocks run by `steps`
+    // hold theirs one after another), and the start of the group that vector b, a
+    // multiple of it, begins
     int group() const { return steps ? 1 : shape.B; }
     void *vec(void *base, int b) const { return static_cast<char *>(base) + (size_t)b * (size_t)ham->n * elem; }
     void spare_buffers(void *out[3]) const;   // the rotating vectors not in P, Q, O (fixed order)

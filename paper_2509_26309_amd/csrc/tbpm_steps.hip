@@ -11,14 +11,18 @@
 // launch reads the closure's vectors once and writes the tile's once for K
 // products, at the price of the closure's extra rows.
 //
-// What bounds it: LDS bandwidth and issue rate (about one clock per CU for a
-// row and product: W gathers, an old value and a store of 16 bytes), no longer
-// memory; and, where a sample has fewer tiles than the card takes at once (512),
-// the latency of a launch: about 10 us for the closure's rows and H, waited for
-// in turn, plus the products.
+// What bounds it: memory first where the vectors stream from it (33.5M rows,
+// complex128, 10 products a launch: 4.77 GB in 1.19 ms, 4.0 TB/s or 82% of a large
+// copy's rate, with the LDS active 46% and the vector ALUs 36% of a CU's busy
+// cycles), the wait for a closure's loads not being covered entirely by the CU's
+// second workgroup; LDS bandwidth and issue rate (about one clock per CU for a row
+// and product: W gathers, an old value and a store of 16 bytes) where they come
+// from the last-level cache; and, where a sample has fewer tiles than the card
+// takes at once (512), the latency of a launch: about 10 us for the closure's
+// rows and H, waited for in turn, plus the products.
 // Measured, against the term and pair kernels: graphene 2048^2, complex128, 16
 // steps: 25.7 -> 10.5 ms; graphene 64^2 (one launch a step), 256 steps: 13.9 ->
-// 3.6 ms; AB bilayer 1024x512, complex64, blocks of 16: 46.5 -> 31.5 ms; graphene
+// 3.6 ms; AB bilayer 1024x512, complex64, blocks of 16: 46.5 -> 31.4 ms; graphene
 // 640x480 with 20% vacancies (CSR), complex128 blocks of 4: 11.0 -> 2.7 ms.
 // Rows of 12 (third neighbours): five hops reach too far, and the staged term
 // kernel stays.
@@ -26,9 +30,10 @@
 // Plan (StepPlan): tiles of at most 1024 rows; per tile the closure's rows in
 // order of hop distance (the tile's own first, each layer ascending), the
 // number of rows within d hops for d <= depth, and 16-bit local columns of the
-// rows within depth - 1 hops (as byte offsets into the closure's vector), and a byte per slot that selects its value: its
-// value table index, or without a table its stored slot.  step_plan_kernel
-// builds it on the device by breadth-first search from the stored ELL columns.
+// rows within depth - 1 hops (as byte offsets into the closure's vector), and a
+// byte per slot that selects its value: its value table index, or without a
+// table its stored slot.  step_plan_kernel builds it on the device by
+// breadth-first search from the stored ELL columns.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -314,7 +319,10 @@ constexpr int STW_OWN = 1024 / STW;        // rows of the tile per lane
 // Closure rows per lane: H's columns and values of a lane's rows, and their
 // p_m and p_m-1, take at most 92 (complex64: 84, its rows need more besides) of
 // the 128 registers that two workgroups leave, beyond which some row lengths
-// spill; two buffers of the closure's rows take at most half the LDS.
+// spill; two buffers of the closure's rows take at most half the LDS.  (The series
+// spills for none.  The moments, whose sums need registers too, spill 92, 138 and
+// 50 registers for complex128 rows of 3, of 4 without and of 5 with the own
+// column, real values, and 2 for complex64 rows of 4 with complex ones.)
 template <typename T, int W, bool REAL>
 constexpr int step_rows()
 {
