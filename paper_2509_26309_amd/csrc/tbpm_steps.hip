@@ -12,8 +12,8 @@
 // products, at the price of the closure's extra rows.
 //
 // What bounds it: memory first where the vectors stream from it (33.5M rows,
-// complex128, 10 products a launch: 4.77 GB in 1.19 ms, 4.0 TB/s or 82% of a large
-// copy's rate, with the LDS active 46% and the vector ALUs 36% of a CU's busy
+// complex128, 10 or 9 products a launch: 4.77 GB in 1.24 ms, 3.8 TB/s or 79% of a
+// large copy's rate, with the LDS active 46% and the vector ALUs 36% of a CU's busy
 // cycles), the wait for a closure's loads not being covered entirely by the CU's
 // second workgroup; LDS bandwidth and issue rate (about one clock per CU for a row
 // and product: W gathers, an old value and a store of 16 bytes) where they come
