@@ -40,7 +40,8 @@ struct TermArgs {
     int64_t n;
     int64_t ld;              // ELL slot stride (rows, padded)
     int32_t w;               // ELL width
-    int32_t rp64;            // 1: row pointer is int64
+    int16_t rp64;            // 1: row pointer is int64
+    int16_t vdiag_real;      // vdiag (below) holds real parts only (double or float)
     const void *x;
     void *y;
     void *out;
@@ -56,20 +57,14 @@ struct TermArgs {
     int64_t pcount;
     const int32_t *patch_ptr;
     int32_t patch_tiles;
-    int32_t vdiag_real;      // vdiag (below) holds real parts only (double or float)
     // Clenshaw mode (FIRST, MID, LAST kinds)
     int32_t cl;
     int32_t no_y;
-    union {
-        const void *psi;     // Clenshaw
-        struct {
-            double cc_re, cc_im;    // forward: c_c
-        };
-    };
-    // patch-reordered H: number of patches (with patch_ptr), patch-local
-    // columns [w][ld] and the halo lists, for the kernel that stages each
-    // patch's x in LDS (KernelShape::staged)
-    int64_t npatch;
+    int32_t npatch;          // patch-reordered H: number of patches (with patch_ptr)
+    const void *psi;         // Clenshaw
+    double cc_re, cc_im;     // (forward: c_c)
+    // patch-reordered H: patch-local columns [w][ld] and the halo lists, for the
+    // kernel that stages each patch's x in LDS (KernelShape::staged)
     const uint64_t *lcol;
     const int32_t *halo_ptr, *halo_rows;
     // value table (staged kernel; null: values from val): one-byte indices,
@@ -79,8 +74,11 @@ struct TermArgs {
     const void *vtab;
     const void *vdiag;
 };
-// (240 bytes: past them a launch reads a line of arguments more, 0.15 us of the 4 that
-// small samples' launches take)
+// 240 bytes, and what few kinds need lies behind what every launch reads: one more line
+// of arguments, or `partials` in the third, costs small samples' launches 0.15 to 0.25
+// us of 4 to 5.  No pointer may share its place with a number: the compiler then no
+// longer knows that it points to global memory and waits for every load before each use
+// (0.07 us of the 1.8 of Clenshaw's launches).
 static_assert(sizeof(TermArgs) == 240, "");
 
 struct KernelShape {
