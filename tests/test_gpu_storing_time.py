@@ -80,3 +80,15 @@ def test_moments_by_the_faster_kernels(cells):
         assert T.tbpm_ham_tiles(ham, 1)["tiles"] > 0
         T.tbpm_ham_destroy(ham)
     assert took[False] <= 1.1 * took[True], took
+
+
+def test_rows_per_tile_of_a_sample_with_gaps():
+    """What growing tiles in ranges leaves over shares tiles: at most 1.4 times as many as
+    full ones (1.6 while only pieces under an eighth of a tile did)."""
+    from paper_2509_26309_amd import tbpm as T
+    lat = supercell(cell_by_name("graphene"), 772, 462, vacancy_p=0.3, seed=3)
+    with T.Context(0) as ctx:
+        ham = ctx.build(lat, dtype=T.TBPM_C64)
+        tiles = T.tbpm_ham_tiles(ham, 1)["tiles"]
+        T.tbpm_ham_destroy(ham)
+    assert 0 < tiles <= 1.4 * lat.n / 1024
